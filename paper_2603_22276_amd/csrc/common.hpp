@@ -149,6 +149,26 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int trace_id, hipStream_t stream)
 // two independent problems of the same kind (layouts, epilogue) in one launch
 hipError_t launch_gemm_bf16_pair(const GemmArgs& a, const GemmArgs& b, int trace_id, hipStream_t stream);
 
+// ---- forward of a few tokens (16-bit storage) ----------------------------------------------------
+constexpr int64_t FEW_TOKENS_MAX = 64;
+struct FewTokensArgs {
+    const bf16_t* x;        // [T, K]
+    const bf16_t* w;        // [N, K]: A for the h launch, W for the y launch
+    int T, N, K, ksplit;
+    float* part;            // h launch: [ksplit][T][N] fp32
+    // y launch
+    const float* h_part;    // [h_slices][T][r]
+    int h_slices, r;
+    const bf16_t* b;        // [N, r]
+    float s, eps;
+    const float *m, *c;     // [N]
+    const bf16_t* bias;     // [N] or nullptr
+    bf16_t *y, *inner, *h_out;   // [T, N]; [T, N] or nullptr; [T, r] or nullptr
+};
+int few_tokens_h_slices(int64_t tokens, int64_t r, int64_t d_in);
+hipError_t launch_few_tokens_h(const FewTokensArgs& a, int dt, hipStream_t st);
+hipError_t launch_few_tokens_y(const FewTokensArgs& a, int dt, hipStream_t st);
+
 // ---- fp32 GEMM (simple LDS-tiled VALU kernel; the fp32 configuration is small) ------------------
 struct SgemmSeg {
     const float* a;

@@ -1,0 +1,264 @@
+// Forward of a few tokens (decode): every product streams its weight matrix once and multiplies it with a handful
+// of token rows, so the launches are bound by reading W (2 d_out d_in bytes) and by their own latency, not by MFMAs.
+//
+//   few_tokens_kernel<..., FINAL = false>   h = x A^T, K cut over workgroups and waves, fp32 slices to scratch
+//   few_tokens_kernel<..., FINAL = true>    y = g (.) (x W^T + s h B^T) (+ bias), g = m / max(c, eps) formed here, h summed
+//                                           from its slices; optionally inner and the saved h
+//
+// The 128 x 128 tiles of the other products would give such a call d_out / 128 workgroups (32 for 256 CUs at
+// d_out = 4096).  Here a workgroup owns 16 or 32 weight rows and its four waves split K, each streaming its own
+// share through a private LDS ring (buffer_load ... lds, 128-byte row segments, no barrier: only its own vmcnt), the
+// token rows beside them in the same ring; the four partial tiles meet in LDS at the end.
+#include "lds_tile.hpp"
+
+namespace dora {
+namespace {
+
+constexpr int WAVES = 4;
+constexpr int STEP_K = 64;   // k per ring slot: row segments of one 128-byte line (256-byte ones measured the same)
+
+// 16 bytes per lane from memory into 1 KB of LDS
+__device__ __forceinline__ void load_1k(char* lds, __amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t soffset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr_t)lds, 16, off, soffset, 0, 0);
+}
+
+// TB: blocks of 16 tokens; MR: blocks of 16 weight rows; DEPTH: ring slots of a wave
+template <int TB, int MR, int DEPTH, bool FINAL, int DT>
+__global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
+{
+    typedef Elem16<DT> E;
+    constexpr int ROWS = MR * 16, TOK = TB * 16;
+    constexpr int SLOT_BYTES = (ROWS + TOK) * STEP_K * 2;
+    constexpr int CPR = STEP_K / 8, RPL = 64 / CPR;    // 16-byte chunks of a row segment, rows per wave-wide load
+    constexpr int LPS = (ROWS + TOK) / RPL;            // wave-wide loads per ring slot
+    constexpr int LPB = 16 / RPL;                      // of them per block of 16 rows
+    constexpr int KSTEPS = STEP_K / 32;                // MFMA k-steps per ring slot
+    constexpr int RED_LD = ROWS + 4;
+    constexpr int RING_BYTES = WAVES * DEPTH * SLOT_BYTES, RED_BYTES = WAVES * TOK * RED_LD * 4;
+    constexpr int LDS_BYTES = RING_BYTES > RED_BYTES ? RING_BYTES : RED_BYTES;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
+    static_assert((DEPTH - 1) * LPS <= 63, "vmcnt is a 6-bit counter");
+    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int group = (int)blockIdx.x / p.ksplit, z = (int)blockIdx.x % p.ksplit;
+    const int n0 = group * ROWS;
+    const int T = p.T, N = p.N, K = p.K;
+
+    // this wave's share of the K steps
+    const int steps = (K + STEP_K - 1) / STEP_K;
+    const int parts = p.ksplit * WAVES, part = z * WAVES + wave;
+    const int s_begin = (int)((int64_t)steps * part / parts), s_end = (int)((int64_t)steps * (part + 1) / parts);
+
+    // descriptors of the weight rows of this group and of the token rows; rows past the end lie beyond them and load zeros
+    const int w_rows = N - n0 < ROWS ? N - n0 : ROWS;
+    __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.w + (int64_t)n0 * K), 0,
+                                                                  (int)(uint32_t)((int64_t)w_rows * K * 2), 0x00020000);
+    __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.x), 0, (int)(uint32_t)((int64_t)T * K * 2),
+                                                                  0x00020000);
+    // lane -> (row, chunk) of load i of a 16-row block
+    uint32_t vo[LPB];
+    int kl[LPB];
+#pragma unroll
+    for (int i = 0; i < LPB; ++i) {
+        const int row = i * RPL + lane / CPR;
+        kl[i] = ((lane % CPR) ^ kc_swizzle<STEP_K>(row)) * 8;
+        vo[i] = (uint32_t)(row * K + kl[i]) * 2u;
+    }
+    char* const ring = smem + wave * (DEPTH * SLOT_BYTES);
+    auto issue = [&](int s, int slot) {
+        char* tile = ring + slot * SLOT_BYTES;
+        const int k0 = s * STEP_K;
+        uint32_t v[LPB];
+#pragma unroll
+        for (int i = 0; i < LPB; ++i) v[i] = (s < s_end && k0 + kl[i] < K) ? vo[i] : 0xFFFFFFFFu;
+        static_for<LPS>([&](auto it) {
+            constexpr int i = decltype(it)::value;
+            constexpr int blk = i / LPB;               // 16-row block of the slot: weights first, then tokens
+            constexpr int tok_blk = blk < MR ? 0 : blk - MR;
+            const uint32_t so = (uint32_t)(((blk < MR ? blk : tok_blk) * 16 * (int64_t)K + k0) * 2);
+            load_1k(tile + i * 1024, blk < MR ? rw : rx, v[i % LPB], so);
+        });
+    };
+
+    f32x4_t acc[MR][TB], accl[MR][TB];
+#pragma unroll
+    for (int i = 0; i < MR; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { acc[i][j][e] = 0.f; accl[i][j][e] = 0.f; }
+
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) issue(s_begin + d, d);
+
+    if constexpr (FINAL) {
+        // low-rank part while the first weight rows are on their way: h from its slices (summed in order, rounded once to
+        // the storage type, as the saved tensor is), B straight from memory; the waves share the k-steps of 32
+        const int r = p.r;
+        for (int st = wave; st * 32 < r; st += WAVES) {
+            const int l = st * 32 + lq * 8;
+            const bool ok = l < r;
+            bf16x8_t hf[TB], bfr[MR];
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                const int t = j * 16 + l16;
+                const int tc = t < T ? t : T - 1;
+                float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                if (ok)
+                    for (int zz = 0; zz < p.h_slices; ++zz) {
+                        const float4* hp = reinterpret_cast<const float4*>(p.h_part + ((int64_t)zz * T + tc) * r + l);
+                        const float4 u = hp[0], v = hp[1];
+                        a[0] += u.x; a[1] += u.y; a[2] += u.z; a[3] += u.w;
+                        a[4] += v.x; a[5] += v.y; a[6] += v.z; a[7] += v.w;
+                    }
+                uint4 o;
+                o.x = E::pack2(a[0], a[1]); o.y = E::pack2(a[2], a[3]); o.z = E::pack2(a[4], a[5]); o.w = E::pack2(a[6], a[7]);
+                hf[j] = __builtin_bit_cast(bf16x8_t, o);
+                if (p.h_out && blockIdx.x == 0 && ok && t < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * r + l) = o;
+            }
+#pragma unroll
+            for (int i = 0; i < MR; ++i) {
+                const int n = n0 + i * 16 + l16;
+                uint4 b = make_uint4(0u, 0u, 0u, 0u);
+                if (ok && n < N) b = *reinterpret_cast<const uint4*>(p.b + (int64_t)n * r + l);
+                bfr[i] = __builtin_bit_cast(bf16x8_t, b);
+            }
+#pragma unroll
+            for (int i = 0; i < MR; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j) accl[i][j] = E::mfma16(bfr[i], hf[j], accl[i][j]);
+        }
+    }
+
+    typedef __attribute__((address_space(3))) const char* lds_cptr_t;
+    const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_cptr_t)ring;
+    uint32_t rd[KSTEPS];
+#pragma unroll
+    for (int q = 0; q < KSTEPS; ++q)
+        rd[q] = ring_lds + (uint32_t)lds_off<STEP_K>(l16, q * 32 + lq * 8);
+    int slot = 0;
+    for (int s = s_begin; s < s_end; ++s) {
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmcnt<(DEPTH - 1) * LPS>();               // the oldest slot has landed
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8_t f[KSTEPS][MR + TB];
+        static_for<KSTEPS * (MR + TB)>([&](auto it) {
+            constexpr int q = decltype(it)::value / (MR + TB), b = decltype(it)::value % (MR + TB);
+            f[q][b] = lds_read_b128<b * 16 * STEP_K * 2>(rd[q] + slot * SLOT_BYTES);
+        });
+        wait_lgkmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(s + DEPTH, slot);                        // its reads are done: refill it
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < KSTEPS; ++q)
+#pragma unroll
+            for (int i = 0; i < MR; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j) acc[i][j] = E::mfma16(f[q][i], f[q][MR + j], acc[i][j]);
+        slot = slot + 1 == DEPTH ? 0 : slot + 1;
+    }
+    wait_vmcnt<0>();                                   // the loads past the end have written their zeros
+    __syncthreads();
+
+    // lane: weight rows 4 lq .. +3 of block i, token l16 of block j.  The four waves' tiles meet in LDS.
+    float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int i = 0; i < MR; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+            float4 v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+            if constexpr (FINAL) {
+                v.x = fmaf(p.s, accl[i][j][0], v.x); v.y = fmaf(p.s, accl[i][j][1], v.y);
+                v.z = fmaf(p.s, accl[i][j][2], v.z); v.w = fmaf(p.s, accl[i][j][3], v.w);
+            }
+            *reinterpret_cast<float4*>(red + (wave * TOK + j * 16 + l16) * RED_LD + i * 16 + lq * 4) = v;
+        }
+    __syncthreads();
+    constexpr int PAIRS = ROWS / 2;
+    for (int e = threadIdx.x; e < TOK * PAIRS; e += 64 * WAVES) {
+        const int t = e / PAIRS, c = (e % PAIRS) * 2, n = n0 + c;
+        if (t >= T || n >= N) continue;                // N is a multiple of 8
+        float v0 = 0.f, v1 = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float2 u = *reinterpret_cast<const float2*>(red + (w * TOK + t) * RED_LD + c);
+            v0 += u.x; v1 += u.y;
+        }
+        if constexpr (FINAL) {
+            const float2 cj = *reinterpret_cast<const float2*>(p.c + n), mj = *reinterpret_cast<const float2*>(p.m + n);
+            const float g0 = mj.x / ((cj.x < p.eps) ? p.eps : cj.x), g1 = mj.y / ((cj.y < p.eps) ? p.eps : cj.y);
+            uint32_t bias = 0u;
+            if (p.bias) bias = *reinterpret_cast<const uint32_t*>(p.bias + n);
+            const int64_t at = (int64_t)t * N + n;
+            *reinterpret_cast<uint32_t*>(p.y + at) = E::pack2(fmaf(g0, v0, E::lo(bias)), fmaf(g1, v1, E::hi(bias)));
+            if (p.inner) *reinterpret_cast<uint32_t*>(p.inner + at) = E::pack2(v0, v1);
+        } else {
+            *reinterpret_cast<float2*>(p.part + ((int64_t)z * T + t) * N + n) = make_float2(v0, v1);
+        }
+    }
+}
+
+// Ring depth and rows per workgroup, all measured with weights that lie in memory (bf16, us of the whole forward at
+// 4096 x 4096 r 384 / 14336 x 4096 r 64 / 8192 x 8192 r 768): up to 8192 weight rows 16 of them make 512 workgroups, two
+// per CU in one go, and a shallow ring that lets two share a CU beats a deep one (1 token 18.3 / 29.7 / 44.1 against
+// 19.1 / 39.1 / 57.5 for eight slots and one workgroup per CU).  Beyond, workgroups of 64 rows: 1.75 rounds of small ones
+// lose to one round of large ones (16 tokens 34.9 -> 27.4 at 14336 rows, but 51.6 -> 59.9 at 8192), and the token rows are
+// re-read for a quarter as many workgroups (32 tokens 41.2 -> 31.4).  With four token blocks that re-reading already
+// asks for 32 rows at 8192 (64 tokens 85.7 -> 75.0), not at 4096 (27.0 against 29.9).
+template <int DT>
+hipError_t launch_y(const FewTokensArgs& a, hipStream_t st)
+{
+    const bool narrow = a.N <= 4096, wide = a.N > 8192;
+#define DORA_FEW(TB, MR, DEPTH) \
+    few_tokens_kernel<TB, MR, DEPTH, true, DT><<<dim3((unsigned)((a.N + MR * 16 - 1) / (MR * 16))), dim3(64 * WAVES), 0, st>>>(a)
+    if (a.T <= 16) { if (wide) DORA_FEW(1, 4, 2); else DORA_FEW(1, 1, 4); }
+    else if (a.T <= 32) { if (wide) DORA_FEW(2, 4, 2); else DORA_FEW(2, 1, 3); }
+    else if (wide) DORA_FEW(4, 4, 2);
+    else if (narrow) DORA_FEW(4, 1, 2);
+    else DORA_FEW(4, 2, 2);
+#undef DORA_FEW
+    return hipGetLastError();
+}
+
+template <int DT>
+hipError_t launch_h(const FewTokensArgs& a, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.N + 15) / 16 * a.ksplit)), block(64 * WAVES);
+    if (a.T <= 16) few_tokens_kernel<1, 1, 4, false, DT><<<grid, block, 0, st>>>(a);
+    else if (a.T <= 32) few_tokens_kernel<2, 1, 3, false, DT><<<grid, block, 0, st>>>(a);
+    else few_tokens_kernel<4, 1, 2, false, DT><<<grid, block, 0, st>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Slices of d_in for h = x A^T: r / 16 workgroups leave most of the chip idle, but every workgroup of the y launch sums
+// all slices of all tokens again, so few of them where there are many tokens, and two ring slots per wave at least.
+int few_tokens_h_slices(int64_t tokens, int64_t r, int64_t d_in)
+{
+    const int64_t groups = (r + 15) / 16;
+    const int64_t tb = (tokens + 15) / 16, steps = (d_in + STEP_K - 1) / STEP_K;
+    int64_t ks = 256 / groups;
+    if (ks > 8 / tb) ks = 8 / tb;
+    if (ks > steps / (2 * WAVES)) ks = steps / (2 * WAVES);
+    return ks < 1 ? 1 : (int)ks;
+}
+
+hipError_t launch_few_tokens_h(const FewTokensArgs& a, int dt, hipStream_t st)
+{
+    TraceScope ts(DORA_K_GEMM_H, st);
+    return dt == DT_F16 ? launch_h<DT_F16>(a, st) : launch_h<DT_BF16>(a, st);
+}
+
+hipError_t launch_few_tokens_y(const FewTokensArgs& a, int dt, hipStream_t st)
+{
+    TraceScope ts(DORA_K_GEMM_FUSED_FWD, st);
+    return dt == DT_F16 ? launch_y<DT_F16>(a, st) : launch_y<DT_BF16>(a, st);
+}
+
+}  // namespace dora
