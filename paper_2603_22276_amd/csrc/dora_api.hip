@@ -470,7 +470,7 @@ size_t dora_workspace_bytes(const dora_desc* desc, int phase)
         case DORA_PHASE_FORWARD: { FwdPlan p; plan_fwd(desc, b, p, true, true, true, true); break; }
         case DORA_PHASE_BACKWARD: { BwdPlan p; plan_bwd(desc, b, p, false, false, false); break; }
         case DORA_PHASE_BACKWARD_RECOMPUTE: { BwdPlan p; plan_bwd(desc, b, p, true, true, true); break; }
-        case DORA_PHASE_FORWARD_DROPOUT: { FwdPlan p; plan_fwd(desc, b, p, true, true, true, false, true); break; }
+        case DORA_PHASE_FORWARD_DROPOUT: { FwdPlan p; plan_fwd(desc, b, p, true, true, true, true, true); break; }
         case DORA_PHASE_BACKWARD_DROPOUT: { BwdPlan p; plan_bwd(desc, b, p, true, true, true, true); break; }
         default: return 0;
     }
@@ -626,9 +626,19 @@ dora_status dora_project(const dora_desc* desc, const void* x, const void* W, co
     return forward_contractions(desc, x, W, A, B, base, h, lora, (hipStream_t)stream);
 }
 
+// inner = x W^T + s h B^T as one K-concatenated product  [s h | x] [B | W]^T, hs = s h; the caller sets epilogue and outputs
+static GemmArgs inner_product(const dora_desc* d, const void* x, const void* W, const void* B, const void* hs)
+{
+    const int T = (int)d->tokens, d_out = (int)d->d_out, d_in = (int)d->d_in, r = (int)d->r;
+    Seg segs[2] = {{hs, r, B, r, r}, {x, d_in, W, d_in, d_in}};
+    return bf16_args(dt_of(d->dtype), true, true, T, d_out, segs, 2, 1.f, nullptr, d_out, false, 0);
+}
+
+// one_product: the K-concatenated forward (h, then [s h | x] [B | W]^T with the compose in its epilogue), else x W^T,
+// h B^T and a compose pass over both.
 static dora_status forward_impl(const dora_desc* desc, const void* x, const void* x_lora, const void* W, const void* A,
                                 const void* B, const float* m, const float* w_norm, const void* bias, void* y, void* saved_h,
-                                void* saved_inner, float* w_norm_out, void* ws, size_t ws_bytes, void* stream)
+                                void* saved_inner, float* w_norm_out, void* ws, size_t ws_bytes, void* stream, bool one_product)
 {
     dora_status st = check_desc(desc, true);
     if (st != DORA_OK) return st;
@@ -638,16 +648,18 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     DORA_OPT_PTR(w_norm); DORA_OPT_PTR(bias); DORA_OPT_PTR(saved_h); DORA_OPT_PTR(saved_inner); DORA_OPT_PTR(w_norm_out);
     const bool need_norm = (w_norm == nullptr);
     const bool dropout = (x_lora != nullptr);
+    const bool need_lora = !one_product && saved_inner == nullptr;
     Bump sizing(nullptr);
     FwdPlan p;
-    plan_fwd(desc, sizing, p, need_norm, saved_h == nullptr, saved_inner == nullptr, false, dropout);
+    plan_fwd(desc, sizing, p, need_norm, saved_h == nullptr, need_lora, one_product, dropout);
     if ((st = check_ws(ws, ws_bytes, sizing.off)) != DORA_OK) return st;
     Bump b(ws);
-    plan_fwd(desc, b, p, need_norm, saved_h == nullptr, saved_inner == nullptr, false, dropout);
+    plan_fwd(desc, b, p, need_norm, saved_h == nullptr, need_lora, one_product, dropout);
     hipStream_t s = (hipStream_t)stream;
-    const int T = (int)desc->tokens, d_out = (int)desc->d_out, d_in = (int)desc->d_in;
+    const int T = (int)desc->tokens, d_out = (int)desc->d_out, d_in = (int)desc->d_in, r = (int)desc->r;
 
-    MagOut mag{m, eff_eps(desc), p.g, p.gm1, false};
+    float* const gm1 = one_product ? nullptr : p.gm1;   // only the compose pass reads g - 1
+    MagOut mag{m, eff_eps(desc), p.g, gm1, false};
     const float* c = w_norm;
     if (need_norm) {
         float* cw = w_norm_out ? w_norm_out : p.c;
@@ -659,9 +671,22 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     if (T == 0) return DORA_OK;
     if (!dropout && few_tokens(desc))
         return forward_few_tokens(desc, x, W, A, B, m, c, bias, y, saved_h, saved_inner, p.skp, s);
-    if (!mag.done) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, p.gm1, d_out, s));
-    // base lands in y and lora in the inner buffer; the compose pass then runs in place on both
+    if (!mag.done) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, gm1, d_out, s));
     void* h = saved_h ? saved_h : p.h;
+    if (one_product) {
+        // h = x A^T, written twice from the same accumulators: as it is (the saved tensor) and scaled by s
+        Seg s1{x, d_in, A, d_in, d_in};
+        DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp, p.hs, desc->s));
+        GemmArgs g = inner_product(desc, x, W, B, p.hs);
+        g.epilogue = EPI_COMPOSE;
+        g.c = y;
+        g.colscale = p.g;
+        g.colbias = (const bf16_t*)bias;
+        g.c2 = saved_inner;
+        DORA_HIP(launch_gemm_bf16(g, DORA_K_GEMM_FUSED_FWD, s));
+        return DORA_OK;
+    }
+    // base lands in y and lora in the inner buffer; the compose pass then runs in place on both
     void* lora = saved_inner ? saved_inner : p.lora;
     if ((st = forward_contractions(desc, x, W, A, B, y, h, lora, s, x_lora, p.skp)) != DORA_OK) return st;
     if (!dropout) {
@@ -676,11 +701,18 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     return DORA_OK;
 }
 
+// bf16 takes the K-concatenated product: one rounding where base, lora and the compose pass had three, and no pass over
+// [tokens, d_out] beside the product (8192 x 8192, r 384, 8192 tokens, forward and backward: 2089 -> 2021 us; 4096 x 4096,
+// 4096 tokens, forward: 216 -> 191 us; 27648 x 5120 and back with recompute: 13.79 -> 12.93 ms).  fp16 keeps the compose
+// pass: s h is rounded to storage before the product, and fp16's exponent range does not hold s h wherever it holds h.
+static bool forward_in_one_product(const dora_desc* d) { return d && d->dtype == DORA_BF16; }
+
 dora_status dora_forward(const dora_desc* desc, const void* x, const void* W, const void* A, const void* B,
                          const float* m, const float* w_norm, const void* bias, void* y, void* saved_h, void* saved_inner,
                          float* w_norm_out, void* ws, size_t ws_bytes, void* stream)
 {
-    return forward_impl(desc, x, nullptr, W, A, B, m, w_norm, bias, y, saved_h, saved_inner, w_norm_out, ws, ws_bytes, stream);
+    return forward_impl(desc, x, nullptr, W, A, B, m, w_norm, bias, y, saved_h, saved_inner, w_norm_out, ws, ws_bytes, stream,
+                        forward_in_one_product(desc));
 }
 
 dora_status dora_forward_dropout(const dora_desc* desc, const void* x, const void* x_lora, const void* W, const void* A,
@@ -689,54 +721,19 @@ dora_status dora_forward_dropout(const dora_desc* desc, const void* x, const voi
                                  void* stream)
 {
     if (desc && desc->tokens > 0 && !x_lora) return DORA_ERR_NULL;
-    return forward_impl(desc, x, x_lora, W, A, B, m, w_norm, bias, y, saved_h, saved_inner, w_norm_out, ws, ws_bytes, stream);
+    // dropout switched off (evaluation): the adapter's input is x itself, so x W^T serves both branches
+    if (desc && desc->tokens > 0 && x_lora == x) x_lora = nullptr;
+    return forward_impl(desc, x, x_lora, W, A, B, m, w_norm, bias, y, saved_h, saved_inner, w_norm_out, ws, ws_bytes, stream,
+                        !x_lora && forward_in_one_product(desc));
 }
 
 dora_status dora_forward_fused(const dora_desc* desc, const void* x, const void* W, const void* A, const void* B,
                                const float* m, const float* w_norm, const void* bias, void* y, void* saved_h, void* saved_inner,
                                float* w_norm_out, void* ws, size_t ws_bytes, void* stream)
 {
-    dora_status st = check_desc(desc, true);
-    if (st != DORA_OK) return st;
-    if (!is16(desc->dtype)) return DORA_ERR_DTYPE;
-    DORA_REQ_PTR(W); DORA_REQ_PTR(A); DORA_REQ_PTR(B); DORA_REQ_PTR(m);
-    if (desc->tokens > 0) { DORA_REQ_PTR(x); DORA_REQ_PTR(y); }
-    DORA_OPT_PTR(w_norm); DORA_OPT_PTR(bias); DORA_OPT_PTR(saved_h); DORA_OPT_PTR(saved_inner); DORA_OPT_PTR(w_norm_out);
-    const bool need_norm = (w_norm == nullptr);
-    Bump sizing(nullptr);
-    FwdPlan p;
-    plan_fwd(desc, sizing, p, need_norm, saved_h == nullptr, false, true);
-    if ((st = check_ws(ws, ws_bytes, sizing.off)) != DORA_OK) return st;
-    Bump b(ws);
-    plan_fwd(desc, b, p, need_norm, saved_h == nullptr, false, true);
-    hipStream_t s = (hipStream_t)stream;
-    const int T = (int)desc->tokens, d_out = (int)desc->d_out, d_in = (int)desc->d_in, r = (int)desc->r;
-
-    MagOut mag{m, eff_eps(desc), p.g, nullptr, false};
-    const float* c = w_norm;
-    if (need_norm) {
-        float* cw = w_norm_out ? w_norm_out : p.c;
-        if ((st = norm_impl(desc, W, A, B, cw, p.norm, s, nullptr, nullptr, nullptr, &mag)) != DORA_OK) return st;
-        c = cw;
-    } else if (w_norm_out && w_norm_out != w_norm) {
-        DORA_HIP(hipMemcpyAsync(w_norm_out, w_norm, sizeof(float) * d_out, hipMemcpyDeviceToDevice, s));
-    }
-    if (T == 0) return DORA_OK;
-    if (few_tokens(desc)) return forward_few_tokens(desc, x, W, A, B, m, c, bias, y, saved_h, saved_inner, p.skp, s);
-    if (!mag.done) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, nullptr, d_out, s));
-    // h = x A^T, written twice from the same accumulators: as it is (the saved tensor) and scaled by s,
-    // the low-rank operand of the K-concatenated product  [s h | x] [B | W]^T = s h B^T + x W^T
-    void* h = saved_h ? saved_h : p.h;
-    Seg s1{x, d_in, A, d_in, d_in};
-    DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp, p.hs, desc->s));
-    Seg segs[2] = {{p.hs, r, B, r, r}, {x, d_in, W, d_in, d_in}};
-    GemmArgs g = bf16_args(dt_of(desc->dtype), true, true, T, d_out, segs, 2, 1.f, y, d_out, false, 0);
-    g.epilogue = EPI_COMPOSE;
-    g.colscale = p.g;
-    g.colbias = (const bf16_t*)bias;
-    g.c2 = saved_inner;
-    DORA_HIP(launch_gemm_bf16(g, DORA_K_GEMM_FUSED_FWD, s));
-    return DORA_OK;
+    if (check_desc(desc, true) == DORA_OK && !is16(desc->dtype)) return DORA_ERR_DTYPE;
+    return forward_impl(desc, x, nullptr, W, A, B, m, w_norm, bias, y, saved_h, saved_inner, w_norm_out, ws, ws_bytes, stream,
+                        true);
 }
 
 // x_lora == nullptr: the plain module (dx = dz W + dh A).  Otherwise the adapter branch has its own input:
@@ -779,9 +776,18 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
 
     const void* h = saved_h;
     const void* inner = saved_inner;
-    if (T > 0 && need_inner) {
-        // recompute (gradient-checkpointing pattern): base -> dz buffer, lora -> inner buffer,
-        // then inner = s*lora + base in place; the dz buffer is overwritten by dz afterwards
+    if (T > 0 && need_inner && !saved_h && forward_in_one_product(desc)) {
+        // recompute (gradient-checkpointing pattern) as the forward forms it; s h waits in the dh buffer
+        Seg s1{xa, d_in, A, d_in, d_in};
+        DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp, p.dh, desc->s));
+        GemmArgs g = inner_product(desc, xa, W, B, p.dh);
+        g.c = p.inner;
+        DORA_HIP(launch_gemm_bf16(g, DORA_K_GEMM_FUSED_FWD, s));
+        inner = p.inner;
+        h = p.h;
+    } else if (T > 0 && need_inner) {
+        // base -> dz buffer, lora -> inner buffer, then inner = s*lora + base in place; the dz buffer is overwritten
+        // by dz afterwards
         void* hbuf = saved_h ? nullptr : p.h;
         if (saved_h) {
             Seg s0{xa, d_in, W, d_in, d_in};
