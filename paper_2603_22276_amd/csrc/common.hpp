@@ -169,22 +169,31 @@ int few_tokens_h_slices(int64_t tokens, int64_t r, int64_t d_in);
 hipError_t launch_few_tokens_h(const FewTokensArgs& a, int dt, hipStream_t st);
 hipError_t launch_few_tokens_y(const FewTokensArgs& a, int dt, hipStream_t st);
 
-// ---- fp32 GEMM (simple LDS-tiled VALU kernel; the fp32 configuration is small) ------------------
+// ---- fp32 GEMM (sgemm_f32.hip) --------------------------------------------------------------------
+// C[M,N] = alpha * sum over segments of  Aop[m,k] * Bop[n,k], operands K-contiguous or K-strided as in GemmArgs
 struct SgemmSeg {
     const float* a;
     const float* b;
-    int64_t sa_m, sa_k, sb_n, sb_k;  // element strides
+    int64_t lda, ldb;
     int K;
 };
 struct SgemmArgs {
     SgemmSeg seg[2];
     int nseg;
     int M, N;
+    int a_kcontig, b_kcontig;
     float alpha;
     float* c;
     int64_t ldc;
 };
+struct SgemmPair {
+    SgemmArgs g[2];
+    int count0;  // workgroups of g[0]; the rest of the grid belongs to g[1]
+};
 hipError_t launch_sgemm_f32(const SgemmArgs& a, int trace_id, hipStream_t stream);
+// two independent problems of the same layouts, both too small for 64 x 64 tiles, in one launch
+bool sgemm_f32_pairs(const SgemmArgs& a, const SgemmArgs& b);
+hipError_t launch_sgemm_f32_pair(const SgemmArgs& a, const SgemmArgs& b, int trace_id, hipStream_t stream);
 
 // ---- element-wise / reduction kernels -----------------------------------------------------------
 hipError_t launch_mag_scale(const float* m, const float* c, float eps, float* g, float* gm1, int d_out, hipStream_t st);
@@ -209,7 +218,8 @@ hipError_t launch_norm_final(const float* base_sq_p, int n_base, const float* cr
 hipError_t launch_rownorm_s0_16(const bf16_t* W, int dt, float* c, int d_out, int d_in, bool squared, hipStream_t st);
 // fp32 path: base_sq, cross, ba_sq and Eq. 5 from W, B, U = W A^T, BG = B G (all fp32)
 hipError_t launch_rownorm_f32(const float* W, const float* base_in, const float* B, const float* U, const float* BG,
-                              double s, float* c, float* terms, int d_out, int d_in, int r, bool squared, hipStream_t st);
+                              double s, float* c, float* terms, int d_out, int d_in, int r, bool squared, hipStream_t st,
+                              const float* m = nullptr, float eps = 0.f, float* g = nullptr, float* gm1 = nullptr);
 
 // out[i] = sum over z (in order) of partials[z * n + i], written in the storage dtype; out2 (may be nullptr)
 // receives alpha2 times the same sum.  n a multiple of 8.

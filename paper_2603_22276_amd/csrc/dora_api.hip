@@ -221,6 +221,16 @@ GemmArgs bf16_args(int dt, bool a_kc, bool b_kc, int M, int N, const Seg* segs, 
     return g;
 }
 
+SgemmArgs f32_args(bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg, float alpha, void* c, int64_t ldc)
+{
+    SgemmArgs g;
+    memset(&g, 0, sizeof(g));
+    for (int i = 0; i < nseg; ++i)
+        g.seg[i] = SgemmSeg{(const float*)segs[i].a, (const float*)segs[i].b, segs[i].lda, segs[i].ldb, segs[i].K};
+    g.nseg = nseg; g.M = M; g.N = N; g.a_kcontig = a_kc; g.b_kcontig = b_kc; g.alpha = alpha; g.c = (float*)c; g.ldc = ldc;
+    return g;
+}
+
 // skp != nullptr (16-bit outputs, one segment): scratch for the K slices of a skinny product; the product is then
 // split as skinny_ksplit says.  c2 / alpha2: optional second output alpha2 * (A B^T) (16-bit storage only).
 hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg, float alpha, void* c,
@@ -240,16 +250,18 @@ hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* se
         g.c2 = c2; g.alpha2 = alpha2;
         return launch_gemm_bf16(g, trace_id, st);
     }
-    SgemmArgs g;
-    memset(&g, 0, sizeof(g));
-    for (int i = 0; i < nseg; ++i) {
-        SgemmSeg& s = g.seg[i];
-        s.a = (const float*)segs[i].a; s.b = (const float*)segs[i].b; s.K = segs[i].K;
-        s.sa_m = a_kc ? segs[i].lda : 1; s.sa_k = a_kc ? 1 : segs[i].lda;
-        s.sb_n = b_kc ? segs[i].ldb : 1; s.sb_k = b_kc ? 1 : segs[i].ldb;
-    }
-    g.nseg = nseg; g.M = M; g.N = N; g.alpha = alpha; g.c = (float*)c; g.ldc = ldc;
-    return launch_sgemm_f32(g, trace_id, st);
+    return launch_sgemm_f32(f32_args(a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc), trace_id, st);
+}
+
+// two independent fp32 contractions of one segment each and the same layouts, in one launch where neither fills the chip
+struct F32Product { int M, N; Seg seg; float alpha; void* c; };
+hipError_t contract_f32_two(bool a_kc, bool b_kc, const F32Product& p, const F32Product& q, int trace_p, int trace_q, hipStream_t st)
+{
+    const SgemmArgs a = f32_args(a_kc, b_kc, p.M, p.N, &p.seg, 1, p.alpha, p.c, p.N);
+    const SgemmArgs b = f32_args(a_kc, b_kc, q.M, q.N, &q.seg, 1, q.alpha, q.c, q.N);
+    if (sgemm_f32_pairs(a, b)) return launch_sgemm_f32_pair(a, b, trace_p, st);
+    hipError_t e = launch_sgemm_f32(a, trace_p, st);
+    return e != hipSuccess ? e : launch_sgemm_f32(b, trace_q, st);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -314,14 +326,14 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
         return DORA_OK;
     }
     // fp32: Algorithm 1 with one chunk spanning d_in; U [d_out, r], G [r, r], BG [d_out, r] in scratch
-    Seg su{W, d_in, A, d_in, d_in};
-    DORA_HIP(contract(DORA_F32, true, true, d_out, r, &su, 1, 1.f, n.U, r, true, DORA_K_NORM_CROSS, st));
-    Seg sg{A, d_in, A, d_in, d_in};
-    DORA_HIP(contract(DORA_F32, true, true, r, r, &sg, 1, 1.f, n.G, r, true, DORA_K_GRAM, st));
+    DORA_HIP(contract_f32_two(true, true, F32Product{d_out, r, Seg{W, d_in, A, d_in, d_in}, 1.f, n.U},
+                              F32Product{r, r, Seg{A, d_in, A, d_in, d_in}, 1.f, n.G}, DORA_K_NORM_CROSS, DORA_K_GRAM, st));
     Seg sb{B, r, n.G, r, r};  // (B G)[j,l] = sum_k B[j,k] G[k,l]: N-side operand K-strided
     DORA_HIP(contract(DORA_F32, true, false, d_out, r, &sb, 1, 1.f, n.BG, r, true, DORA_K_BA_SQ, st));
     DORA_HIP(launch_rownorm_f32((const float*)W, base_sq, (const float*)B, n.U, n.BG, (double)d->s, c, terms, d_out, d_in,
-                                r, false, st));
+                                r, false, st, mag ? mag->m : nullptr, mag ? mag->eps : 0.f, mag ? mag->g : nullptr,
+                                mag ? mag->gm1 : nullptr));
+    if (mag) mag->done = true;
     if (G_out) DORA_HIP(hipMemcpyAsync(G_out, n.G, sizeof(float) * (size_t)r * r, hipMemcpyDeviceToDevice, st));
     return DORA_OK;
 }
@@ -404,11 +416,16 @@ dora_status forward_contractions(const dora_desc* d, const void* x, const void* 
     const int T = (int)d->tokens, d_out = (int)d->d_out, d_in = (int)d->d_in, r = (int)d->r;
     Seg s0{x, d_in, W, d_in, d_in};
     Seg s1{xa ? xa : x, d_in, A, d_in, d_in};
-    // (base and h are NOT paired into one launch: h's extra tiles would form a fifth, nearly empty
+    // (16-bit: base and h are NOT paired into one launch: h's extra tiles would form a fifth, nearly empty
     // round behind the four full rounds of 256 x 256 base tiles and cost more than a launch of their own)
     // (h after base, not before: it then finds part of x still in the memory-side cache; the other order costs 10 us)
-    DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st));
-    DORA_HIP(contract(d->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, st, skp));
+    if (d->dtype == DORA_F32) {
+        DORA_HIP(contract_f32_two(true, true, F32Product{T, d_out, s0, 1.f, base}, F32Product{T, r, s1, 1.f, h}, DORA_K_GEMM_BASE,
+                                  DORA_K_GEMM_H, st));
+    } else {
+        DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st));
+        DORA_HIP(contract(d->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, st, skp));
+    }
     Seg s2{h, r, B, r, r};
     DORA_HIP(contract(d->dtype, true, true, T, d_out, &s2, 1, 1.f, lora, d_out, false, DORA_K_GEMM_LORA, st));
     return DORA_OK;
@@ -839,6 +856,9 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         GemmArgs ga = bf16_args(dt_of(dt), false, false, r, d_in, &sa, 1, 1.f, dA, d_in, true, 0);
         GemmArgs gb = bf16_args(dt_of(dt), false, false, d_out, r, &sb, 1, desc->s, dB, r, true, 0);
         DORA_HIP(launch_gemm_bf16_pair(ga, gb, DORA_K_GEMM_DA, s));
+    } else if (dA && dB) {
+        DORA_HIP(contract_f32_two(false, false, F32Product{r, d_in, sa, 1.f, dA}, F32Product{d_out, r, sb, desc->s, dB},
+                                  DORA_K_GEMM_DA, DORA_K_GEMM_DB, s));
     } else {
         if (dA) DORA_HIP(contract(dt, false, false, r, d_in, &sa, 1, 1.f, dA, d_in, true, DORA_K_GEMM_DA, s));
         if (dB) DORA_HIP(contract(dt, false, false, d_out, r, &sb, 1, desc->s, dB, r, true, DORA_K_GEMM_DB, s));

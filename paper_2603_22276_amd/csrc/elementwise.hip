@@ -169,11 +169,13 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, in
 
 // fp32 configuration: the three terms of Eq. 2 for one row per wavefront, from U = W A^T and BG = B G.
 // base_in != nullptr: the base term is read from it instead of being summed from W (Sec. 2.3: W is frozen, so
-// its squared row norms can be computed once).  squared: write the radicand itself, not its root.
+// its squared row norms can be computed once).  squared: write the radicand itself, not its root.  m != nullptr: Eq. 6
+// follows, as in norm_final_kernel.
 __global__ void rownorm_f32_kernel(const float* __restrict__ W, const float* __restrict__ base_in,
                                    const float* __restrict__ B, const float* __restrict__ U,
                                    const float* __restrict__ BG, float two_s, float s2, float* __restrict__ c,
-                                   float* __restrict__ terms, int d_out, int d_in, int r, bool squared)
+                                   float* __restrict__ terms, int d_out, int d_in, int r, bool squared,
+                                   const float* __restrict__ m, float eps, float* __restrict__ g, float* __restrict__ gm1)
 {
     int lane = threadIdx.x & 63;
     int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -203,7 +205,14 @@ __global__ void rownorm_f32_kernel(const float* __restrict__ W, const float* __r
         if (c) {
             float rad = base_sq + two_s * cross + s2 * ba;
             rad = (rad < 0.f) ? 0.f : rad;
-            c[row] = squared ? rad : __fsqrt_rn(rad);
+            const float cj = squared ? rad : __fsqrt_rn(rad);
+            c[row] = cj;
+            if (m) {
+                float cc = (cj < eps) ? eps : cj;
+                float mj = m[row];
+                if (g) g[row] = mj / cc;
+                if (gm1) gm1[row] = (mj - cc) / cc;
+            }
         }
     }
 }
@@ -485,12 +494,13 @@ hipError_t launch_rownorm_s0_16(const bf16_t* W, int dt, float* c, int d_out, in
 }
 
 hipError_t launch_rownorm_f32(const float* W, const float* base_in, const float* B, const float* U, const float* BG,
-                              double s, float* c, float* terms, int d_out, int d_in, int r, bool squared, hipStream_t st)
+                              double s, float* c, float* terms, int d_out, int d_in, int r, bool squared, hipStream_t st,
+                              const float* m, float eps, float* g, float* gm1)
 {
     if (d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_NORM_FINAL, st);
     rownorm_f32_kernel<<<dim3((d_out + 3) / 4), dim3(256), 0, st>>>(W, base_in, B, U, BG, (float)(2.0 * s),
-                                                                    (float)(s * s), c, terms, d_out, d_in, r, squared);
+                                                                    (float)(s * s), c, terms, d_out, d_in, r, squared, m, eps, g, gm1);
     return hipGetLastError();
 }
 
