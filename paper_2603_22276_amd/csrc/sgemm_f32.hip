@@ -10,7 +10,7 @@
 // zero on both sides, by selection, so that a NaN or infinity in a neighbouring row is not multiplied in.
 //
 // Against 32 x 32 and 64 x 64 tiles on the vector unit with one serial K loop per workgroup, forward and backward:
-// 256 x 512, r 16, 64 tokens 172 -> 53 us; 1000 x 772, r 36, 1500 tokens 569 -> 197 us.
+// 256 x 512, r 16, 64 tokens 172 -> 49 us; 1000 x 772, r 36, 1500 tokens 569 -> 171 us.
 #include "common.hpp"
 
 namespace dora {
@@ -114,26 +114,33 @@ __global__ __launch_bounds__(64 * WK) void sgemm_split_kernel(SgemmPair grp)
     }
 }
 
-// Many tiles: 64 x 64 of C per workgroup, 32 x 32 per wave, K in steps of 32 through two LDS buffers; the next step is
-// fetched into registers (a 4 x 4 block per thread, turned around on the way for a K-strided operand) while this one is
-// multiplied.
+// LDS offset (floats) of the 16-byte chunk `c` (four k) of row `row` in a [64][32] tile of the kernel below: rows of 128
+// bytes, chunks XORed so that the 16 rows of a fragment read cover all 16 slots of 256 bytes, and so that the rows 4 apart
+// which a wave turns around on the way in do as well as rows of one parity can (two lanes a slot).
+__device__ __forceinline__ int tile_off(int row, int c) { return row * 32 + ((c ^ (row >> 1) ^ (row >> 4)) & 7) * 4; }
+
+// Many tiles: 64 x 64 of C per workgroup, 32 x 32 per wave, K in steps of 32 through two LDS buffers.  One or two
+// workgroups per CU do not hide a load's latency, so steps are fetched into registers two ahead; a K-strided operand is
+// turned around, 4 x 4 elements per thread, on the way into LDS.  (One step ahead and rows padded to 144 bytes: dz W + dh A of
+// 1500 x 772 x 1036 in 76 us, 56 now.)
 template <bool A_KC, bool B_KC>
 __global__ __launch_bounds__(256) void sgemm_tile_kernel(SgemmArgs p)
 {
-    constexpr int TS = 64, TK = 32, LD = TK + 4;
-    __shared__ __attribute__((aligned(16))) float lds[2][2][TS * LD];
+    constexpr int TS = 64, TK = 32;
+    __shared__ __attribute__((aligned(256))) float lds[2][2][TS * TK];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const int M = p.M, N = p.N;
     const int tiles_n = (N + TS - 1) / TS;
     const int m0 = (int)(blockIdx.x / tiles_n) * TS, n0 = (int)(blockIdx.x % tiles_n) * TS;
     const int wm0 = wave / 2 * 32, wn0 = wave % 2 * 32;
-    // threads 0..127 bring in the M-side operand, the others the N-side one: rows 4 rg .. +3, k 4 kg .. +3 of a step
+    // threads 0..127 bring in the M-side operand, the others the N-side one, 16 elements of a step each: k 4 kg .. +3 of
+    // rows rg, rg + 16, +32, +48 (K-contiguous) or rows 4 rg .. +3 of k 4 kg .. +3 (K-strided)
     const bool n_side = wave >= 2;
     const bool kc = n_side ? B_KC : A_KC;
     const int blk = tid & 127;
     const int rg = kc ? blk / (TK / 4) : blk % (TS / 4), kg = kc ? blk % (TK / 4) : blk / (TS / 4);
-    const int row0 = (n_side ? n0 : m0) + rg * 4, rows = n_side ? N : M;
+    const int row0 = (n_side ? n0 : m0) + (kc ? rg : rg * 4), rows = n_side ? N : M;
     f32x4_t acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -145,43 +152,48 @@ __global__ __launch_bounds__(256) void sgemm_tile_kernel(SgemmArgs p)
         const float* const base = n_side ? sg.b : sg.a;
         const int64_t ld = n_side ? sg.ldb : sg.lda;
         const int K = sg.K, steps = (K + TK - 1) / TK;
-        float4 v[4];
-        auto fetch = [&](int step) {
+        auto fetch = [&](int step, float4 (&v)[4]) {
             const int k = step * TK + kg * 4;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (kc) {
-                    const int rr = row0 + i < rows ? row0 + i : rows - 1, kk = k < K ? k : K - 4;
+                    const int row = row0 + 16 * i;
+                    const int rr = row < rows ? row : rows - 1, kk = k < K ? k : K - 4;
                     v[i] = *reinterpret_cast<const float4*>(base + (int64_t)rr * ld + kk);
-                    if (k >= K) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
                 } else {                               // rows is a multiple of four
                     const int rr = row0 < rows ? row0 : rows - 4, kk = k + i < K ? k + i : K - 1;
                     v[i] = *reinterpret_cast<const float4*>(base + (int64_t)kk * ld + rr);
-                    if (k + i >= K) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             }
         };
-        auto stage = [&](int buf) {
-            float* dst = &lds[buf][n_side][rg * 4 * LD + kg * 4];
+        auto stage = [&](int step, const float4 (&v)[4]) {
+            float* const tile = lds[step & 1][n_side];
+            const int k = step * TK + kg * 4;
+            float4 w[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *reinterpret_cast<float4*>(dst + i * LD) =
-                    kc ? v[i] : make_float4(get(v[0], i), get(v[1], i), get(v[2], i), get(v[3], i));
+            for (int i = 0; i < 4; ++i) {
+                w[i] = v[i];
+                if (k + (kc ? 0 : i) >= K) w[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (kc) *reinterpret_cast<float4*>(tile + tile_off(rg + 16 * i, kg)) = w[i];
+                else *reinterpret_cast<float4*>(tile + tile_off(rg * 4 + i, kg)) =
+                         make_float4(get(w[0], i), get(w[1], i), get(w[2], i), get(w[3], i));
+            }
         };
-        if (steps > 0) { fetch(0); stage(0); }
-        __syncthreads();
-        for (int t = 0; t < steps; ++t) {
-            const int buf = t & 1;
-            if (t + 1 < steps) fetch(t + 1);
-            const float* as = &lds[buf][0][(wm0 + l16) * LD + lq * 4];
-            const float* bs = &lds[buf][1][(wn0 + l16) * LD + lq * 4];
+        // step t from LDS; `next` holds step t + 1 (staged at the end), `far` takes step t + 2
+        auto body = [&](int t, const float4 (&next)[4], float4 (&far)[4]) {
+            if (t + 2 < steps) fetch(t + 2, far);
+            const float* const as = lds[t & 1][0];
+            const float* const bs = lds[t & 1][1];
 #pragma unroll
             for (int q = 0; q < TK / 16; ++q) {
                 float4 a[2], b[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    a[i] = *reinterpret_cast<const float4*>(as + i * 16 * LD + q * 16);
-                    b[i] = *reinterpret_cast<const float4*>(bs + i * 16 * LD + q * 16);
+                    a[i] = *reinterpret_cast<const float4*>(as + tile_off(wm0 + i * 16 + l16, q * 4 + lq));
+                    b[i] = *reinterpret_cast<const float4*>(bs + tile_off(wn0 + i * 16 + l16, q * 4 + lq));
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -190,8 +202,16 @@ __global__ __launch_bounds__(256) void sgemm_tile_kernel(SgemmArgs p)
 #pragma unroll
                         for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(get(b[j], e), get(a[i], e), acc[i][j]);
             }
-            if (t + 1 < steps) stage(buf ^ 1);         // read last in step t - 1, before the barrier that ended it
+            if (t + 1 < steps) stage(t + 1, next);     // that buffer was read last in step t - 1, before its barrier
             __syncthreads();
+        };
+        float4 va[4], vb[4];
+        if (steps > 0) { fetch(0, va); stage(0, va); }
+        if (steps > 1) fetch(1, vb);
+        __syncthreads();
+        for (int t = 0; t < steps; t += 2) {
+            body(t, vb, va);
+            if (t + 1 < steps) body(t + 1, va, vb);
         }
     }
 #pragma unroll
