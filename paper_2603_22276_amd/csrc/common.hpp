@@ -202,10 +202,11 @@ hipError_t launch_compose_fwd(int dtype, const void* base, const void* lora, con
                               const void* bias, float s, void* out, int write_delta, void* inner, int64_t tokens,
                               int d_out, hipStream_t st);
 int compose_bwd_slabs(int64_t tokens, int d_out, int dtype);
-// dzb != nullptr: also dzb = gm1 (.) dy (then gm1 must be given)
+// dzb != nullptr: also dzb = gm1 (.) dy (then gm1 must be given); m != nullptr: g is the row norm, and g and gm1 are
+// formed from it, m and eps in the same launch
 hipError_t launch_compose_bwd(int dtype, const void* dy, const void* inner, const float* g, const float* gm1, void* dz,
                               void* dzb, float* partial /* [slabs][d_out] or nullptr */, int64_t tokens, int d_out,
-                              hipStream_t st);
+                              hipStream_t st, const float* m = nullptr, float eps = 0.f);
 hipError_t launch_dm_final(const float* partial, int slabs, const float* c, float eps, float* dm, int d_out, hipStream_t st);
 // G = sum of partials; Ghi + Glo ~ G as two 16-bit terms of element type dt (both may be nullptr)
 hipError_t launch_gram_reduce(const float* partials, int ksplit, int r, float* G, bf16_t* Ghi, bf16_t* Glo, int dt,

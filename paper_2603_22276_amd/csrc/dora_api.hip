@@ -789,7 +789,8 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         if ((st = norm_impl(desc, W, A, B, p.c, p.norm, s, nullptr, nullptr, nullptr, &mag)) != DORA_OK) return st;
         c = p.c;
     }
-    if (!mag.done) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, p.gm1, d_out, s));
+    const bool mag_in_compose = !mag.done && !need_inner;   // then the compose backward is the only reader of g
+    if (!mag.done && !mag_in_compose) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, p.gm1, d_out, s));
 
     const void* h = saved_h;
     const void* inner = saved_inner;
@@ -825,8 +826,8 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
 
     // compose backward: dz = g*dy (and (g-1)*dy for a separate adapter input) and the fused two-stage column
     // reduction for dm
-    DORA_HIP(launch_compose_bwd(dt, dy, inner, p.g, p.gm1, p.dz, need_dzb ? p.dzb : nullptr, dm ? p.dm_partial : nullptr, T,
-                                d_out, s));
+    DORA_HIP(launch_compose_bwd(dt, dy, inner, mag_in_compose ? c : p.g, p.gm1, p.dz, need_dzb ? p.dzb : nullptr,
+                                dm ? p.dm_partial : nullptr, T, d_out, s, mag_in_compose ? m : nullptr, eff_eps(desc)));
     if (dm) DORA_HIP(launch_dm_final(p.dm_partial, compose_bwd_slabs(T, d_out, dt), c, eff_eps(desc), dm, d_out, s));
 
     // dh = s * dz B   (gradient reaching h)

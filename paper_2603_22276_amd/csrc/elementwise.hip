@@ -75,6 +75,23 @@ template <> struct Vec<float> {
     static __device__ __forceinline__ raw_t pack(const float* f) { return make_float4(f[0], f[1], f[2], f[3]); }
 };
 
+// p[0] + p[stride] + ... in index order, U loads in flight: the launches that sum a handful of partials per thread are
+// bound by the latency of their loads, one after the other when each waits for the sum so far (norm of 4096 x 4096, r 384:
+// 9.7 us in the last launch of the norm).  8192 x 8192, r 128: 62 -> 53 us for the four launches of a norm.
+template <int U>
+__device__ __forceinline__ float sum_partials(const float* __restrict__ p, int n, int64_t stride)
+{
+    float acc = 0.f;
+    for (int i = 0; i < n; i += U) {
+        float v[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) v[e] = p[(int64_t)(i + e < n ? i + e : n - 1) * stride];
+#pragma unroll
+        for (int e = 0; e < U; ++e) acc += i + e < n ? v[e] : 0.f;
+    }
+    return acc;
+}
+
 // ------------------------------------------------------------------------------------------------
 // Eq. 6 and the explicit small correction of Sec. 3.1.
 __global__ void mag_scale_kernel(const float* __restrict__ m, const float* __restrict__ c, float eps,
@@ -100,10 +117,9 @@ __global__ void norm_final_kernel(const float* __restrict__ base_p, int n_base, 
 {
     int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= d_out) return;
-    float base_sq = 0.f, cross = 0.f, ba = 0.f;
-    for (int i = 0; i < n_base; ++i) base_sq += base_p[(int64_t)i * d_out + j];
-    for (int i = 0; i < n_cross; ++i) cross += cross_p[(int64_t)i * d_out + j];
-    for (int i = 0; i < n_ba; ++i) ba += ba_p[(int64_t)i * d_out + j];
+    const float base_sq = sum_partials<8>(base_p + j, n_base, d_out);
+    const float cross = sum_partials<8>(cross_p + j, n_cross, d_out);
+    const float ba = sum_partials<4>(ba_p + j, n_ba, d_out);
     if (terms) {
         terms[j] = base_sq;
         terms[(int64_t)d_out + j] = cross;
@@ -129,8 +145,7 @@ __global__ void gram_reduce_kernel(const float* __restrict__ p, int ksplit, int 
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= rr) return;
-    float acc = 0.f;
-    for (int z = 0; z < ksplit; ++z) acc += p[(int64_t)z * rr + i];
+    const float acc = sum_partials<16>(p + i, ksplit, rr);
     if (G) G[i] = acc;
     if (!Ghi) return;
     typedef Elem16<DT> E;
@@ -309,13 +324,16 @@ __global__ __launch_bounds__(CW* CH) void compose_fwd_kernel(const T* base_, con
 
 // Compose backward: dz = g*dy, and (DM) the first stage of the column sum of dy*inner over this slab.
 // SPLIT: also dzb = (g-1)*dy, the gradient reaching the adapter branch's own base when that branch has an
-// input of its own (dz then reaches lora only, scaled by s in the products that follow).
+// input of its own (dz then reaches lora only, scaled by s in the products that follow).  m != nullptr: g is the row
+// norm and Eq. 6 is formed here, as in mag_scale_kernel: a launch of d_out threads costs more than a few divisions per
+// workgroup of a pass over [tokens, d_out].
 template <typename T, bool DM, bool SPLIT, int CW, int CH>
 __global__ __launch_bounds__(CW* CH) void compose_bwd_kernel(const T* __restrict__ dy_, const T* __restrict__ inner_,
                                                               const float* __restrict__ g, const float* __restrict__ gm1,
                                                               T* __restrict__ dz_, T* __restrict__ dzb_,
                                                               float* __restrict__ partial, int64_t tokens, int d_out,
-                                                              int rows_per_wg, int col_blocks)
+                                                              int rows_per_wg, int col_blocks, const float* __restrict__ m,
+                                                              float eps)
 {
     typedef Vec<T> V;
     typedef typename V::raw_t raw_t;
@@ -329,8 +347,16 @@ __global__ __launch_bounds__(CW* CH) void compose_bwd_kernel(const T* __restrict
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         gv[i] = active ? g[col + i] : 0.f;
-        g1[i] = (SPLIT && active) ? gm1[col + i] : 0.f;
+        g1[i] = (SPLIT && active && !m) ? gm1[col + i] : 0.f;
         acc[i] = 0.f;
+    }
+    if (m && active) {   // g is the row norm
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float cc = (gv[i] < eps) ? eps : gv[i], mj = m[col + i];
+            gv[i] = mj / cc;
+            if (SPLIT) g1[i] = (mj - cc) / cc;
+        }
     }
     const int64_t row_begin = slab * rows_per_wg;
     int64_t row_end = row_begin + rows_per_wg;
@@ -418,7 +444,7 @@ __global__ __launch_bounds__(DMF_W* DMF_H) void dm_final_kernel(const float* __r
         int per = (slabs + DMF_H - 1) / DMF_H;
         int z0 = threadIdx.y * per;
         int z1 = z0 + per < slabs ? z0 + per : slabs;
-        for (int z = z0; z < z1; ++z) acc += partial[(int64_t)z * d_out + j];
+        if (z0 < z1) acc = sum_partials<8>(partial + (int64_t)z0 * d_out + j, z1 - z0, d_out);
     }
     red[threadIdx.y][threadIdx.x] = acc;
     __syncthreads();
@@ -449,7 +475,8 @@ hipError_t launch_norm_final(const float* base_p, int n_base, const float* cross
     if (d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_NORM_FINAL, st);
     // 2s and s^2 are formed in double and rounded once (App. C item 3)
-    norm_final_kernel<<<dim3((d_out + 255) / 256), dim3(256), 0, st>>>(base_p, n_base, cross_p, n_cross, ba_p, n_ba,
+    // blocks of one wave: a few thousand threads in all, so that every CU has some of the loads
+    norm_final_kernel<<<dim3((d_out + 63) / 64), dim3(64), 0, st>>>(base_p, n_base, cross_p, n_cross, ba_p, n_ba,
                                                                        (float)(2.0 * s), (float)(s * s), c, terms, d_out,
                                                                        m, eps, g, gm1);
     return hipGetLastError();
@@ -572,7 +599,7 @@ int compose_bwd_slabs(int64_t tokens, int d_out, int dtype)
 
 template <typename T>
 static hipError_t compose_bwd_t(const void* dy, const void* inner, const float* g, const float* gm1, void* dz, void* dzb,
-                                float* partial, int64_t tokens, int d_out, hipStream_t st)
+                                float* partial, int64_t tokens, int d_out, hipStream_t st, const float* m, float eps)
 {
     constexpr int N = Vec<T>::N;
     int cpr = d_out / N;
@@ -583,7 +610,7 @@ static hipError_t compose_bwd_t(const void* dy, const void* inner, const float* 
     dim3 block(BWD_CW, BWD_CH);
 #define DORA_LAUNCH_BWD(DM, SP)                                                                                   \
     compose_bwd_kernel<T, DM, SP, BWD_CW, BWD_CH><<<grid, block, 0, st>>>((const T*)dy, (const T*)inner, g, gm1, (T*)dz, (T*)dzb, partial, \
-                                                           tokens, d_out, BWD_ROWS_PER_WG, col_blocks)
+                                                           tokens, d_out, BWD_ROWS_PER_WG, col_blocks, m, eps)
     if (partial) { if (dzb) DORA_LAUNCH_BWD(true, true); else DORA_LAUNCH_BWD(true, false); }
     else { if (dzb) DORA_LAUNCH_BWD(false, true); else DORA_LAUNCH_BWD(false, false); }
 #undef DORA_LAUNCH_BWD
@@ -591,13 +618,14 @@ static hipError_t compose_bwd_t(const void* dy, const void* inner, const float* 
 }
 
 hipError_t launch_compose_bwd(int dtype, const void* dy, const void* inner, const float* g, const float* gm1, void* dz,
-                              void* dzb, float* partial, int64_t tokens, int d_out, hipStream_t st)
+                              void* dzb, float* partial, int64_t tokens, int d_out, hipStream_t st, const float* m,
+                              float eps)
 {
     if (tokens == 0 || d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_COMPOSE_BWD, st);
-    if (dtype == DORA_BF16) return compose_bwd_t<bf16_t>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st);
-    if (dtype == DORA_F16) return compose_bwd_t<f16_t>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st);
-    return compose_bwd_t<float>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st);
+    if (dtype == DORA_BF16) return compose_bwd_t<bf16_t>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st, m, eps);
+    if (dtype == DORA_F16) return compose_bwd_t<f16_t>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st, m, eps);
+    return compose_bwd_t<float>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st, m, eps);
 }
 
 hipError_t launch_dm_final(const float* partial, int slabs, const float* c, float eps, float* dm, int d_out, hipStream_t st)
