@@ -123,7 +123,7 @@ struct GemmArgs {
     float alpha;
     void* c;
     int64_t ldc;
-    int ksplit;                // split of segment 0's K range (nseg must be 1 when > 1)
+    int ksplit;                // split of segment 0's K range (fp32 stores and row-dots only)
     int tag;                   // 0 or 1: selects a differently named (otherwise identical) kernel instance
     int dt;                    // DT_BF16 or DT_F16: element type of both operands, of a 16-bit C and of rowdot / colbias
     const float* colscale;     // EPI_COMPOSE: [N] fp32
@@ -223,9 +223,10 @@ hipError_t launch_rownorm_f32(const float* W, const float* base_in, const float*
                               const float* m = nullptr, float eps = 0.f, float* g = nullptr, float* gm1 = nullptr);
 
 // out[i] = sum over z (in order) of partials[z * n + i], written in the storage dtype; out2 (may be nullptr)
-// receives alpha2 times the same sum.  n a multiple of 8.
+// receives alpha2 times the same sum.  n a multiple of 8.  colscale != nullptr: rows of `cols` elements, out is
+// colscale[col] times the sum (+ colbias[col] where given).
 hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, int dtype, void* out, float alpha2, void* out2,
-                                hipStream_t st);
+                                hipStream_t st, const float* colscale = nullptr, const void* colbias = nullptr, int cols = 0);
 
 hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st);
 hipError_t launch_mfma_probe(const void* operands, float* sink, int iters, int workgroups, hipStream_t st);

@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -189,11 +190,12 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
     }
 }
 
-// Split of K for the skinny products with a 16-bit output (h = x A^T, dh = s dz B): with [tokens, r] outputs of
-// 128 x 128 tiles a launch at 4096 tokens has 96 workgroups for 256 CUs.  When at most half the CUs would have
-// work, K is cut into slices (fp32 partials in the workspace, summed in slice order by a small reduce launch) so
-// that the launch approaches one workgroup per CU, each slice keeping at least 16 K steps.
-inline int skinny_ksplit(int dtype, int64_t M, int64_t N, int64_t K)
+// Split of K for the products with a 16-bit output whose 128 x 128 tiles leave at least half the CUs without work: h = x A^T
+// and dh = s dz B over [tokens, r] (96 workgroups at 4096 tokens, r 384), x W^T and dz W of short batches (32 at 512 tokens,
+// 1024 x 4096).  K is cut into slices (fp32 partials in the workspace, summed in slice order by a small reduce launch) so
+// that the launch approaches one workgroup per CU, each slice keeping at least 16 K steps.  (x W^T + s h B^T of 512 tokens,
+// 1024 x 4096: 29 us in one piece, 13.6 + 4 in four slices; the step of that module 107 -> 93 us.)
+inline int product_ksplit(int dtype, int64_t M, int64_t N, int64_t K)
 {
     if (!is16(dtype) || M <= 0) return 1;
     const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE);
@@ -231,8 +233,23 @@ SgemmArgs f32_args(bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg
     return g;
 }
 
-// skp != nullptr (16-bit outputs, one segment): scratch for the K slices of a skinny product; the product is then
-// split as skinny_ksplit says.  c2 / alpha2: optional second output alpha2 * (A B^T) (16-bit storage only).
+// One 16-bit product; skp != nullptr: scratch for the K slices, the product is then split as product_ksplit says and the
+// reduce launch does what the epilogue (EPI_STORE_BF16 or EPI_COMPOSE) would have done.
+hipError_t launch_product(const GemmArgs& g, int trace_id, float* skp, hipStream_t st)
+{
+    const int ks = (skp && g.ldc == g.N) ? product_ksplit(DORA_BF16, g.M, g.N, g.seg[0].K) : 1;
+    if (ks <= 1) return launch_gemm_bf16(g, trace_id, st);
+    const bool compose = g.epilogue == EPI_COMPOSE;
+    GemmArgs p = g;
+    p.epilogue = EPI_STORE_F32; p.c = skp; p.ksplit = ks; p.c2 = nullptr;
+    hipError_t e = launch_gemm_bf16(p, trace_id, st);
+    if (e != hipSuccess) return e;
+    return launch_splitk_reduce(skp, ks, (int64_t)g.M * g.N, g.dt == DT_F16 ? DORA_F16 : DORA_BF16, g.c, compose ? 1.f : g.alpha2,
+                                g.c2, st, compose ? g.colscale : nullptr, g.colbias, g.N);
+}
+
+// skp != nullptr (16-bit outputs): scratch for the K slices of the first segment.  c2 / alpha2: optional second output
+// alpha2 * (A B^T) (16-bit storage only).
 hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg, float alpha, void* c,
                     int64_t ldc, bool c_f32, int trace_id, hipStream_t st, float* skp = nullptr, void* c2 = nullptr,
                     float alpha2 = 0.f)
@@ -240,15 +257,8 @@ hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* se
     if (is16(dtype)) {
         const int tag = (trace_id == DORA_K_GEMM_LORA || trace_id == DORA_K_GEMM_DB) ? 1 : 0;
         GemmArgs g = bf16_args(dt_of(dtype), a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc, c_f32, tag);
-        const int ks = (skp && nseg == 1 && !c_f32 && ldc == N) ? skinny_ksplit(dtype, M, N, segs[0].K) : 1;
-        if (ks > 1) {
-            g.epilogue = EPI_STORE_F32; g.c = skp; g.ksplit = ks;
-            hipError_t e = launch_gemm_bf16(g, trace_id, st);
-            if (e != hipSuccess) return e;
-            return launch_splitk_reduce(skp, ks, (int64_t)M * N, dtype, c, alpha2, c2, st);
-        }
         g.c2 = c2; g.alpha2 = alpha2;
-        return launch_gemm_bf16(g, trace_id, st);
+        return launch_product(g, trace_id, c_f32 ? nullptr : skp, st);
     }
     return launch_sgemm_f32(f32_args(a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc), trace_id, st);
 }
@@ -344,11 +354,18 @@ struct FwdPlan {
     NormPlan norm;
     float *c, *g, *gm1;
     void *h, *lora, *hs, *base_a;
-    float* skp;   // K slices of the skinny product h = xa A^T (nullptr: not split)
+    float* skp;   // K slices of h = xa A^T, then of x W^T (nullptr: neither is split)
 };
 // Forward of a few tokens in 16-bit storage: two launches that stream the weights (few_tokens.hip) instead of tiles.
 // At 4096 x 4096, r = 384: 1 token 18 us against 41, 64 tokens 27 against 43 (from 65 tokens on the tiles take over).
 inline bool few_tokens(const dora_desc* d) { return is16(d->dtype) && d->tokens > 0 && d->tokens <= FEW_TOKENS_MAX; }
+
+// scratch for the K slices of a [tokens, n] product over k
+inline size_t slice_floats(const dora_desc* d, int64_t n, int64_t k)
+{
+    const int ks = product_ksplit(d->dtype, d->tokens, n, k);
+    return ks > 1 ? (size_t)ks * d->tokens * n : 0;
+}
 
 void plan_fwd(const dora_desc* d, Bump& b, FwdPlan& p, bool need_norm, bool need_h, bool need_lora,
               bool need_hs = false, bool need_base_a = false)
@@ -362,21 +379,16 @@ void plan_fwd(const dora_desc* d, Bump& b, FwdPlan& p, bool need_norm, bool need
     if (need_lora) p.lora = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
     if (need_hs) p.hs = b.take_bytes((size_t)d->tokens * d->r * esize(d->dtype));
     if (need_base_a) p.base_a = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
-    int ks = skinny_ksplit(d->dtype, d->tokens, d->r, d->d_in);
-    if (few_tokens(d)) {
-        const int few = few_tokens_h_slices(d->tokens, d->r, d->d_in);
-        ks = ks > 1 && ks > few ? ks : few;
-        p.skp = b.take<float>((size_t)ks * d->tokens * d->r);
-    } else if (ks > 1) {
-        p.skp = b.take<float>((size_t)ks * d->tokens * d->r);
-    }
+    size_t slices = few_tokens(d) ? (size_t)few_tokens_h_slices(d->tokens, d->r, d->d_in) * d->tokens * d->r : 0;
+    slices = std::max({slices, slice_floats(d, d->r, d->d_in), slice_floats(d, d->d_out, d->d_in)});
+    if (slices) p.skp = b.take<float>(slices);
 }
 
 struct BwdPlan {
     NormPlan norm;
     float *c, *g, *gm1, *dm_partial;
     void *dz, *dh, *h, *inner, *dzb;
-    float* skp;   // K slices of the skinny products dh = s dz B and (recomputed) h = xa A^T
+    float* skp;   // K slices of whichever product is under way (nullptr: none is split)
 };
 void plan_bwd(const dora_desc* d, Bump& b, BwdPlan& p, bool need_norm, bool need_h, bool need_inner,
               bool need_dzb = false)
@@ -392,10 +404,10 @@ void plan_bwd(const dora_desc* d, Bump& b, BwdPlan& p, bool need_norm, bool need
     if (need_h) p.h = b.take_bytes((size_t)d->tokens * d->r * esize(d->dtype));
     if (need_inner) p.inner = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
     if (need_dzb) p.dzb = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
-    const int ks_dh = skinny_ksplit(d->dtype, d->tokens, d->r, d->d_out);
-    const int ks_h = need_h ? skinny_ksplit(d->dtype, d->tokens, d->r, d->d_in) : 1;
-    const int ks = ks_dh > ks_h ? ks_dh : ks_h;
-    if (ks > 1) p.skp = b.take<float>((size_t)ks * d->tokens * d->r);
+    size_t slices = std::max(slice_floats(d, d->r, d->d_out), slice_floats(d, d->d_in, d->d_out));
+    if (need_h) slices = std::max(slices, slice_floats(d, d->r, d->d_in));
+    if (need_inner) slices = std::max(slices, slice_floats(d, d->d_out, d->d_in));
+    if (slices) p.skp = b.take<float>(slices);
 }
 
 dora_status check_ws(void* ws, size_t ws_bytes, size_t need)
@@ -423,7 +435,7 @@ dora_status forward_contractions(const dora_desc* d, const void* x, const void* 
         DORA_HIP(contract_f32_two(true, true, F32Product{T, d_out, s0, 1.f, base}, F32Product{T, r, s1, 1.f, h}, DORA_K_GEMM_BASE,
                                   DORA_K_GEMM_H, st));
     } else {
-        DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st));
+        DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st, skp));
         DORA_HIP(contract(d->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, st, skp));
     }
     Seg s2{h, r, B, r, r};
@@ -643,15 +655,15 @@ dora_status dora_project(const dora_desc* desc, const void* x, const void* W, co
     return forward_contractions(desc, x, W, A, B, base, h, lora, (hipStream_t)stream);
 }
 
-// inner = x W^T + s h B^T as one K-concatenated product  [s h | x] [B | W]^T, hs = s h; the caller sets epilogue and outputs
+// inner = x W^T + s h B^T as one K-concatenated product  [x | s h] [W | B]^T, hs = s h; the caller sets epilogue and outputs
 static GemmArgs inner_product(const dora_desc* d, const void* x, const void* W, const void* B, const void* hs)
 {
     const int T = (int)d->tokens, d_out = (int)d->d_out, d_in = (int)d->d_in, r = (int)d->r;
-    Seg segs[2] = {{hs, r, B, r, r}, {x, d_in, W, d_in, d_in}};
+    Seg segs[2] = {{x, d_in, W, d_in, d_in}, {hs, r, B, r, r}};
     return bf16_args(dt_of(d->dtype), true, true, T, d_out, segs, 2, 1.f, nullptr, d_out, false, 0);
 }
 
-// one_product: the K-concatenated forward (h, then [s h | x] [B | W]^T with the compose in its epilogue), else x W^T,
+// one_product: the K-concatenated forward (h, then [x | s h] [W | B]^T with the compose in its epilogue), else x W^T,
 // h B^T and a compose pass over both.
 static dora_status forward_impl(const dora_desc* desc, const void* x, const void* x_lora, const void* W, const void* A,
                                 const void* B, const float* m, const float* w_norm, const void* bias, void* y, void* saved_h,
@@ -700,7 +712,7 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
         g.colscale = p.g;
         g.colbias = (const bf16_t*)bias;
         g.c2 = saved_inner;
-        DORA_HIP(launch_gemm_bf16(g, DORA_K_GEMM_FUSED_FWD, s));
+        DORA_HIP(launch_product(g, DORA_K_GEMM_FUSED_FWD, p.skp, s));
         return DORA_OK;
     }
     // base lands in y and lora in the inner buffer; the compose pass then runs in place on both
@@ -713,7 +725,7 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     // LoRA dropout: the compose runs on the adapter branch's own base x_lora W^T and its delta is added to
     // the frozen layer's output already in y
     Seg sa{x_lora, d_in, W, d_in, d_in};
-    DORA_HIP(contract(desc->dtype, true, true, T, d_out, &sa, 1, 1.f, p.base_a, d_out, false, DORA_K_GEMM_BASE, s));
+    DORA_HIP(contract(desc->dtype, true, true, T, d_out, &sa, 1, 1.f, p.base_a, d_out, false, DORA_K_GEMM_BASE, s, p.skp));
     DORA_HIP(launch_compose_fwd(desc->dtype, p.base_a, lora, p.g, p.gm1, bias, desc->s, y, 2, saved_inner, T, d_out, s));
     return DORA_OK;
 }
@@ -800,7 +812,7 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp, p.dh, desc->s));
         GemmArgs g = inner_product(desc, xa, W, B, p.dh);
         g.c = p.inner;
-        DORA_HIP(launch_gemm_bf16(g, DORA_K_GEMM_FUSED_FWD, s));
+        DORA_HIP(launch_product(g, DORA_K_GEMM_FUSED_FWD, p.skp, s));
         inner = p.inner;
         h = p.h;
     } else if (T > 0 && need_inner) {
@@ -809,7 +821,7 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         void* hbuf = saved_h ? nullptr : p.h;
         if (saved_h) {
             Seg s0{xa, d_in, W, d_in, d_in};
-            DORA_HIP(contract(dt, true, true, T, d_out, &s0, 1, 1.f, p.dz, d_out, false, DORA_K_GEMM_BASE, s));
+            DORA_HIP(contract(dt, true, true, T, d_out, &s0, 1, 1.f, p.dz, d_out, false, DORA_K_GEMM_BASE, s, p.skp));
             Seg s2{saved_h, r, B, r, r};
             DORA_HIP(contract(dt, true, true, T, d_out, &s2, 1, 1.f, p.inner, d_out, false, DORA_K_GEMM_LORA, s));
         } else {
@@ -838,16 +850,16 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
     if (!dropout) {
         if (dx) {  // dx = dz W + dh A : one contraction over the concatenated K range
             Seg sx[2] = {{p.dz, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};
-            DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s));
+            DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
         }
     } else {
         if (dx) {  // frozen path: dx = dy W
             Seg sx{dy, d_out, W, d_in, d_out};
-            DORA_HIP(contract(dt, true, false, T, d_in, &sx, 1, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s));
+            DORA_HIP(contract(dt, true, false, T, d_in, &sx, 1, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
         }
         if (dx_lora) {  // adapter path: dx_lora = ((g-1) dy) W + dh A
             Seg sx[2] = {{p.dzb, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};
-            DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx_lora, d_in, false, DORA_K_GEMM_DX, s));
+            DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx_lora, d_in, false, DORA_K_GEMM_DX, s, p.skp));
         }
     }
     Seg sa{p.dh, r, xa, d_in, T};  // dA = dh^T xa

@@ -155,10 +155,12 @@ __global__ void gram_reduce_kernel(const float* __restrict__ p, int ksplit, int 
     Glo[i] = (bf16_t)(E::pack2(rem, 0.f) & 0xffffu);
 }
 
-// Sum of the K slices of a split contraction, in slice order, rounded once to the storage dtype.
+// Sum of the K slices of a split contraction, in slice order, rounded once to the storage dtype; with colscale the
+// first output is y = g (.) inner (+ bias), formed from the fp32 sum.
 template <typename T>
 __global__ void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, int64_t n, T* __restrict__ out,
-                                     float alpha2, T* __restrict__ out2)
+                                     float alpha2, T* __restrict__ out2, const float* __restrict__ colscale,
+                                     const T* __restrict__ colbias, int cols)
 {
     typedef Vec<T> V;
     constexpr int N = V::N;
@@ -174,7 +176,18 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, in
             acc[e] += v.x; acc[e + 1] += v.y; acc[e + 2] += v.z; acc[e + 3] += v.w;
         }
     }
-    *reinterpret_cast<typename V::raw_t*>(out + i) = V::pack(acc);
+    if (colscale) {
+        const int col = (int)(i % cols);
+        float v[N], bv[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) bv[e] = 0.f;
+        if (colbias) V::unpack(*reinterpret_cast<const typename V::raw_t*>(colbias + col), bv);
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[e] = fmaf(colscale[col + e], acc[e], bv[e]);
+        *reinterpret_cast<typename V::raw_t*>(out + i) = V::pack(v);
+    } else {
+        *reinterpret_cast<typename V::raw_t*>(out + i) = V::pack(acc);
+    }
     if (out2) {
 #pragma unroll
         for (int e = 0; e < N; ++e) acc[e] *= alpha2;
@@ -494,18 +507,21 @@ hipError_t launch_gram_reduce(const float* partials, int ksplit, int r, float* G
 }
 
 hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, int dtype, void* out, float alpha2, void* out2,
-                                hipStream_t st)
+                                hipStream_t st, const float* colscale, const void* colbias, int cols)
 {
     if (n == 0) return hipSuccess;
     TraceScope ts(DORA_K_SPLITK_REDUCE, st);
     const int per = dtype == DORA_F32 ? 4 : 8;
     dim3 grid((unsigned)((n / per + 255) / 256)), block(256);
     if (dtype == DORA_BF16)
-        splitk_reduce_kernel<bf16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (bf16_t*)out, alpha2, (bf16_t*)out2);
+        splitk_reduce_kernel<bf16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (bf16_t*)out, alpha2, (bf16_t*)out2, colscale,
+                                                    (const bf16_t*)colbias, cols);
     else if (dtype == DORA_F16)
-        splitk_reduce_kernel<f16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (f16_t*)out, alpha2, (f16_t*)out2);
+        splitk_reduce_kernel<f16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (f16_t*)out, alpha2, (f16_t*)out2, colscale,
+                                                    (const f16_t*)colbias, cols);
     else
-        splitk_reduce_kernel<float><<<grid, block, 0, st>>>(partials, ksplit, n, (float*)out, alpha2, (float*)out2);
+        splitk_reduce_kernel<float><<<grid, block, 0, st>>>(partials, ksplit, n, (float*)out, alpha2, (float*)out2, colscale,
+                                                    (const float*)colbias, cols);
     return hipGetLastError();
 }
 

@@ -225,15 +225,14 @@ __global__ __launch_bounds__(T::THREADS) void gemm_bf16_kernel(GemmPair grp)
     const TileCoord tc = map_tile(wg_id, tiles_m, tiles_n, p.ksplit);
     const int m0 = tc.tm * BM, n0 = tc.tn * BN;
 
-    // flattened K-step schedule over the segments; split-K slices segment 0 only
+    // flattened K-step schedule over the segments; split-K slices segment 0, the last slice takes segment 1 as well
     const int kt0_total = (p.seg[0].K + BK - 1) / BK;
     const int kt1_total = (p.nseg > 1) ? (p.seg[1].K + BK - 1) / BK : 0;
     int t_begin = 0, t_end = kt0_total + kt1_total;
     if (p.ksplit > 1) {
-        int per = (kt0_total + p.ksplit - 1) / p.ksplit;
-        t_begin = tc.z * per;
-        t_end = t_begin + per < kt0_total ? t_begin + per : kt0_total;
-        if (t_end < t_begin) t_end = t_begin;
+        const int per = (kt0_total + p.ksplit - 1) / p.ksplit;
+        t_begin = tc.z * per < kt0_total ? tc.z * per : kt0_total;
+        if (tc.z < p.ksplit - 1) t_end = t_begin + per < kt0_total ? t_begin + per : kt0_total;
     }
     const int nsteps = t_end - t_begin;
 

@@ -1,0 +1,65 @@
+"""16-bit products whose K is split because their tiles would leave most of the chip idle: x W^T with the low-rank segment in
+the last slice (and the compose in the reduce launch), dz W + dh A, dh and h; ragged K, a K whose slices are of unequal
+length, a single tile, and the entry points that share the scratch."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dora_oracle as O
+from paper_2603_22276_amd import binding as D
+from paper_2603_22276_amd import inputs as I
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # d_out, d_in, r, tokens: K of 2048 and above is split where the output has at most 128 tiles
+    (136, 4104, 40, 130), (4104, 264, 24, 130), (64, 2048, 8, 65), (264, 3080, 136, 300), (2056, 2056, 72, 333), (72, 9224, 64, 129),
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d_out,d_in,r,tokens", CASES)
+def test_split_products(dtype, d_out, d_in, r, tokens):
+    cfg = I.stress(I.DoraConfig(f"split_{d_out}_{d_in}_{r}_{tokens}", d_out, d_in, r, tokens, dtype, 32.0, 1e-3, seed_offset=9400))
+    mod = G.Module(cfg)
+    tol = G.TOL[dtype]["tensor"]
+    oi = dict(x=mod.f64("x"), W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=mod.inp["m"].astype(np.float64),
+              s=float(mod.inp["s"]), eps=cfg.eps)
+    f, b = O.forward(**oi), O.backward(mod.f64("dy"), **oi)
+    bias = torch.linspace(-1, 1, d_out, device=G.DEV).to(mod.W.dtype)
+    for fused in (False, True):
+        out = mod.forward(fused=fused)
+        for k in ("y", "h", "inner"):
+            G.assert_close(k, G.to_f64(out[k]), f[k], tol)
+        kept = mod.forward(w_norm=out["c"], save=False, fused=fused, bias=bias)
+        G.assert_close("y+bias", G.to_f64(kept["y"]), f["y"] + G.to_f64(bias), tol)
+    for grads in (mod.backward(w_norm=out["c"], h=out["h"], inner=out["inner"]), mod.backward(), mod.backward(h=out["h"])):
+        for k in ("dx", "dA", "dB", "dm"):
+            G.assert_close(k, G.to_f64(grads[k]), b[k], tol)
+
+
+@pytest.mark.parametrize("d_out,d_in", [(136, 4104), (4104, 136)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_split_products_with_an_adapter_input_of_its_own(dtype, d_out, d_in):
+    cfg = I.stress(I.DoraConfig(f"split_dropout_{d_out}", d_out, d_in, 40, 130, dtype, 32.0, 1e-3, seed_offset=9401))
+    mod = G.Module(cfg)
+    tol = G.TOL[dtype]["tensor"]
+    T, do, di, r = cfg.tokens, cfg.d_out, cfg.d_in, cfg.r
+    xl = I.dropped_input(cfg, mod.inp["x"], 0.25)
+    x_lora = G.to_dev(xl)
+    oi = dict(W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=mod.inp["m"].astype(np.float64), s=float(mod.inp["s"]), eps=cfg.eps)
+    f = O.forward(mod.f64("x"), **oi, x_lora=I.to_f64(xl))
+    b = O.backward_dropout(mod.f64("dy"), mod.f64("x"), I.to_f64(xl), **oi)
+    y, h, inner, c = G.empty((T, do), dtype), G.empty((T, r), dtype), G.empty((T, do), dtype), G.empty_f32(do)
+    D.dora_forward_dropout(mod.desc, mod.x, x_lora, mod.W, mod.A, mod.B, mod.m, None, None, y, h, inner, c,
+                           G.workspace(mod.desc, D.PHASE_FORWARD_DROPOUT))
+    for k, v in (("y", y), ("h", h), ("inner", inner)):
+        G.assert_close(k, G.to_f64(v), f[k], tol)
+    for saved in ((c, h, inner), (None, None, None)):
+        dx, dxl = G.empty((T, di), dtype), G.empty((T, di), dtype)
+        dA, dB, dm = G.empty_f32(r, di), G.empty_f32(do, r), G.empty_f32(do)
+        D.dora_backward_dropout(mod.desc, mod.dy, x_lora, mod.W, mod.A, mod.B, mod.m, *saved, dx, dxl, dA, dB, dm,
+                                G.workspace(mod.desc, D.PHASE_BACKWARD_DROPOUT))
+        for k, v in (("dx", dx), ("dx_lora", dxl), ("dA", dA), ("dB", dB), ("dm", dm)):
+            G.assert_close(k, G.to_f64(v), b[k], tol)
