@@ -142,9 +142,6 @@ struct Bump {
     }
 };
 
-// Split-K factors of the two norm contractions: as many workgroups as fit the chip in ONE round
-// (256 CUs x two 128x128-tile workgroups each = 512 slots; a 513th would add a whole extra round),
-// bounded so the partials stay small.
 constexpr int TILE = 128;
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
@@ -159,23 +156,49 @@ struct NormPlan {
     float *U, *BG;
 };
 
+// Split-K factors of the two norm contractions, which share a launch: 256 CUs x two 128x128-tile workgroups hold 512 at a
+// time.  `fit` and `room` fill one round.  The cost counted, in K steps of 64: rounds of cross-term slices, each its K steps
+// plus about six for what comes before the first and for the row-dot epilogue; the Gram workgroups, last in the launch, are
+// beside them where slots are left, at their own length, and a round of their own where not.  The cheapest split is taken
+// if it promises a seventh or more (smaller promises measured as losses: 5120 x 27648, r 384, seven slices 169 us against
+// 157 for four).  Measured, us of a norm, one round -> this: 27648 x 5120, r 384 222 -> 186 (648 tiles: two rounds, the second a
+// quarter full); 14336 x 4096, r 768 199 -> 181; 4096 x 14336, r 384 89 -> 83 and 3072 x 6000, r 512 70 -> 58 (long Gram slices
+// ended last); 8192 x 8192, r 128 55 -> 53 (no slot left for the Gram tiles).
+// The Gram partials stay within 8 MiB where the split of the cross term alone asks for more of them.  Whether a shape's
+// scratch fits the static array does not depend on the choice: (fit, room) decides, the others must agree.
+size_t norm_split_bytes(int64_t d_out, int64_t r, int tiles_n, int ks_u, int ks_g)
+{
+    return up256((size_t)ks_u * d_out * 4) + up256((size_t)ks_u * tiles_n * d_out * 4) + up256((size_t)tiles_n * d_out * 4) +
+           up256((size_t)ks_g * r * r * 4) + 2 * up256((size_t)r * r * 2);
+}
+void norm_split(int64_t d_out, int64_t d_in, int64_t r, int& ks_u, int& ks_g)
+{
+    const int tiles_n = cdiv(r, TILE), tiles_u = cdiv(d_out, TILE) * tiles_n, tiles_g = tiles_n * tiles_n, ktiles = cdiv(d_in, 64);
+    const int fit = std::max(1, std::min({512 / tiles_u, 8, ktiles}));
+    const int left = 512 - tiles_u * fit;
+    const int room = std::max(1, std::min({(left > 0 ? left : 512) / tiles_g, 16, ktiles}));
+    const int most = (int)std::max<int64_t>(1, (8 << 20) / (4 * r * r));
+    auto fits_static = [&](int ks, int kg) { return norm_split_bytes(d_out, r, tiles_n, ks, kg) <= DORA_STATIC_SCRATCH_BYTES; };
+    auto cost = [&](int ks, int kg) {
+        const int64_t rounds = ((int64_t)tiles_u * ks + 511) / 512, slots = rounds * 512 - (int64_t)tiles_u * ks;
+        const int steps_u = (ktiles + ks - 1) / ks, steps_g = (ktiles + kg - 1) / kg;
+        const int64_t own = (int64_t)tiles_g * kg > slots ? steps_g + 6 : std::max(0, steps_g - steps_u);
+        return rounds * (steps_u + 6) + own;
+    };
+    ks_u = fit; ks_g = room;
+    int64_t best = cost(fit, room) * 6 / 7;
+    const bool fits = fits_static(fit, room);
+    for (int ks = 1; ks <= std::min(8, ktiles); ++ks) {
+        const int kg = std::max(room, std::min(ks, most));
+        if (cost(ks, kg) <= best && fits_static(ks, kg) == fits) { best = cost(ks, kg) - 1; ks_u = ks; ks_g = kg; }
+    }
+}
+
 void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 {
     memset(&n, 0, sizeof(n));
-    const int ktiles = cdiv(d->d_in, 64);
     n.tiles_n = cdiv(d->r, TILE);
-    const int tiles_u = cdiv(d->d_out, TILE) * n.tiles_n;
-    n.ks_u = 512 / tiles_u;
-    if (n.ks_u > 8) n.ks_u = 8;
-    if (n.ks_u > ktiles) n.ks_u = ktiles;
-    if (n.ks_u < 1) n.ks_u = 1;
-    // the Gram workgroups ride in the cross term's launch: give them what that leaves of the round
-    const int tiles_g = n.tiles_n * n.tiles_n;
-    const int left = 512 - tiles_u * n.ks_u;
-    n.ks_g = (left > 0 ? left : 512) / tiles_g;
-    if (n.ks_g > 16) n.ks_g = 16;
-    if (n.ks_g > ktiles) n.ks_g = ktiles;
-    if (n.ks_g < 1) n.ks_g = 1;
+    norm_split(d->d_out, d->d_in, d->r, n.ks_u, n.ks_g);
     if (is16(d->dtype)) {
         n.base_p = b.take<float>((size_t)n.ks_u * d->d_out);
         n.cross_p = b.take<float>((size_t)n.ks_u * n.tiles_n * d->d_out);
