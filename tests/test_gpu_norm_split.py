@@ -1,0 +1,22 @@
+"""The split of the norm's cross term and Gram matrix over one launch: tiles that fill one round exactly, more tiles than
+one round holds, Gram slices bounded by their scratch, K of one step (no split possible) and K ragged in every slice."""
+import numpy as np
+import pytest
+
+from oracle import dora_oracle as O
+from paper_2603_22276_amd import inputs as I
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(8192, 1096, 128), (3072, 3016, 512), (9000, 1480, 384), (27648, 648, 384), (14336, 1160, 768), (4096, 64, 384), (520, 8, 8)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d_out,d_in,r", CASES)
+def test_norm_over_its_splits(dtype, d_out, d_in, r):
+    cfg = I.stress(I.DoraConfig(f"norm_split_{d_out}_{d_in}_{r}", d_out, d_in, r, 1, dtype, 32.0, 1e-3, seed_offset=9500))
+    mod = G.Module(cfg)
+    ref = O.dense_row_norm(mod.f64("W"), mod.f64("A"), mod.f64("B"), float(mod.inp["s"]))
+    G.assert_norm_close(G.to_f64(mod.norm()), ref, 1e-5)   # fp32 sums of exact products, Gram to 16 bits or better: no storage rounding
