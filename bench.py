@@ -551,7 +551,7 @@ def c3_extras(args, torch, D, G):
             other_step()
         ms_other, _ = time_steps(torch, other_step, args.steps)
         out["other_forward_path"] = {
-            "forward_path": "base, lora, compose pass" if args.fused_forward else "fused epilogue",
+            "forward_path": "dora_forward" if args.fused_forward else "dora_forward_fused",
             "ms_per_step_without_event_pairs": ms_other, "tokens_per_s": wl.tokens / (ms_other * 1e-3)}
         library = {}
         cfg = mod.cfg
@@ -658,7 +658,7 @@ def main():
         out.update({"dtype": "bf16" if cfg.dtype == "bf16" else "f32", "data": "synthetic",
                     "config": {"workload": wl.name, "tokens": wl.tokens, "phase": wl.phase_text,
                                "modules": [{"d_out": m.cfg.d_out, "d_in": m.cfg.d_in, "r": m.cfg.r} for m in wl.modules],
-                               "forward_path": "fused epilogue" if args.fused_forward else "base, lora, compose pass"}})
+                               "forward_path": "dora_forward_fused" if args.fused_forward else "dora_forward"}})
         if len(wl.modules) == 1:
             out["config"].update({"d_out": cfg.d_out, "d_in": cfg.d_in, "r": cfg.r})
         out["cpu_baseline"] = None if args.no_cpu_baseline else cpu_baseline(samples, args.config in ("C3", "C4"), note)

@@ -178,6 +178,7 @@ dora_status dora_project(const dora_desc* desc, const void* x, const void* W, co
 /*
  * Whole forward of the module (App. A item 1): norm (unless w_norm is given), g,
  * base = x W^T, h = x A^T, lora = h B^T, compose;  y = base + delta = g (.) (base + s*lora).
+ * DORA_BF16 runs the K-concatenated product of dora_forward_fused; DORA_F16 and DORA_F32 run base, lora and a compose pass.
  *   x [tokens, d_in], W, A, B : const `dtype`.   m : const fp32 [d_out].
  *   w_norm : const fp32 [d_out] or NULL (NULL: computed here into the workspace).
  *   bias : const `dtype` [d_out] or NULL: bias of the frozen base layer.  It takes no part in the
