@@ -9,13 +9,14 @@
 // d_out = 4096).  Here a workgroup owns 16 or 32 weight rows and its four waves split K, each streaming its own
 // share through a private LDS ring (buffer_load ... lds, 128-byte row segments, no barrier: only its own vmcnt), the
 // token rows beside them in the same ring; the four partial tiles meet in LDS at the end.
+#include "few_tokens_loads.hpp"
 #include "lds_tile.hpp"
 
 namespace dora {
 namespace {
 
 constexpr int WAVES = 4;
-constexpr int STEP_K = 64;   // k per ring slot: row segments of one 128-byte line (256-byte ones measured the same)
+constexpr int STEP_K = FewTokensLoads<1, 1>::STEP_K;   // k per ring slot: row segments of one 128-byte line (256-byte ones measured the same)
 
 // 16 bytes per lane from memory into 1 KB of LDS
 __device__ __forceinline__ void load_1k(char* lds, __amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t soffset)
@@ -28,11 +29,11 @@ template <int TB, int MR, int DEPTH, bool FINAL, int DT>
 __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
 {
     typedef Elem16<DT> E;
-    constexpr int ROWS = MR * 16, TOK = TB * 16;
+    typedef FewTokensLoads<TB, MR> L;
+    constexpr int ROWS = L::ROWS, TOK = L::TOK;
     constexpr int SLOT_BYTES = (ROWS + TOK) * STEP_K * 2;
-    constexpr int CPR = STEP_K / 8, RPL = 64 / CPR;    // 16-byte chunks of a row segment, rows per wave-wide load
-    constexpr int LPS = (ROWS + TOK) / RPL;            // wave-wide loads per ring slot
-    constexpr int LPB = 16 / RPL;                      // of them per block of 16 rows
+    constexpr int LPS = L::COUNT;                      // wave-wide loads per ring slot
+    constexpr int LPB = 16 / L::LOAD_ROWS;             // of them per block of 16 rows
     constexpr int KSTEPS = STEP_K / 32;                // MFMA k-steps per ring slot
     constexpr int RED_LD = ROWS + 4;
     constexpr int RING_BYTES = WAVES * DEPTH * SLOT_BYTES, RED_BYTES = WAVES * TOK * RED_LD * 4;
@@ -53,35 +54,36 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     const int parts = p.ksplit * WAVES, part = z * WAVES + wave;
     const int s_begin = (int)((int64_t)steps * part / parts), s_end = (int)((int64_t)steps * (part + 1) / parts);
 
-    // descriptors of the weight rows of this group and of the token rows; rows past the end lie beyond them and load zeros
+    // descriptors of the weight rows of this group and of the token rows
     const int w_rows = N - n0 < ROWS ? N - n0 : ROWS;
     __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.w + (int64_t)n0 * K), 0,
                                                                   (int)(uint32_t)((int64_t)w_rows * K * 2), 0x00020000);
     __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.x), 0, (int)(uint32_t)((int64_t)T * K * 2),
                                                                   0x00020000);
-    // lane -> (row, chunk) of load i of a 16-row block
-    uint32_t vo[LPB];
+    // per-lane offsets of a slot's loads at k0 = 0; the swizzle, and with it k, repeats every 16 rows
+    uint32_t vo[LPS];
     int kl[LPB];
 #pragma unroll
-    for (int i = 0; i < LPB; ++i) {
-        const int row = i * RPL + lane / CPR;
-        kl[i] = ((lane % CPR) ^ kc_swizzle<STEP_K>(row)) * 8;
-        vo[i] = (uint32_t)(row * K + kl[i]) * 2u;
+    for (int i = 0; i < LPS; ++i) {
+        const int row = L::row(i, lane);
+        const int k = ((lane % L::LANES_PER_ROW) ^ kc_swizzle<STEP_K>(row)) * 8;
+        vo[i] = L::vector_offset(row, L::weights(i) ? w_rows : T, k, K);
+        if (i < LPB) kl[i] = k;
     }
     char* const ring = smem + wave * (DEPTH * SLOT_BYTES);
     auto issue = [&](int s, int slot) {
         char* tile = ring + slot * SLOT_BYTES;
         const int k0 = s * STEP_K;
-        uint32_t v[LPB];
-#pragma unroll
-        for (int i = 0; i < LPB; ++i) v[i] = (s < s_end && k0 + kl[i] < K) ? vo[i] : 0xFFFFFFFFu;
-        static_for<LPS>([&](auto it) {
-            constexpr int i = decltype(it)::value;
-            constexpr int blk = i / LPB;               // 16-row block of the slot: weights first, then tokens
-            constexpr int tok_blk = blk < MR ? 0 : blk - MR;
-            const uint32_t so = (uint32_t)(((blk < MR ? blk : tok_blk) * 16 * (int64_t)K + k0) * 2);
-            load_1k(tile + i * 1024, blk < MR ? rw : rx, v[i % LPB], so);
-        });
+        const int k_end = s < s_end ? K : 0;           // a step past this wave's share brings zeros
+        auto load_slot = [&](auto&& offset) {
+            static_for<LPS>([&](auto it) {
+                constexpr int i = decltype(it)::value;
+                load_1k(tile + i * 1024, L::weights(i) ? rw : rx, offset(i), L::scalar_offset(k0));
+            });
+        };
+        // whole steps take their offsets as they are (masked every time, 122 shapes take 0.6 % longer on average)
+        if (k0 + STEP_K <= k_end) load_slot([&](int i) { return vo[i]; });
+        else load_slot([&](int i) { return L::step_offset(vo[i], kl[i % LPB], k0, k_end); });
     };
 
     f32x4_t acc[MR][TB], accl[MR][TB];
