@@ -1,6 +1,8 @@
 """Forward of a few tokens (the weight-streaming kernels): both forward entry points against the fp64 oracle where
 these kernels can go wrong - edges of the 16-token and 16-row blocks, K shorter than one ring slot, ragged K, more
-waves than K steps, ranks that end inside a k-step - up to the first token count that takes the tiled path."""
+waves than K steps, ranks that end inside a k-step - up to the first token count that takes the tiled path; then every
+tile the y launch chooses from: 64 weight rows per workgroup beyond 8192 of them, 32 between 4096 and 8192 with more than
+32 tokens, with a ragged last group and token counts that end inside and right before a block of 16."""
 import numpy as np
 import pytest
 import torch
@@ -16,6 +18,8 @@ pytestmark = pytest.mark.gpu
 CASES = [  # d_out, d_in, r, tokens
     (8, 8, 8, 1), (24, 64, 8, 2), (264, 72, 24, 15), (200, 1000, 40, 16), (520, 392, 136, 17), (72, 2312, 384, 31),
     (1032, 520, 72, 32), (136, 4104, 40, 33), (520, 264, 392, 48), (264, 1032, 8, 64), (264, 392, 40, 65),
+    (8200, 72, 24, 1), (8248, 136, 8, 17), (8264, 200, 40, 33), (8256, 64, 8, 64), (4104, 136, 24, 33), (8184, 72, 8, 64),
+    (8216, 72, 16, 48), (4112, 200, 8, 49),
 ]
 
 
