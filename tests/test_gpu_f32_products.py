@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 CASES = [  # d_out, d_in, r, tokens
     (4, 4, 4, 1), (36, 20, 4, 3), (32, 252, 8, 33), (260, 256, 12, 31), (64, 260, 20, 257), (132, 1028, 36, 65),
     (512, 68, 4, 1021), (516, 516, 72, 961), (1000, 772, 36, 1500),
+    # 195 tiles of 64 x 64 in dA, then in dB: both operands K-strided, K (tokens) shorter and longer than a step, no multiple of four
+    (68, 4100, 132, 37), (4100, 68, 132, 37), (68, 4100, 132, 1), (4100, 68, 132, 101),
 ]
 
 
