@@ -379,9 +379,30 @@ struct FwdPlan {
     void *h, *lora, *hs, *base_a;
     float* skp;   // K slices of h = xa A^T, then of x W^T (nullptr: neither is split)
 };
-// Forward of a few tokens in 16-bit storage: two launches that stream the weights (few_tokens.hip) instead of tiles.
-// At 4096 x 4096, r = 384: 1 token 18 us against 41, 64 tokens 27 against 43 (from 65 tokens on the tiles take over).
-inline bool few_tokens(const dora_desc* d) { return is16(d->dtype) && d->tokens > 0 && d->tokens <= FEW_TOKENS_MAX; }
+// Forward of a few tokens in 16-bit storage: two launches that stream the weights (few_tokens.hip) instead of tiles, where
+// they are the faster ones.  Every workgroup of the second launch first sums h and multiplies it with its rows of B, which
+// costs tokens times rank whatever d_in is, and beyond 16384 rows of W its workgroups need a second round.  Measured with
+// weights and inputs rotated through 600 MB, time against the tiles' (one_product: the K-concatenated product):
+//   up to 16384 rows: 4096 x 4096, r 384, 1 token 20 us / 36, 64 tokens 34 / 40; 17 to 32 tokens 0.85 to 1.1 at r 1536, up
+//     to 1.1 beyond; 33 to 64 tokens 0.78 to 0.96 at r 640, 0.92 to 1.09 at 768 (the upper half past 48 tokens),
+//     1.2 to 1.4 at 1536 (8192 x 2048, r 2048, 64 tokens 78 us / 54)
+//   beyond: up to 16 tokens 0.5 to 0.9 up to r 2048 (past 32768 rows 0.9 to 1.0 at 1024, 1.1 at 1536); 17 to 32 tokens 0.8 to
+//     1.03 up to r 256, 1.0 to 1.1 at 384, and up to 1.2 for d_in 8192; 33 to 64 tokens 0.8 to 1.0 up to r 128 for d_in 2048
+//     to 4096, 1.0 to 1.3 for shorter rows (27648 x 5120, r 384, 64 tokens 112 us / 96)
+// Base, lora and a compose pass are slower tiles, so against those the lines lie further out: 0.8 to 0.95 at r 1024 and 64
+// tokens, and beyond 16384 rows up to 16 tokens 0.4 to 1.05, 32 tokens 0.7 to 1.0 at r 384, 64 tokens 0.8 to 1.0 at r 256.
+inline bool few_tokens(const dora_desc* d, bool one_product)
+{
+    const int64_t T = d->tokens, r = d->r;
+    if (!is16(d->dtype) || T <= 0 || T > FEW_TOKENS_MAX) return false;
+    if (d->d_out <= 16384) {
+        if (T <= 32) return T <= 16 || !one_product || r <= 1536;
+        return r <= (one_product ? (T <= 48 ? 768 : 640) : 1024);
+    }
+    if (T <= 16) return !one_product || r <= (d->d_out <= 32768 ? 2048 : 1024);
+    if (T <= 32) return r <= (one_product ? 256 : 512) && d->d_in <= 5120;
+    return one_product ? r <= 128 && d->d_in >= 2048 && d->d_in <= 4096 : r <= 256 && d->d_in <= 4096;
+}
 
 // scratch for the K slices of a [tokens, n] product over k
 inline size_t slice_floats(const dora_desc* d, int64_t n, int64_t k)
@@ -402,7 +423,8 @@ void plan_fwd(const dora_desc* d, Bump& b, FwdPlan& p, bool need_norm, bool need
     if (need_lora) p.lora = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
     if (need_hs) p.hs = b.take_bytes((size_t)d->tokens * d->r * esize(d->dtype));
     if (need_base_a) p.base_a = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
-    size_t slices = few_tokens(d) ? (size_t)few_tokens_h_slices(d->tokens, d->r, d->d_in) * d->tokens * d->r : 0;
+    // (where the K-concatenated product gives way to few_tokens, the compose pass does too)
+    size_t slices = few_tokens(d, false) ? (size_t)few_tokens_h_slices(d->tokens, d->r, d->d_in) * d->tokens * d->r : 0;
     slices = std::max({slices, slice_floats(d, d->r, d->d_in), slice_floats(d, d->d_out, d->d_in)});
     if (slices) p.skp = b.take<float>(slices);
 }
@@ -721,7 +743,7 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
         DORA_HIP(hipMemcpyAsync(w_norm_out, w_norm, sizeof(float) * d_out, hipMemcpyDeviceToDevice, s));
     }
     if (T == 0) return DORA_OK;
-    if (!dropout && few_tokens(desc))
+    if (!dropout && few_tokens(desc, one_product))
         return forward_few_tokens(desc, x, W, A, B, m, c, bias, y, saved_h, saved_inner, p.skp, s);
     if (!mag.done) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, gm1, d_out, s));
     void* h = saved_h ? saved_h : p.h;
