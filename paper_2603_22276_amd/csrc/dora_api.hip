@@ -173,33 +173,38 @@ size_t norm_split_bytes(int64_t d_out, int64_t r, int tiles_n, int ks_u, int ks_
 }
 void norm_split(int64_t d_out, int64_t d_in, int64_t r, int& ks_u, int& ks_g)
 {
-    const int tiles_n = cdiv(r, TILE), tiles_u = cdiv(d_out, TILE) * tiles_n, tiles_g = tiles_n * tiles_n, ktiles = cdiv(d_in, 64);
-    const int fit = std::max(1, std::min({512 / tiles_u, 8, ktiles}));
-    const int left = 512 - tiles_u * fit;
-    const int room = std::max(1, std::min({(left > 0 ? left : 512) / tiles_g, 16, ktiles}));
-    const int most = (int)std::max<int64_t>(1, (8 << 20) / (4 * r * r));
-    auto fits_static = [&](int ks, int kg) { return norm_split_bytes(d_out, r, tiles_n, ks, kg) <= DORA_STATIC_SCRATCH_BYTES; };
-    auto cost = [&](int ks, int kg) {
-        const int64_t rounds = ((int64_t)tiles_u * ks + 511) / 512, slots = rounds * 512 - (int64_t)tiles_u * ks;
-        const int steps_u = (ktiles + ks - 1) / ks, steps_g = (ktiles + kg - 1) / kg;
-        const int64_t own = (int64_t)tiles_g * kg > slots ? steps_g + 6 : std::max(0, steps_g - steps_u);
+    // 64 bits: the tiles of G alone number up to (2^28 / TILE)^2
+    const int64_t tiles_n = (r + TILE - 1) / TILE, tiles_u = (d_out + TILE - 1) / TILE * tiles_n, tiles_g = tiles_n * tiles_n;
+    const int64_t ktiles = (d_in + 63) / 64;
+    const int64_t fit = std::max<int64_t>(1, std::min<int64_t>({512 / tiles_u, 8, ktiles}));
+    const int64_t left = 512 - tiles_u * fit;
+    const int64_t room = std::max<int64_t>(1, std::min<int64_t>({(left > 0 ? left : 512) / tiles_g, 16, ktiles}));
+    const int64_t most = std::max<int64_t>(1, (8 << 20) / (4 * r * r));
+    auto fits_static = [&](int64_t ks, int64_t kg) {
+        return norm_split_bytes(d_out, r, (int)tiles_n, (int)ks, (int)kg) <= DORA_STATIC_SCRATCH_BYTES;
+    };
+    auto cost = [&](int64_t ks, int64_t kg) {
+        const int64_t rounds = (tiles_u * ks + 511) / 512, slots = rounds * 512 - tiles_u * ks;
+        const int64_t steps_u = (ktiles + ks - 1) / ks, steps_g = (ktiles + kg - 1) / kg;
+        const int64_t own = tiles_g * kg > slots ? steps_g + 6 : std::max<int64_t>(0, steps_g - steps_u);
         return rounds * (steps_u + 6) + own;
     };
-    ks_u = fit; ks_g = room;
-    int64_t best = cost(fit, room) * 6 / 7;
+    int64_t best_u = fit, best_g = room, best = cost(fit, room) * 6 / 7;
     const bool fits = fits_static(fit, room);
-    for (int ks = 1; ks <= std::min(8, ktiles); ++ks) {
-        const int kg = std::max(room, std::min(ks, most));
-        if (cost(ks, kg) <= best && fits_static(ks, kg) == fits) { best = cost(ks, kg) - 1; ks_u = ks; ks_g = kg; }
+    for (int64_t ks = 1; ks <= std::min<int64_t>(8, ktiles); ++ks) {
+        const int64_t kg = std::max(room, std::min(ks, most));
+        if (cost(ks, kg) <= best && fits_static(ks, kg) == fits) { best = cost(ks, kg) - 1; best_u = ks; best_g = kg; }
     }
+    ks_u = (int)best_u;
+    ks_g = (int)best_g;
 }
 
 void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 {
     memset(&n, 0, sizeof(n));
     n.tiles_n = cdiv(d->r, TILE);
-    norm_split(d->d_out, d->d_in, d->r, n.ks_u, n.ks_g);
     if (is16(d->dtype)) {
+        norm_split(d->d_out, d->d_in, d->r, n.ks_u, n.ks_g);
         n.base_p = b.take<float>((size_t)n.ks_u * d->d_out);
         n.cross_p = b.take<float>((size_t)n.ks_u * n.tiles_n * d->d_out);
         n.ba_p = b.take<float>((size_t)n.tiles_n * d->d_out);

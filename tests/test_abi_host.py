@@ -61,6 +61,15 @@ def test_workspace_sizes():
     assert D.dora_workspace_bytes(desc(d_out=64, tokens=4_000_000, d_in=8, r=8), D.PHASE_BACKWARD) > 0
 
 
+def test_largest_ranks_size_a_workspace():
+    # tiles of the Gram matrix past 32 bits: 65536 x 65536 of them, and the largest rank a tensor of 2^31 elements allows
+    for r in (8388608, 2 ** 28 - 8):
+        for dtype in (D.DORA_BF16, D.DORA_F16, D.DORA_F32):
+            d = desc(d_out=8 if dtype != D.DORA_F32 else 4, d_in=8 if dtype != D.DORA_F32 else 4, r=r, tokens=0, dtype=dtype)
+            for phase in (D.PHASE_NORM, D.PHASE_FORWARD, D.PHASE_BACKWARD_RECOMPUTE):
+                assert D.dora_workspace_bytes(d, phase) > r * r * 4
+
+
 def call(fn, *args):
     with pytest.raises(D.DoraError) as e:
         fn(*args)
