@@ -16,7 +16,8 @@
  *     are never held in fp16.
  *   - Shape limits: d_out, d_in, r multiples of 8 (bf16, fp16) or of 4 (fp32);
  *     tokens >= 0 (0 is a no-op that still
- *     computes weight-only results); every tensor below 2^31 elements.
+ *     computes weight-only results); every tensor below 2^31 elements, the Gram
+ *     matrix [r, r] included where a call forms the norm in bf16 or fp16 (s != 0).
  *   - `ws` is caller-provided scratch of at least dora_workspace_bytes(desc,
  *     phase) bytes, 256-byte aligned.  The library allocates no device memory,
  *     keeps no state between calls, enqueues everything on `stream` (a

@@ -332,6 +332,7 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
         return DORA_OK;
     }
     if (is16(d->dtype)) {
+        if ((int64_t)r * r >= MAX_ELEMS) return DORA_ERR_SHAPE;   // G is an operand of the B G product
         const int dt = dt_of(d->dtype);
         GemmArgs g;
         // cross term (Eq. 3) and base term: U = W A^T tile by tile, reduced against B in registers

@@ -70,6 +70,19 @@ def test_largest_ranks_size_a_workspace():
                 assert D.dora_workspace_bytes(d, phase) > r * r * 4
 
 
+def test_rank_whose_gram_matrix_cannot_be_an_operand_is_refused():
+    L = D.lib()
+    for r in (46344, 65536, 65544):   # r * r past 2^31, and past 2^32 where 32 bits wrap to 0 and to a small number
+        for dtype in (D.DORA_BF16, D.DORA_F16):
+            d = desc(d_out=8, d_in=8, r=r, tokens=0, dtype=dtype)
+            big = D.dora_workspace_bytes(d, D.PHASE_BACKWARD_RECOMPUTE)
+            assert L.dora_norm(ctypes.byref(d), FAKE, FAKE, FAKE, FAKE, FAKE, big, None) == 2
+            assert L.dora_norm_terms(ctypes.byref(d), FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, big, None) == 2
+            assert L.dora_forward(ctypes.byref(d), None, FAKE, FAKE, FAKE, FAKE, None, None, None, None, None, None, FAKE, big, None) == 2
+            assert L.dora_backward(ctypes.byref(d), None, None, FAKE, FAKE, FAKE, FAKE, None, None, None, None, FAKE, FAKE, None,
+                                   FAKE, big, None) == 2
+
+
 def call(fn, *args):
     with pytest.raises(D.DoraError) as e:
         fn(*args)
