@@ -148,3 +148,18 @@ def test_no_mfma_reads_a_fragment_before_its_wait(tmp_path):
     bad = {k: h for k, h in ((k, lint_kernel(v)) for k, v in kernels.items()) if h}
     assert not bad, "MFMA issued before the LDS read feeding it is covered by a wait: %r" % (
         {k[-60:]: h[:3] for k, h in bad.items()},)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_no_mfma_of_the_few_token_kernel_reads_a_fragment_before_its_wait(tmp_path):
+    asm = tmp_path / "few_tokens.s"
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-S", "--cuda-device-only", "-o", str(asm), os.path.join(ROOT, "paper_2603_22276_amd", "csrc", "few_tokens.hip")]
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert proc.returncode == 0, proc.stdout[-2000:]
+    kernels = dict(re.findall(r"^(_ZN\S*few_tokens_kernel\S*):[^\n]*\n(.*?)^\.Lfunc_end", asm.read_text(), flags=re.S | re.M))
+    assert len(kernels) == 20, "ten tiles in each of the two 16-bit types"
+    for name, text in kernels.items():
+        lines = text.split("\n")
+        assert any("v_mfma" in l for l in lines) and sum("ds_read_b128" in l for l in lines) >= 4, name
+        assert not lint_kernel(lines), name
