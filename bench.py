@@ -33,11 +33,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3    # MI355X fp32 vector ALU (the fp32 configuration runs on the VALU)
+PEAK_FP32_TFLOPS = 157.3    # MI355X fp32 MFMA (the vector ALU has the same rate)
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 
 HBM_BOUND = {"compose_fwd", "compose_bwd", "mag_scale"}
-K_BASE, K_DX, K_FUSED = 6, 13, 18
+K_BASE, K_COMPOSE_FWD, K_DX, K_FUSED = 6, 9, 13, 18
 N_KERNEL_IDS = 20
 METRIC_FMT = "DoRA {phase} tokens/s at d_in={d_in} r={r} {dtype}; %MFMA and %HBM peak"
 
@@ -291,14 +291,14 @@ def kernel_table(D, torch, wl, reps, dominant_live):
         if hbm:
             bound, ach, peak, unit = "hbm", nbytes / secs / 1e9, PEAK_HBM_GBS, "GB/s"
         elif fp32:
-            bound, ach, peak, unit = "alu", flops / secs / 1e12, PEAK_FP32_TFLOPS, "TFLOP/s"
+            bound, ach, peak, unit = "mfma", flops / secs / 1e12, PEAK_FP32_TFLOPS, "TFLOP/s"
         else:
             bound, ach, peak, unit = "mfma", flops / secs / 1e12, PEAK_BF16_TFLOPS, "TFLOP/s"
         kernels.append({"kernel": n, "launches_per_step": t["launches"] / reps, "avg_us": secs / t["launches"] * 1e6,
                         "us_per_step": secs / reps * 1e6, "bound": bound, "achieved": ach, "peak": peak, "unit": unit,
                         "frac": ach / peak, "gbytes_per_s_algorithmic": nbytes / secs / 1e9,
                         "timed": "inside the timed steps" if live and live[1] > 0 else "separate pass, every launch bracketed"})
-    contr = [k for k in kernels if k["bound"] in ("mfma", "alu") and tot[k["kernel"]]["flops"] > 0]
+    contr = [k for k in kernels if k["bound"] == "mfma" and tot[k["kernel"]]["flops"] > 0]
     flops = sum(tot[k["kernel"]]["flops"] for k in contr)
     secs = sum(k["us_per_step"] for k in contr) * 1e-6
     return kernels, (flops / secs / 1e12 if secs > 0 else None)
@@ -490,7 +490,7 @@ def measure(wl, args, torch, D, extras):
         "warmup": args.warmup, "ms_per_step": ms_per_step, "step_ms_hip_events": per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "roofline": roofline,
-        "mfma_frac_all_contractions": (contr_rate / (PEAK_BF16_TFLOPS if dom["bound"] != "alu" else PEAK_FP32_TFLOPS)
+        "mfma_frac_all_contractions": (contr_rate / (PEAK_FP32_TFLOPS if wl.modules[0].cfg.dtype == "f32" else PEAK_BF16_TFLOPS)
                                        if contr_rate else None),
         "hbm_frac_compose_fwd": next((k["frac"] for k in kernels if k["kernel"] == "compose_fwd"), None),
         "hbm_frac_compose_bwd": next((k["frac"] for k in kernels if k["kernel"] == "compose_bwd"), None),
@@ -524,8 +524,8 @@ def recompute_extras(args, torch):
 
 
 def c3_extras(args, torch, D, G):
-    """Figures reported beside `value` for the single bf16 modules: the step as a HIP graph, the other forward
-    path, and what this card sustains on a plain copy and a register-resident MFMA loop."""
+    """Figures reported beside `value` for the single bf16 modules: the step as a HIP graph, the forward as separate
+    calls, and what this card sustains on a plain copy and a register-resident MFMA loop."""
     def extras(wl, ms_untraced):
         mod = wl.modules[0]
         desc = mod.desc
@@ -542,19 +542,38 @@ def c3_extras(args, torch, D, G):
         except Exception as exc:  # pragma: no cover - informational figure only
             print(f"bench.py: graph replay not measured ({exc})", file=sys.stderr)
         out["ms_per_step_graph_replay"] = ms_graph
-        other = D.dora_forward if args.fused_forward else D.dora_forward_fused
+        # the forward as separate calls, with base, h and lora in memory and a compose pass over them: what dora_forward does
+        # in fp16 and fp32 (in bf16 it is one product, and dora_forward_fused makes the same launches)
+        cfg = mod.cfg
+        base, lora = torch.empty_like(mod.y), torch.empty_like(mod.y)
+        h = mod.h if mod.h is not None else torch.empty((cfg.tokens, cfg.r), dtype=mod.y.dtype, device=G.DEV)
+        g, gm1 = torch.empty_like(mod.c), torch.empty_like(mod.c)
 
         def other_step():
-            mod.forward(other)
+            D.dora_norm(desc, mod.W, mod.A, mod.B, mod.c, mod.ws)
+            D.dora_mag_scale(desc, mod.m, mod.c, g, gm1)
+            D.dora_project(desc, mod.x, mod.W, mod.A, mod.B, base, h, lora)
+            D.dora_compose(desc, base, lora, g, gm1, mod.y, False, mod.inner)
             mod.backward()
         for _ in range(2):
             other_step()
         ms_other, _ = time_steps(torch, other_step, args.steps)
+        D.dora_trace_reset()
+        D.dora_trace_select(1 << K_COMPOSE_FWD)
+        D.dora_trace_enable(True)
+        for _ in range(args.steps):
+            other_step()
+        torch.cuda.synchronize()
+        D.dora_trace_enable(False)
+        D.dora_trace_collect()
+        compose_ms, compose_n = D.dora_trace_get(K_COMPOSE_FWD)
+        compose_bytes = kernel_work(cfg, inner_saved=mod.inner is not None)["compose_fwd"][1]
         out["other_forward_path"] = {
-            "forward_path": "dora_forward" if args.fused_forward else "dora_forward_fused",
-            "ms_per_step_without_event_pairs": ms_other, "tokens_per_s": wl.tokens / (ms_other * 1e-3)}
+            "forward_path": "dora_norm, dora_mag_scale, dora_project, dora_compose",
+            "ms_per_step_without_event_pairs": ms_other, "tokens_per_s": wl.tokens / (ms_other * 1e-3),
+            "hbm_frac_compose_fwd": compose_bytes * compose_n / (compose_ms * 1e-3) / 1e9 / PEAK_HBM_GBS}
+        del base, lora
         library = {}
-        cfg = mod.cfg
         if cfg.dtype == "bf16":
             # the vendor library's GEMM on this module's own x and W, for context (HIP events on torch's stream)
             yy = torch.empty((cfg.tokens, cfg.d_out), dtype=torch.bfloat16, device=G.DEV)
@@ -626,8 +645,7 @@ def main():
     ap.add_argument("--c5-layers", type=int, default=32)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--fused-forward", action="store_true",
-                    help="forward through dora_forward_fused (compose folded into the GEMM epilogue) instead of the\n"
-                         "base / lora / compose sequence (C2, C3)")
+                    help="forward through dora_forward_fused (C2, C3; in bf16 dora_forward makes the same launches)")
     ap.add_argument("--cpu-sample-tokens", type=int, default=0,
                     help="tokens of the oracle's sample (default: the whole batch; 1024 per module for C4)")
     ap.add_argument("--norm-sweep", action="store_true",
