@@ -170,8 +170,10 @@ dora_status dora_compose_backward(const dora_desc* desc, const void* dy, const v
 /*
  * The three forward contractions on their own (App. A item 1): base = x W^T [tokens, d_out],
  * h = x A^T [tokens, r], lora = h B^T [tokens, d_out], each rounded once to `dtype`.
- * The launches dora_forward makes for these steps, except that without a workspace h = x A^T is never
- * split along K (dora_forward splits it when its tiles would leave most of the chip idle).  Needs no workspace.
+ * DORA_F32, and DORA_F16 beyond a few tokens: the launches dora_forward makes for these steps, except that without
+ * a workspace no product is split along K (dora_forward splits base and h when their tiles would leave most of the
+ * chip idle).  dora_forward in DORA_BF16 and of a few tokens forms y in other launches, with fewer roundings.  Needs
+ * no workspace.
  */
 dora_status dora_project(const dora_desc* desc, const void* x, const void* W, const void* A, const void* B,
                          void* base, void* h, void* lora, void* stream);
@@ -180,6 +182,7 @@ dora_status dora_project(const dora_desc* desc, const void* x, const void* W, co
  * Whole forward of the module (App. A item 1): norm (unless w_norm is given), g,
  * base = x W^T, h = x A^T, lora = h B^T, compose;  y = base + delta = g (.) (base + s*lora).
  * DORA_BF16 runs the K-concatenated product of dora_forward_fused; DORA_F16 and DORA_F32 run base, lora and a compose pass.
+ * Up to 64 tokens in either 16-bit type: two launches that stream A and W once, where they are the faster ones.
  *   x [tokens, d_in], W, A, B : const `dtype`.   m : const fp32 [d_out].
  *   w_norm : const fp32 [d_out] or NULL (NULL: computed here into the workspace).
  *   bias : const `dtype` [d_out] or NULL: bias of the frozen base layer.  It takes no part in the
@@ -196,7 +199,7 @@ dora_status dora_forward(const dora_desc* desc, const void* x, const void* W, co
 
 /*
  * Same result as dora_forward, computed without the base / lora round trip: one K-concatenated
- * contraction  inner = [s*h | x] [B | W]^T  (the h = x A^T product writes both h and s*h from its
+ * contraction  inner = [x | s*h] [W | B]^T  (the h = x A^T product writes both h and s*h from its
  * accumulators) whose epilogue writes y = g (.) inner (+ bias) and, if asked, inner.
  * The cancellation issue of Sec. 3.1 concerns the *delta* form only; g (.) inner taken from an fp32
  * accumulator has none.  DORA_BF16 and DORA_F16 descs only (DORA_ERR_DTYPE otherwise).  Arguments, workspace

@@ -38,12 +38,12 @@ enum {
     DORA_K_DM_FINAL = 11,    /* second stage of the dm column reduction                */
     DORA_K_GEMM_DH = 12,     /* dh = s dz B                                            */
     DORA_K_GEMM_DX = 13,     /* dx = dz W + dh A                                       */
-    DORA_K_GEMM_DA = 14,     /* dA = dh^T x (bf16: the same launch also computes dB)   */
+    DORA_K_GEMM_DA = 14,     /* dA = dh^T x (16-bit, small fp32: dB in the same launch)*/
     DORA_K_GEMM_DB = 15,     /* dB = s dz^T h                                          */
     DORA_K_PROBE_COPY = 16,  /* dora_probe_copy                                        */
     DORA_K_PROBE_MFMA = 17,  /* dora_probe_mfma                                        */
-    DORA_K_GEMM_FUSED_FWD = 18, /* y = g (.) ([s*h | x] [B | W]^T), dora_forward_fused  */
-    DORA_K_SPLITK_REDUCE = 19,  /* fixed-order sum of the K slices of a skinny product    */
+    DORA_K_GEMM_FUSED_FWD = 18, /* y = g (.) ([x | s*h] [W | B]^T); y of a few tokens    */
+    DORA_K_SPLITK_REDUCE = 19,  /* fixed-order sum of the K slices of a short product     */
     DORA_K_COUNT = 20
 };
 void dora_trace_enable(int on);

@@ -161,9 +161,9 @@ struct NormPlan {
 // plus about six for what comes before the first and for the row-dot epilogue; the Gram workgroups, last in the launch, are
 // beside them where slots are left, at their own length, and a round of their own where not.  The cheapest split is taken
 // if it promises a seventh or more (smaller promises measured as losses: 5120 x 27648, r 384, seven slices 169 us against
-// 157 for four).  Measured, us of a norm, one round -> this: 27648 x 5120, r 384 222 -> 186 (648 tiles: two rounds, the second a
-// quarter full); 14336 x 4096, r 768 199 -> 181; 4096 x 14336, r 384 89 -> 83 and 3072 x 6000, r 512 70 -> 58 (long Gram slices
-// ended last); 8192 x 8192, r 128 55 -> 53 (no slot left for the Gram tiles).
+// 157 for four).  Measured over weight sets of 1.2 GB in turn, us of a norm, one round -> this: 27648 x 5120, r 384 224 -> 191
+// (648 tiles: two rounds, the second a quarter full); 14336 x 4096, r 768 203 -> 185; 4096 x 14336, r 384 92 -> 82 and
+// 3072 x 6000, r 512 72 -> 59 (long Gram slices ended last); 8192 x 8192, r 128 55.6 -> 53.8 (no slot left for the Gram tiles).
 // The Gram partials stay within 8 MiB where the split of the cross term alone asks for more of them.  Whether a shape's
 // scratch fits the static array does not depend on the choice: (fit, room) decides, the others must agree.
 size_t norm_split_bytes(int64_t d_out, int64_t r, int tiles_n, int ks_u, int ks_g)

@@ -6,7 +6,7 @@
 //                                           from its slices; optionally inner and the saved h
 //
 // The 128 x 128 tiles of the other products would give such a call d_out / 128 workgroups (32 for 256 CUs at
-// d_out = 4096).  Here a workgroup owns 16 or 32 weight rows and its four waves split K, each streaming its own
+// d_out = 4096).  Here a workgroup owns 16, 32 or 64 weight rows and its four waves split K, each streaming its own
 // share through a private LDS ring (buffer_load ... lds, 128-byte row segments, no barrier: only its own vmcnt), the
 // token rows beside them in the same ring; the four partial tiles meet in LDS at the end.
 #include "few_tokens_loads.hpp"
@@ -205,13 +205,16 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     }
 }
 
-// Ring depth and rows per workgroup, all measured with weights that lie in memory (bf16, us of the whole forward at
-// 4096 x 4096 r 384 / 14336 x 4096 r 64 / 8192 x 8192 r 768): up to 8192 weight rows 16 of them make 512 workgroups, two
-// per CU in one go, and a shallow ring that lets two share a CU beats a deep one (1 token 18.3 / 29.7 / 44.1 against
-// 19.1 / 39.1 / 57.5 for eight slots and one workgroup per CU).  Beyond, workgroups of 64 rows: 1.75 rounds of small ones
-// lose to one round of large ones (16 tokens 34.9 -> 27.4 at 14336 rows, but 51.6 -> 59.9 at 8192), and the token rows are
-// re-read for a quarter as many workgroups (32 tokens 41.2 -> 31.4).  With four token blocks that re-reading already
-// asks for 32 rows at 8192 (64 tokens 85.7 -> 75.0), not at 4096 (27.0 against 29.9).
+// Ring depth and rows per workgroup: us of a forward in bf16, one after the other over as many sets of weights and inputs as
+// make 600 MB, so that no set is left in a cache from its last turn.
+//  - Up to 8192 weight rows 16 of them make at most 512 workgroups, two per CU in one go, and a shallow ring that lets two
+//    share a CU beats a deep one (1 token at 8192 x 8192, r 768 47.7 against 59.9 for eight slots, at 4104 x 4096, r 64
+//    15.4 / 20.5) and workgroups of 64 rows (8192 x 4096, r 64, 1 and 32 tokens 20.0 and 27.7 / 23.8 and 29.4).
+//  - Beyond, 16 rows would need a second round, and 64 rows win from the first row on (8200 x 4096, r 64 24.0 and 29.1 / 25.5
+//    and 32.4, 10240 24.8 and 31.1 / 29.7 and 36.9, 14336 28.7 and 32.7 / 32.5 and 44.9); the token rows are then re-read for
+//    a quarter as many workgroups.
+//  - With four token blocks that re-reading asks for 32 rows above 4096 of them (64 tokens at 4104 x 4096, r 64 27.9 / 32.8
+//    for 16 rows, 8192 x 4096 32.3 / 37.2), not at 4096 (r 384 34.4 / 37.1 the other way round).
 template <int DT>
 hipError_t launch_y(const FewTokensArgs& a, hipStream_t st)
 {
