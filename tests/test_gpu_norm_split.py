@@ -20,3 +20,16 @@ def test_norm_over_its_splits(dtype, d_out, d_in, r):
     mod = G.Module(cfg)
     ref = O.dense_row_norm(mod.f64("W"), mod.f64("A"), mod.f64("B"), float(mod.inp["s"]))
     G.assert_norm_close(G.to_f64(mod.norm()), ref, 1e-5)   # fp32 sums of exact products, Gram to 16 bits or better: no storage rounding
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_norm_error_does_not_grow_with_the_slices(dtype):
+    # Two slices of K = 4096: a lane sums 4096 / 4 squares, the eight of a fragment first, so 128 sums in a row.  Rounded to
+    # nearest at random they are off by sqrt(128 / 3) 2^-25 of the lane's sum (2e-7), four lanes and two slices by 7e-8 of
+    # the row's, its root by half of that, itself rounded to 3e-8 (rms): 5e-8, and twice that for the low-rank terms and
+    # the spread.  One running sum over the slice: 5.7e-7 in bf16, 1.2e-7 in fp16.
+    cfg = I.stress(I.DoraConfig("norm_error", 4096, 8192, 768, 1, dtype, 32.0, 1e-3, seed_offset=9501))
+    mod = G.Module(cfg)
+    ref = O.dense_row_norm(mod.f64("W"), mod.f64("A"), mod.f64("B"), float(mod.inp["s"]))
+    c = G.to_f64(mod.norm())
+    assert np.sqrt(np.sum((c - ref) ** 2) / np.sum(ref ** 2)) <= 1e-7
