@@ -652,7 +652,7 @@ def main():
                     help="instead of the step benchmark: time dora_norm alone over ranks and the weight shapes of Table 5")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs the DoRA module on ONE GPU; --gpus N with N > 1 is not supported "
+        print("bench.py: the DoRA module runs on ONE GPU; --gpus N with N > 1 is not supported "
               "(no collectives are part of the path).", file=sys.stderr)
         sys.exit(2)
     if args.norm_sweep:

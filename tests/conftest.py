@@ -14,7 +14,7 @@ def pytest_configure(config):
 
 def pytest_collection_modifyitems(config, items):
     # GPU tests are skipped (not failed) when no device is visible, so that a plain
-    # `pytest tests` works on the CPU container; `-m gpu` on the GPU machine runs them.
+    # `pytest tests` works on the CPU container; `-m gpu` where there is one runs them.
     try:
         import torch
 
