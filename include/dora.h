@@ -73,9 +73,9 @@ size_t dora_workspace_bytes(const dora_desc* desc, int phase);
 
 /*
  * Row-wise norm of the composed weight, w_norm[j] = || W[j,:] + s (B A)[j,:] ||_2, by the
- * factored form of Sec. 2 (Eq. 2-5, Algorithm 1): base_sq + 2s*cross + s^2*ba_sq, with
- * U = W A^T and G = A A^T accumulated in fp32 and never written as dense [d_out, d_in]
- * data.  s == 0 skips the cross and Gram terms (Algorithm 1, notes).  Negative radicands
+ * factored form of Sec. 2 (Eq. 2-5, Algorithm 1): base_sq + 2s*cross + s^2*ba_sq, accumulated in
+ * fp32, nothing of size [d_out, d_in] written: from U = W A^T and G = A A^T, or (16-bit storage,
+ * r up to 384) with the cross and BA-norm terms summed over tiles of B A that stay in registers.  s == 0 skips the cross and Gram terms (Algorithm 1, notes).  Negative radicands
  * clamp to 0, NaN propagates (App. C item 3).
  *   W, A, B : device, const, `dtype`.   w_norm : device, out, fp32 [d_out].
  */
@@ -106,8 +106,8 @@ dora_status dora_norm_static(const dora_desc* desc, const void* W, const void* A
  *   dora_base_sq     : base_sq[j] = sum_k W[j,k]^2, fp32 accumulation of the exact products.
  *                      W : device, const, `dtype` [d_out, d_in].  base_sq : device, out, fp32 [d_out].
  *                      Needs no workspace; desc->r and desc->tokens are not read.
- *   dora_norm_cached : dora_norm with that buffer as the base term: W is read once (for the cross
- *                      term) and never squared.  Same workspace, outputs and error behaviour as
+ *   dora_norm_cached : dora_norm with that buffer as the base term: W is read once, for the cross
+ *                      term.  Same workspace, outputs and error behaviour as
  *                      dora_norm; the caller owns base_sq and must recompute it if W changes.
  */
 dora_status dora_base_sq(const dora_desc* desc, const void* W, float* base_sq, void* stream);

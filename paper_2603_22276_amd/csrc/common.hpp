@@ -169,6 +169,18 @@ int few_tokens_h_slices(int64_t tokens, int64_t r, int64_t d_in);
 hipError_t launch_few_tokens_h(const FewTokensArgs& a, int dt, hipStream_t st);
 hipError_t launch_few_tokens_y(const FewTokensArgs& a, int dt, hipStream_t st);
 
+// ---- the three sums of the row norm (16-bit storage, norm_rows.hip) ------------------------------
+constexpr int64_t NORM_ROWS_MAX_RANK = 384;
+struct NormRowsArgs {
+    const bf16_t* w;        // [d_out, d_in]
+    const bf16_t* a;        // [r, d_in]
+    const bf16_t* b;        // [d_out, r]
+    int d_out, d_in, r;
+    int slices, tiles_per_slice;   // slices of tiles_per_slice column tiles of 128 each; none of them empty
+    float* part;            // [3][slices][d_out]: base_sq, cross, ba_sq
+};
+hipError_t launch_norm_rows(const NormRowsArgs& a, int dt, hipStream_t st);
+
 // ---- fp32 GEMM (sgemm_f32.hip) --------------------------------------------------------------------
 // C[M,N] = alpha * sum over segments of  Aop[m,k] * Bop[n,k], operands K-contiguous or K-strided as in GemmArgs
 struct SgemmSeg {

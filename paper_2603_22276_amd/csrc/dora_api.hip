@@ -149,9 +149,11 @@ struct NormPlan {
     int tiles_n;   // N tiles of the [d_out, r] row-dot contractions
     int ks_u;      // split of d_in for U = W A^T
     int ks_g;      // split of d_in for G = A A^T
-    // bf16 path
+    // 16-bit path
     float *base_p, *cross_p, *ba_p, *gram_p, *G;
     bf16_t *Ghi, *Glo;
+    int slices, tiles_per_slice;   // of the columns, where the three sums come from one launch (r <= NORM_ROWS_MAX_RANK)
+    float* part;                   // [3][slices][d_out]
     // fp32 path
     float *U, *BG;
 };
@@ -199,11 +201,28 @@ void norm_split(int64_t d_out, int64_t d_in, int64_t r, int& ks_u, int& ks_g)
     ks_g = (int)best_g;
 }
 
+// Slices of the columns for the launch that forms the three sums (norm_rows.hip): the cheapest in rounds of workgroups, two
+// to a CU up to r 128, one beyond, counted in cycles of a tile (its share of reading W, or its MFMAs) and of what comes before
+// the first.
+void norm_slices(int64_t d_out, int64_t d_in, int64_t r, size_t fixed_bytes, size_t most_bytes, int& slices, int& tiles_per_slice)
+{
+    const int64_t blocks = (d_out + TILE - 1) / TILE, tiles = (d_in + TILE - 1) / TILE;
+    const int64_t at_once = r <= 128 ? 512 : 256, tile = r <= 128 ? 6600 : std::max<int64_t>((r + 63) / 64 * 850 + 600, 3300), first = 8000;
+    int64_t best = -1;
+    for (int64_t n = 1; n <= std::min<int64_t>(64, tiles) && (n == 1 || blocks * n <= 4096); ++n) {
+        const int64_t per = (tiles + n - 1) / n, used = (tiles + per - 1) / per;
+        const int64_t cost = (blocks * used + at_once - 1) / at_once * (per * tile + first);
+        if (n > 1 && fixed_bytes + up256((size_t)3 * used * d_out * 4) > most_bytes) break;
+        if (best < 0 || cost < best) { best = cost; slices = (int)used; tiles_per_slice = (int)per; }
+    }
+}
+
 void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 {
     memset(&n, 0, sizeof(n));
     n.tiles_n = cdiv(d->r, TILE);
     if (is16(d->dtype)) {
+        const Bump start = b;
         norm_split(d->d_out, d->d_in, d->r, n.ks_u, n.ks_g);
         n.base_p = b.take<float>((size_t)n.ks_u * d->d_out);
         n.cross_p = b.take<float>((size_t)n.ks_u * n.tiles_n * d->d_out);
@@ -211,6 +230,15 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
         n.gram_p = b.take<float>((size_t)n.ks_g * d->r * d->r);
         n.Ghi = b.take<bf16_t>((size_t)d->r * d->r);
         n.Glo = b.take<bf16_t>((size_t)d->r * d->r);
+        if (d->r > NORM_ROWS_MAX_RANK) return;
+        // One launch: its partial sums and, where the caller asks for G, the slices of the Gram matrix take the place of all
+        // of these.  Which shapes fit the static array stays as the split above has it.
+        const size_t gram = up256((size_t)n.ks_g * d->r * d->r * 4);
+        norm_slices(d->d_out, d->d_in, d->r, gram, std::max<size_t>(b.off - start.off, DORA_STATIC_SCRATCH_BYTES), n.slices, n.tiles_per_slice);
+        Bump o = start;
+        n.part = o.take<float>((size_t)3 * n.slices * d->d_out);
+        n.gram_p = o.take<float>((size_t)n.ks_g * d->r * d->r);
+        b.off = std::max(b.off, o.off);
     } else {
         n.U = b.take<float>((size_t)d->d_out * d->r);
         n.G = b.take<float>((size_t)d->r * d->r);
@@ -334,6 +362,24 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
     if (is16(d->dtype)) {
         if ((int64_t)r * r >= MAX_ELEMS) return DORA_ERR_SHAPE;   // G is an operand of the B G product
         const int dt = dt_of(d->dtype);
+        // past that rank B no longer fits the registers of a workgroup
+        if (r <= NORM_ROWS_MAX_RANK) {
+            const NormRowsArgs a{(const bf16_t*)W, (const bf16_t*)A, (const bf16_t*)B, d_out, d_in, r, n.slices, n.tiles_per_slice, n.part};
+            DORA_HIP(launch_norm_rows(a, dt, st));
+            if (G_out) {
+                Seg sg{A, d_in, A, d_in, d_in};
+                GemmArgs g = bf16_args(dt, true, true, r, r, &sg, 1, 1.f, n.gram_p, r, true, 0);
+                g.ksplit = n.ks_g;
+                DORA_HIP(launch_gemm_bf16(g, DORA_K_GRAM, st));
+                DORA_HIP(launch_gram_reduce(n.gram_p, n.ks_g, r, G_out, nullptr, nullptr, dt, st));
+            }
+            const size_t all = (size_t)n.slices * d_out;
+            DORA_HIP(launch_norm_final(base_sq ? base_sq : n.part, base_sq ? 1 : n.slices, n.part + all, n.slices, n.part + 2 * all,
+                                       n.slices, (double)d->s, c, terms, d_out, st, mag ? mag->m : nullptr, mag ? mag->eps : 0.f,
+                                       mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr));
+            if (mag) mag->done = true;
+            return DORA_OK;
+        }
         GemmArgs g;
         // cross term (Eq. 3) and base term: U = W A^T tile by tile, reduced against B in registers
         memset(&g, 0, sizeof(g));

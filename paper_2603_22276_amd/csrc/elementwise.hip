@@ -107,29 +107,52 @@ __global__ void mag_scale_kernel(const float* __restrict__ m, const float* __res
     if (gm1) gm1[j] = (mj - cc) / cc;  // the subtraction is exact when m/cc is within [1/2, 2]
 }
 
-// Eq. 5 from the partial sums the norm kernels left behind; partials are added in index order.
+// Eq. 5 from its three fp32 terms: the sum in double, one rounding of the radicand and one of the root.  Clamps what is below
+// zero; NaN is not, and propagates (App. C item 3).
+__device__ __forceinline__ float radicand(float base_sq, float cross, float ba_sq, float two_s, float s2)
+{
+    const float rad = (float)((double)base_sq + (double)two_s * cross + (double)s2 * ba_sq);
+    return (rad < 0.f) ? 0.f : rad;
+}
+
+// Eq. 5 from the partial sums the norm kernels left behind, in a fixed order: NF_H threads per row take every NF_H-th each.
 // terms != nullptr: the three summed terms are also written, as rows of a [3, d_out] array (base_sq,
 // cross, ba_sq); c == nullptr: only the terms are wanted.  m != nullptr: Eq. 6 follows in the same launch
 // (g and / or gm1, exactly as mag_scale_kernel forms them).
-__global__ void norm_final_kernel(const float* __restrict__ base_p, int n_base, const float* __restrict__ cross_p,
-                                  int n_cross, const float* __restrict__ ba_p, int n_ba, float two_s, float s2,
-                                  float* __restrict__ c, float* __restrict__ terms, int d_out,
+constexpr int NF_W = 32, NF_H = 8;
+__global__ __launch_bounds__(NF_W* NF_H) void norm_final_kernel(const float* __restrict__ base_p, int n_base,
+                                  const float* __restrict__ cross_p, int n_cross, const float* __restrict__ ba_p, int n_ba,
+                                  float two_s, float s2, float* __restrict__ c, float* __restrict__ terms, int d_out,
                                   const float* __restrict__ m, float eps, float* __restrict__ g, float* __restrict__ gm1)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= d_out) return;
-    const float base_sq = sum_partials<8>(base_p + j, n_base, d_out);
-    const float cross = sum_partials<8>(cross_p + j, n_cross, d_out);
-    const float ba = sum_partials<4>(ba_p + j, n_ba, d_out);
+    __shared__ float red[3][NF_H][NF_W];
+    const int x = threadIdx.x, y = threadIdx.y, j = blockIdx.x * NF_W + x;
+    const int64_t first = (int64_t)y * d_out + j, stride = (int64_t)NF_H * d_out;
+    auto share = [&](int n) { return n > y ? (n - y + NF_H - 1) / NF_H : 0; };
+    if (j < d_out) {
+        red[0][y][x] = sum_partials<4>(base_p + first, share(n_base), stride);
+        red[1][y][x] = sum_partials<4>(cross_p + first, share(n_cross), stride);
+        red[2][y][x] = sum_partials<4>(ba_p + first, share(n_ba), stride);
+    }
+    __syncthreads();
+    if (y != 0 || j >= d_out) return;
+    // (in double: eight sums of a like size one after the other in fp32 cost the norm 1e-8 to 2e-8 of its 5e-8)
+    float sum[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        double v = red[k][0][x];
+#pragma unroll
+        for (int i = 1; i < NF_H; ++i) v += red[k][i][x];
+        sum[k] = (float)v;
+    }
+    const float base_sq = sum[0], cross = sum[1], ba = sum[2];
     if (terms) {
         terms[j] = base_sq;
         terms[(int64_t)d_out + j] = cross;
         terms[2 * (int64_t)d_out + j] = ba;
     }
     if (!c) return;
-    float rad = base_sq + two_s * cross + s2 * ba;
-    rad = (rad < 0.f) ? 0.f : rad;  // NaN is not < 0: it propagates (App. C item 3)
-    const float cj = __fsqrt_rn(rad);
+    const float cj = __fsqrt_rn(radicand(base_sq, cross, ba, two_s, s2));
     c[j] = cj;
     if (m) {
         float cc = (cj < eps) ? eps : cj;
@@ -232,8 +255,7 @@ __global__ void rownorm_f32_kernel(const float* __restrict__ W, const float* __r
             terms[2 * (int64_t)d_out + row] = ba;
         }
         if (c) {
-            float rad = base_sq + two_s * cross + s2 * ba;
-            rad = (rad < 0.f) ? 0.f : rad;
+            const float rad = radicand(base_sq, cross, ba, two_s, s2);
             const float cj = squared ? rad : __fsqrt_rn(rad);
             c[row] = cj;
             if (m) {
@@ -489,8 +511,7 @@ hipError_t launch_norm_final(const float* base_p, int n_base, const float* cross
     if (d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_NORM_FINAL, st);
     // 2s and s^2 are formed in double and rounded once (App. C item 3)
-    // blocks of one wave: a few thousand threads in all, so that every CU has some of the loads
-    norm_final_kernel<<<dim3((d_out + 63) / 64), dim3(64), 0, st>>>(base_p, n_base, cross_p, n_cross, ba_p, n_ba,
+    norm_final_kernel<<<dim3((d_out + NF_W - 1) / NF_W), dim3(NF_W, NF_H), 0, st>>>(base_p, n_base, cross_p, n_cross, ba_p, n_ba,
                                                                        (float)(2.0 * s), (float)(s * s), c, terms, d_out,
                                                                        m, eps, g, gm1);
     return hipGetLastError();
