@@ -85,6 +85,14 @@ template <> struct Elem16<DT_F16> {
     }
 };
 
+// Eq. 5 from its three fp32 terms: the sum in double, one rounding of the radicand and one of the root.  Clamps what is below
+// zero; NaN is not, and propagates (App. C item 3).
+__device__ __forceinline__ float radicand(float base_sq, float cross, float ba_sq, float two_s, float s2)
+{
+    const float rad = (float)((double)base_sq + (double)two_s * cross + (double)s2 * ba_sq);
+    return (rad < 0.f) ? 0.f : rad;
+}
+
 // ---- kernel timing hook (see dora_trace_* in dora_measure.h) ------------------------------------------
 void trace_begin(int kernel_id, hipStream_t stream);
 void trace_end(int kernel_id, hipStream_t stream);
@@ -181,13 +189,20 @@ struct NormRowsArgs {
 };
 hipError_t launch_norm_rows(const NormRowsArgs& a, int dt, hipStream_t st);
 
-// ---- fp32 GEMM (sgemm_f32.hip) --------------------------------------------------------------------
-// C[M,N] = alpha * sum over segments of  Aop[m,k] * Bop[n,k], operands K-contiguous or K-strided as in GemmArgs
+// ---- fp32 products (sgemm_f32.hip) ----------------------------------------------------------------
+// C[M,N] = alpha * rowscale[m] * sum over segments of  ascale[k] Aop[m,k] * Bop[n,k], operands K-contiguous or K-strided as in
+// GemmArgs
+struct RowScale {            // g as it is (m == nullptr), or formed from the row norm: m / max(g, eps), Eq. 6
+    const float* g;          // nullptr: no scale
+    const float* m;
+    float eps;
+};
 struct SgemmSeg {
     const float* a;
     const float* b;
     int64_t lda, ldb;
     int K;
+    bool scaled;             // ascale applies (M side K-contiguous, N side K-strided; in tiles only a scale that needs no forming)
 };
 struct SgemmArgs {
     SgemmSeg seg[2];
@@ -197,15 +212,56 @@ struct SgemmArgs {
     float alpha;
     float* c;
     int64_t ldc;
+    RowScale ascale, rowscale;
+    // composed != 0: the product is lora and c holds base; it receives y = base + (gm1 base + g (s lora)) (+ bias), inner
+    // (may be nullptr) s lora + base
+    int composed;
+    const float *g, *gm1, *bias;
+    float s;
+    float* inner;
 };
-struct SgemmPair {
-    SgemmArgs g[2];
-    int count0;  // workgroups of g[0]; the rest of the grid belongs to g[1]
+// the two stages of dm's column sum: partial[slab][j] = sum of dy[t][j] inner[t][j] over COLUMN_SUM_ROWS tokens; dm[j] = the
+// sum of those in order / max(c[j], eps)
+constexpr int COLUMN_SUM_ROWS = 64;
+struct ColumnSum {
+    const float *dy, *inner;
+    int64_t tokens;
+    int d_out;
+    float* partial;
 };
-hipError_t launch_sgemm_f32(const SgemmArgs& a, int trace_id, hipStream_t stream);
-// two independent problems of the same layouts, both too small for 64 x 64 tiles, in one launch
-bool sgemm_f32_pairs(const SgemmArgs& a, const SgemmArgs& b);
-hipError_t launch_sgemm_f32_pair(const SgemmArgs& a, const SgemmArgs& b, int trace_id, hipStream_t stream);
+struct ColumnFinal {
+    const float* partial;
+    int slabs;
+    const float* c;
+    float eps;
+    float* dm;
+    int d_out;
+};
+struct ScaleOut {            // out[j] = the scale, j < n
+    RowScale scale;
+    float* out;
+    int n;
+};
+inline int column_sum_slabs(int64_t tokens) { return (int)((tokens + COLUMN_SUM_ROWS - 1) / COLUMN_SUM_ROWS); }
+// up to three products and smaller pieces of work that do not need one another, in one launch
+hipError_t launch_f32(const SgemmArgs* g, int n, const ColumnSum* sum, const ColumnFinal* fin, const ScaleOut* scale, int trace_id,
+                      hipStream_t stream);
+// norm of W + s B A from tiles of B A that stay in registers, Eq. 5 and (m != nullptr) Eq. 6 in the one launch; base_in: the
+// base term, or nullptr; terms: [3, d_out] or nullptr; c may be nullptr where terms is not.  slices > 1: only the partial sums,
+// to part [3][slices][d_out]
+struct NormF32Args {
+    const float *w, *a, *b;
+    int d_out, d_in, r;
+    const float* base_in;
+    float two_s, s2;
+    float *c, *terms;
+    const float* m;
+    float eps;
+    float *g, *gm1;
+    int slices;
+    float* part;
+};
+hipError_t launch_norm_f32(const NormF32Args& a, hipStream_t stream);
 
 // ---- element-wise / reduction kernels -----------------------------------------------------------
 hipError_t launch_mag_scale(const float* m, const float* c, float eps, float* g, float* gm1, int d_out, hipStream_t st);
@@ -229,10 +285,8 @@ hipError_t launch_norm_final(const float* base_sq_p, int n_base, const float* cr
                              int n_ba, double s, float* c, float* terms, int d_out, hipStream_t st,
                              const float* m = nullptr, float eps = 0.f, float* g = nullptr, float* gm1 = nullptr);
 hipError_t launch_rownorm_s0_16(const bf16_t* W, int dt, float* c, int d_out, int d_in, bool squared, hipStream_t st);
-// fp32 path: base_sq, cross, ba_sq and Eq. 5 from W, B, U = W A^T, BG = B G (all fp32)
-hipError_t launch_rownorm_f32(const float* W, const float* base_in, const float* B, const float* U, const float* BG,
-                              double s, float* c, float* terms, int d_out, int d_in, int r, bool squared, hipStream_t st,
-                              const float* m = nullptr, float eps = 0.f, float* g = nullptr, float* gm1 = nullptr);
+// fp32: the row norms of W alone (or their squares); terms ([3, d_out]: base_sq, 0, 0) and c may be nullptr
+hipError_t launch_rownorm_f32(const float* W, float* c, float* terms, int d_out, int d_in, bool squared, hipStream_t st);
 
 // out[i] = sum over z (in order) of partials[z * n + i], written in the storage dtype; out2 (may be nullptr)
 // receives alpha2 times the same sum.  n a multiple of 8.  colscale != nullptr: rows of `cols` elements, out is

@@ -149,13 +149,12 @@ struct NormPlan {
     int tiles_n;   // N tiles of the [d_out, r] row-dot contractions
     int ks_u;      // split of d_in for U = W A^T
     int ks_g;      // split of d_in for G = A A^T
-    // 16-bit path
-    float *base_p, *cross_p, *ba_p, *gram_p, *G;
+    // 16-bit path of higher ranks
+    float *base_p, *cross_p, *ba_p, *gram_p;
     bf16_t *Ghi, *Glo;
-    int slices, tiles_per_slice;   // of the columns, where the three sums come from one launch (r <= NORM_ROWS_MAX_RANK)
+    // where the three sums come from one launch (16-bit up to NORM_ROWS_MAX_RANK, fp32)
+    int slices, tiles_per_slice;   // of the columns
     float* part;                   // [3][slices][d_out]
-    // fp32 path
-    float *U, *BG;
 };
 
 // Split-K factors of the two norm contractions, which share a launch: 256 CUs x two 128x128-tile workgroups hold 512 at a
@@ -240,9 +239,14 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
         n.gram_p = o.take<float>((size_t)n.ks_g * d->r * d->r);
         b.off = std::max(b.off, o.off);
     } else {
-        n.U = b.take<float>((size_t)d->d_out * d->r);
-        n.G = b.take<float>((size_t)d->r * d->r);
-        n.BG = b.take<float>((size_t)d->d_out * d->r);
+        // Slices of the columns: a workgroup takes 16 rows, and 512 columns by 64 of the rank in a step of about 3.4 us.  More
+        // than one slice costs a launch (4 us), so only for work of more than three steps that leaves CUs without any: 64 x
+        // 2048, r 128 35 us in one slice, 14 in four; 2048 x 2048, r 128 37, and 23 in two.  (The scratch is that of U, G and B G, which decides what fits the static array.)
+        const int64_t steps = (int64_t)cdiv(d->d_in, 512) * cdiv(d->r, 64), blocks = cdiv(d->d_out, 16);
+        n.slices = steps <= 3 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>({256 / blocks, cdiv(d->d_in, 512), d->r / 3, 32}));
+        n.part = b.take<float>((size_t)d->d_out * d->r);
+        b.take<float>((size_t)d->r * d->r);
+        b.take<float>((size_t)d->d_out * d->r);
     }
 }
 
@@ -284,7 +288,7 @@ SgemmArgs f32_args(bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg
     SgemmArgs g;
     memset(&g, 0, sizeof(g));
     for (int i = 0; i < nseg; ++i)
-        g.seg[i] = SgemmSeg{(const float*)segs[i].a, (const float*)segs[i].b, segs[i].lda, segs[i].ldb, segs[i].K};
+        g.seg[i] = SgemmSeg{(const float*)segs[i].a, (const float*)segs[i].b, segs[i].lda, segs[i].ldb, segs[i].K, false};
     g.nseg = nseg; g.M = M; g.N = N; g.a_kcontig = a_kc; g.b_kcontig = b_kc; g.alpha = alpha; g.c = (float*)c; g.ldc = ldc;
     return g;
 }
@@ -316,18 +320,8 @@ hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* se
         g.c2 = c2; g.alpha2 = alpha2;
         return launch_product(g, trace_id, c_f32 ? nullptr : skp, st);
     }
-    return launch_sgemm_f32(f32_args(a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc), trace_id, st);
-}
-
-// two independent fp32 contractions of one segment each and the same layouts, in one launch where neither fills the chip
-struct F32Product { int M, N; Seg seg; float alpha; void* c; };
-hipError_t contract_f32_two(bool a_kc, bool b_kc, const F32Product& p, const F32Product& q, int trace_p, int trace_q, hipStream_t st)
-{
-    const SgemmArgs a = f32_args(a_kc, b_kc, p.M, p.N, &p.seg, 1, p.alpha, p.c, p.N);
-    const SgemmArgs b = f32_args(a_kc, b_kc, q.M, q.N, &q.seg, 1, q.alpha, q.c, q.N);
-    if (sgemm_f32_pairs(a, b)) return launch_sgemm_f32_pair(a, b, trace_p, st);
-    hipError_t e = launch_sgemm_f32(a, trace_p, st);
-    return e != hipSuccess ? e : launch_sgemm_f32(b, trace_q, st);
+    const SgemmArgs g = f32_args(a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc);
+    return launch_f32(&g, 1, nullptr, nullptr, nullptr, trace_id, st);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -351,12 +345,12 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
                 base_sq = n.base_p;
             }
             if (base_sq) DORA_HIP(launch_norm_final(base_sq, 1, nullptr, 0, nullptr, 0, 0.0, c, terms, d_out, st));
-            else DORA_HIP(launch_rownorm_f32((const float*)W, nullptr, nullptr, nullptr, nullptr, 0.0, c, terms, d_out, d_in, r, false, st));
+            else DORA_HIP(launch_rownorm_f32((const float*)W, c, terms, d_out, d_in, false, st));
             return DORA_OK;
         }
         if (base_sq) DORA_HIP(launch_norm_final(base_sq, 1, nullptr, 0, nullptr, 0, 0.0, c, nullptr, d_out, st));
         else if (is16(d->dtype)) DORA_HIP(launch_rownorm_s0_16((const bf16_t*)W, dt_of(d->dtype), c, d_out, d_in, false, st));
-        else DORA_HIP(launch_rownorm_f32((const float*)W, nullptr, nullptr, nullptr, nullptr, 0.0, c, nullptr, d_out, d_in, r, false, st));
+        else DORA_HIP(launch_rownorm_f32((const float*)W, c, nullptr, d_out, d_in, false, st));
         return DORA_OK;
     }
     if (is16(d->dtype)) {
@@ -410,16 +404,19 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
         if (mag) mag->done = true;
         return DORA_OK;
     }
-    // fp32: Algorithm 1 with one chunk spanning d_in; U [d_out, r], G [r, r], BG [d_out, r] in scratch
-    DORA_HIP(contract_f32_two(true, true, F32Product{d_out, r, Seg{W, d_in, A, d_in, d_in}, 1.f, n.U},
-                              F32Product{r, r, Seg{A, d_in, A, d_in, d_in}, 1.f, n.G}, DORA_K_NORM_CROSS, DORA_K_GRAM, st));
-    Seg sb{B, r, n.G, r, r};  // (B G)[j,l] = sum_k B[j,k] G[k,l]: N-side operand K-strided
-    DORA_HIP(contract(DORA_F32, true, false, d_out, r, &sb, 1, 1.f, n.BG, r, true, DORA_K_BA_SQ, st));
-    DORA_HIP(launch_rownorm_f32((const float*)W, base_sq, (const float*)B, n.U, n.BG, (double)d->s, c, terms, d_out, d_in,
-                                r, false, st, mag ? mag->m : nullptr, mag ? mag->eps : 0.f, mag ? mag->g : nullptr,
-                                mag ? mag->gm1 : nullptr));
+    const NormF32Args a{(const float*)W, (const float*)A, (const float*)B, d_out, d_in, r, base_sq, (float)(2.0 * d->s),
+                        (float)((double)d->s * d->s), c, terms, mag ? mag->m : nullptr, mag ? mag->eps : 0.f,
+                        mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr, n.slices, n.part};
+    DORA_HIP(launch_norm_f32(a, st));
+    const size_t all = (size_t)n.slices * d_out;
+    if (n.slices > 1)
+        DORA_HIP(launch_norm_final(base_sq ? base_sq : n.part, base_sq ? 1 : n.slices, n.part + all, n.slices, n.part + 2 * all,
+                                   n.slices, (double)d->s, c, terms, d_out, st, a.m, a.eps, a.g, a.gm1));
     if (mag) mag->done = true;
-    if (G_out) DORA_HIP(hipMemcpyAsync(G_out, n.G, sizeof(float) * (size_t)r * r, hipMemcpyDeviceToDevice, st));
+    if (G_out) {
+        Seg sg{A, d_in, A, d_in, d_in};
+        DORA_HIP(contract(DORA_F32, true, true, r, r, &sg, 1, 1.f, G_out, r, true, DORA_K_GRAM, st));
+    }
     return DORA_OK;
 }
 
@@ -516,7 +513,7 @@ dora_status check_ws(void* ws, size_t ws_bytes, size_t need)
     return DORA_OK;
 }
 
-// base = x W^T, h = x A^T, lora = h B^T (App. A item 1)
+// base = x W^T, h = x A^T, lora = h B^T (App. A item 1; lora == nullptr: not that one)
 // xa: the adapter branch's input (x itself unless LoRA dropout gives that branch an input of its own)
 dora_status forward_contractions(const dora_desc* d, const void* x, const void* W, const void* A, const void* B,
                                  void* base, void* h, void* lora, hipStream_t st, const void* xa = nullptr,
@@ -529,15 +526,27 @@ dora_status forward_contractions(const dora_desc* d, const void* x, const void* 
     // round behind the four full rounds of 256 x 256 base tiles and cost more than a launch of their own)
     // (h after base, not before: it then finds part of x still in the memory-side cache; the other order costs 10 us)
     if (d->dtype == DORA_F32) {
-        DORA_HIP(contract_f32_two(true, true, F32Product{T, d_out, s0, 1.f, base}, F32Product{T, r, s1, 1.f, h}, DORA_K_GEMM_BASE,
-                                  DORA_K_GEMM_H, st));
+        const SgemmArgs g[2] = {f32_args(true, true, T, d_out, &s0, 1, 1.f, base, d_out), f32_args(true, true, T, r, &s1, 1, 1.f, h, r)};
+        DORA_HIP(launch_f32(g, 2, nullptr, nullptr, nullptr, DORA_K_GEMM_BASE, st));
     } else {
         DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st, skp));
         DORA_HIP(contract(d->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, st, skp));
     }
+    if (!lora) return DORA_OK;
     Seg s2{h, r, B, r, r};
     DORA_HIP(contract(d->dtype, true, true, T, d_out, &s2, 1, 1.f, lora, d_out, false, DORA_K_GEMM_LORA, st));
     return DORA_OK;
+}
+
+// fp32: lora = h B^T composed in its own launch; y holds base and receives y, inner (may be nullptr)
+hipError_t f32_lora_composed(const dora_desc* d, const void* h, const void* B, const float* g, const float* gm1, const void* bias,
+                             void* y, void* inner, hipStream_t st)
+{
+    const int T = (int)d->tokens, d_out = (int)d->d_out, r = (int)d->r;
+    Seg s2{h, r, B, r, r};
+    SgemmArgs a = f32_args(true, true, T, d_out, &s2, 1, 1.f, y, d_out);
+    a.composed = 1; a.g = g; a.gm1 = gm1; a.bias = (const float*)bias; a.s = d->s; a.inner = (float*)inner;
+    return launch_f32(&a, 1, nullptr, nullptr, nullptr, DORA_K_GEMM_LORA, st);
 }
 
 // y = g (.) (x W^T + s (x A^T) B^T) (+ bias) of a few tokens; c: the row norm (g is formed in the last launch)
@@ -649,7 +658,7 @@ dora_status dora_base_sq(const dora_desc* desc, const void* W, float* base_sq, v
     const int d_out = (int)desc->d_out, d_in = (int)desc->d_in;
     hipStream_t s = (hipStream_t)stream;
     if (is16(desc->dtype)) DORA_HIP(launch_rownorm_s0_16((const bf16_t*)W, dt_of(desc->dtype), base_sq, d_out, d_in, true, s));
-    else DORA_HIP(launch_rownorm_f32((const float*)W, nullptr, nullptr, nullptr, nullptr, 0.0, base_sq, nullptr, d_out, d_in, 0, true, s));
+    else DORA_HIP(launch_rownorm_f32((const float*)W, base_sq, nullptr, d_out, d_in, true, s));
     return DORA_OK;
 }
 
@@ -774,7 +783,8 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     DORA_OPT_PTR(w_norm); DORA_OPT_PTR(bias); DORA_OPT_PTR(saved_h); DORA_OPT_PTR(saved_inner); DORA_OPT_PTR(w_norm_out);
     const bool need_norm = (w_norm == nullptr);
     const bool dropout = (x_lora != nullptr);
-    const bool need_lora = !one_product && saved_inner == nullptr;
+    const bool f32_plain = desc->dtype == DORA_F32 && !dropout;
+    const bool need_lora = !one_product && !f32_plain && saved_inner == nullptr;
     Bump sizing(nullptr);
     FwdPlan p;
     plan_fwd(desc, sizing, p, need_norm, saved_h == nullptr, need_lora, one_product, dropout);
@@ -810,6 +820,11 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
         g.colbias = (const bf16_t*)bias;
         g.c2 = saved_inner;
         DORA_HIP(launch_product(g, DORA_K_GEMM_FUSED_FWD, p.skp, s));
+        return DORA_OK;
+    }
+    if (f32_plain) {
+        if ((st = forward_contractions(desc, x, W, A, B, y, h, nullptr, s)) != DORA_OK) return st;
+        DORA_HIP(f32_lora_composed(desc, h, B, p.g, p.gm1, bias, y, saved_inner, s));
         return DORA_OK;
     }
     // base lands in y and lora in the inner buffer; the compose pass then runs in place on both
@@ -860,6 +875,44 @@ dora_status dora_forward_fused(const dora_desc* desc, const void* x, const void*
     if (check_desc(desc, true) == DORA_OK && !is16(desc->dtype)) return DORA_ERR_DTYPE;
     return forward_impl(desc, x, nullptr, W, A, B, m, w_norm, bias, y, saved_h, saved_inner, w_norm_out, ws, ws_bytes, stream,
                         true);
+}
+
+// fp32, plain module, in two launches: dh and the first stage of dm's column sum, then dx, dA, dB and its second stage.  dz = g
+// (.) dy is not written: g goes into the operands as they are read (formed on the way, and for the second launch, where only
+// the norm is there), into dB as its rows are stored.  (compose backward, column
+// sum, dh, dx and dA with dB as launches of their own: a pass over [tokens, d_out] and three launches more.)
+static dora_status backward_f32(const dora_desc* d, const void* dy, const void* x, const void* W, const void* A, const void* B,
+                                RowScale g, const float* c, const void* h, const void* inner, void* dx, float* dA, float* dB,
+                                float* dm, float* dm_partial, float* g_buf, void* dh, hipStream_t s)
+{
+    const int T = (int)d->tokens, d_out = (int)d->d_out, d_in = (int)d->d_in, r = (int)d->r;
+    SgemmArgs q[3];
+    int n = 0;
+    if (dx || dA) {
+        Seg sh{dy, d_out, B, r, d_out};
+        q[n] = f32_args(true, false, T, r, &sh, 1, d->s, dh, r);
+        q[n].seg[0].scaled = true; q[n++].ascale = g;
+    }
+    const ColumnSum sum{(const float*)dy, (const float*)inner, T, d_out, dm_partial};
+    const ScaleOut form{g, g_buf, d_out};
+    DORA_HIP(launch_f32(q, n, dm && T > 0 ? &sum : nullptr, nullptr, g.m ? &form : nullptr, DORA_K_GEMM_DH, s));
+    if (g.m) g = RowScale{g_buf, nullptr, 0.f};
+    n = 0;
+    if (dx) {
+        Seg sx[2] = {{dy, d_out, W, d_in, d_out}, {dh, r, A, d_in, r}};
+        q[n] = f32_args(true, false, T, d_in, sx, 2, 1.f, dx, d_in);
+        q[n].seg[0].scaled = true; q[n++].ascale = g;
+    }
+    Seg sa{dh, r, x, d_in, T}, sb{dy, d_out, h, r, T};
+    if (dA) q[n++] = f32_args(false, false, r, d_in, &sa, 1, 1.f, dA, d_in);
+    if (dB) {
+        q[n] = f32_args(false, false, d_out, r, &sb, 1, d->s, dB, r);
+        if (T > 0) q[n].rowscale = g;
+        ++n;
+    }
+    const ColumnFinal fin{dm_partial, column_sum_slabs(T), c, eff_eps(d), dm, d_out};
+    DORA_HIP(launch_f32(q, n, nullptr, dm ? &fin : nullptr, nullptr, DORA_K_GEMM_DX, s));
+    return DORA_OK;
 }
 
 // x_lora == nullptr: the plain module (dx = dz W + dh A).  Otherwise the adapter branch has its own input:
@@ -915,23 +968,28 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
     } else if (T > 0 && need_inner) {
         // base -> dz buffer, lora -> inner buffer, then inner = s*lora + base in place; the dz buffer is overwritten
         // by dz afterwards
-        void* hbuf = saved_h ? nullptr : p.h;
+        void* const lora = dt == DORA_F32 ? nullptr : p.inner;
         if (saved_h) {
             Seg s0{xa, d_in, W, d_in, d_in};
             DORA_HIP(contract(dt, true, true, T, d_out, &s0, 1, 1.f, p.dz, d_out, false, DORA_K_GEMM_BASE, s, p.skp));
             Seg s2{saved_h, r, B, r, r};
-            DORA_HIP(contract(dt, true, true, T, d_out, &s2, 1, 1.f, p.inner, d_out, false, DORA_K_GEMM_LORA, s));
+            if (lora) DORA_HIP(contract(dt, true, true, T, d_out, &s2, 1, 1.f, lora, d_out, false, DORA_K_GEMM_LORA, s));
         } else {
-            if ((st = forward_contractions(desc, xa, W, A, B, p.dz, hbuf, p.inner, s, nullptr, p.skp)) != DORA_OK) return st;
-            h = hbuf;
+            if ((st = forward_contractions(desc, xa, W, A, B, p.dz, p.h, lora, s, nullptr, p.skp)) != DORA_OK) return st;
+            h = p.h;
         }
-        DORA_HIP(launch_compose_fwd(dt, p.dz, p.inner, p.g, p.gm1, nullptr, desc->s, nullptr, 0, p.inner, T, d_out, s));
+        if (lora) DORA_HIP(launch_compose_fwd(dt, p.dz, p.inner, p.g, p.gm1, nullptr, desc->s, nullptr, 0, p.inner, T, d_out, s));
+        else DORA_HIP(f32_lora_composed(desc, h, B, p.g, p.gm1, nullptr, p.dz, p.inner, s));
         inner = p.inner;
     } else if (T > 0 && need_h) {
         Seg s1{xa, d_in, A, d_in, d_in};
         DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp));
         h = p.h;
     }
+
+    if (dt == DORA_F32 && !dropout)
+        return backward_f32(desc, dy, xa, W, A, B, mag_in_compose ? RowScale{c, m, eff_eps(desc)} : RowScale{p.g, nullptr, 0.f}, c, h,
+                            inner, dx, dA, dB, dm, p.dm_partial, p.g, p.dh, s);
 
     // compose backward: dz = g*dy (and (g-1)*dy for a separate adapter input) and the fused two-stage column
     // reduction for dm
@@ -967,8 +1025,8 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         GemmArgs gb = bf16_args(dt_of(dt), false, false, d_out, r, &sb, 1, desc->s, dB, r, true, 0);
         DORA_HIP(launch_gemm_bf16_pair(ga, gb, DORA_K_GEMM_DA, s));
     } else if (dA && dB) {
-        DORA_HIP(contract_f32_two(false, false, F32Product{r, d_in, sa, 1.f, dA}, F32Product{d_out, r, sb, desc->s, dB},
-                                  DORA_K_GEMM_DA, DORA_K_GEMM_DB, s));
+        const SgemmArgs q[2] = {f32_args(false, false, r, d_in, &sa, 1, 1.f, dA, d_in), f32_args(false, false, d_out, r, &sb, 1, desc->s, dB, r)};
+        DORA_HIP(launch_f32(q, 2, nullptr, nullptr, nullptr, DORA_K_GEMM_DA, s));
     } else {
         if (dA) DORA_HIP(contract(dt, false, false, r, d_in, &sa, 1, 1.f, dA, d_in, true, DORA_K_GEMM_DA, s));
         if (dB) DORA_HIP(contract(dt, false, false, d_out, r, &sb, 1, desc->s, dB, r, true, DORA_K_GEMM_DB, s));

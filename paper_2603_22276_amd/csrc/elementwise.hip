@@ -107,14 +107,6 @@ __global__ void mag_scale_kernel(const float* __restrict__ m, const float* __res
     if (gm1) gm1[j] = (mj - cc) / cc;  // the subtraction is exact when m/cc is within [1/2, 2]
 }
 
-// Eq. 5 from its three fp32 terms: the sum in double, one rounding of the radicand and one of the root.  Clamps what is below
-// zero; NaN is not, and propagates (App. C item 3).
-__device__ __forceinline__ float radicand(float base_sq, float cross, float ba_sq, float two_s, float s2)
-{
-    const float rad = (float)((double)base_sq + (double)two_s * cross + (double)s2 * ba_sq);
-    return (rad < 0.f) ? 0.f : rad;
-}
-
 // Eq. 5 from the partial sums the norm kernels left behind, in a fixed order: NF_H threads per row take every NF_H-th each.
 // terms != nullptr: the three summed terms are also written, as rows of a [3, d_out] array (base_sq,
 // cross, ba_sq); c == nullptr: only the terms are wanted.  m != nullptr: Eq. 6 follows in the same launch
@@ -219,52 +211,25 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, in
     }
 }
 
-// fp32 configuration: the three terms of Eq. 2 for one row per wavefront, from U = W A^T and BG = B G.
-// base_in != nullptr: the base term is read from it instead of being summed from W (Sec. 2.3: W is frozen, so
-// its squared row norms can be computed once).  squared: write the radicand itself, not its root.  m != nullptr: Eq. 6
-// follows, as in norm_final_kernel.
-__global__ void rownorm_f32_kernel(const float* __restrict__ W, const float* __restrict__ base_in,
-                                   const float* __restrict__ B, const float* __restrict__ U,
-                                   const float* __restrict__ BG, float two_s, float s2, float* __restrict__ c,
-                                   float* __restrict__ terms, int d_out, int d_in, int r, bool squared,
-                                   const float* __restrict__ m, float eps, float* __restrict__ g, float* __restrict__ gm1)
+// fp32, W alone (s == 0, Algorithm 1, notes; the cached base term of Sec. 2.3): one row per wavefront.  squared: write the
+// sum itself, not its root.  terms != nullptr: base_sq, and zeros for cross and ba_sq.
+__global__ void rownorm_f32_kernel(const float* __restrict__ W, float* __restrict__ c, float* __restrict__ terms, int d_out, int d_in,
+                                   bool squared)
 {
     int lane = threadIdx.x & 63;
     int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (row >= d_out) return;
-    float base_sq = 0.f, cross = 0.f, ba = 0.f;
+    float base_sq = 0.f;
     const float* w = W + (int64_t)row * d_in;
-    if (!base_in)
-        for (int k = lane; k < d_in; k += 64) { float v = w[k]; base_sq = fmaf(v, v, base_sq); }
-    if (U) {
-        const float* b = B + (int64_t)row * r;
-        const float* u = U + (int64_t)row * r;
-        const float* bg = BG + (int64_t)row * r;
-        for (int l = lane; l < r; l += 64) { float bv = b[l]; cross = fmaf(bv, u[l], cross); ba = fmaf(bv, bg[l], ba); }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        base_sq += __shfl_xor(base_sq, o);
-        cross += __shfl_xor(cross, o);
-        ba += __shfl_xor(ba, o);
-    }
+    for (int k = lane; k < d_in; k += 64) { float v = w[k]; base_sq = fmaf(v, v, base_sq); }
+    for (int o = 32; o > 0; o >>= 1) base_sq += __shfl_xor(base_sq, o);
     if (lane == 0) {
-        if (base_in) base_sq = base_in[row];
         if (terms) {
             terms[row] = base_sq;
-            terms[(int64_t)d_out + row] = cross;
-            terms[2 * (int64_t)d_out + row] = ba;
+            terms[(int64_t)d_out + row] = 0.f;
+            terms[2 * (int64_t)d_out + row] = 0.f;
         }
-        if (c) {
-            const float rad = radicand(base_sq, cross, ba, two_s, s2);
-            const float cj = squared ? rad : __fsqrt_rn(rad);
-            c[row] = cj;
-            if (m) {
-                float cc = (cj < eps) ? eps : cj;
-                float mj = m[row];
-                if (g) g[row] = mj / cc;
-                if (gm1) gm1[row] = (mj - cc) / cc;
-            }
-        }
+        if (c) c[row] = squared ? base_sq : __fsqrt_rn(base_sq);
     }
 }
 
@@ -558,14 +523,11 @@ hipError_t launch_rownorm_s0_16(const bf16_t* W, int dt, float* c, int d_out, in
     return hipGetLastError();
 }
 
-hipError_t launch_rownorm_f32(const float* W, const float* base_in, const float* B, const float* U, const float* BG,
-                              double s, float* c, float* terms, int d_out, int d_in, int r, bool squared, hipStream_t st,
-                              const float* m, float eps, float* g, float* gm1)
+hipError_t launch_rownorm_f32(const float* W, float* c, float* terms, int d_out, int d_in, bool squared, hipStream_t st)
 {
     if (d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_NORM_FINAL, st);
-    rownorm_f32_kernel<<<dim3((d_out + 3) / 4), dim3(256), 0, st>>>(W, base_in, B, U, BG, (float)(2.0 * s),
-                                                                    (float)(s * s), c, terms, d_out, d_in, r, squared, m, eps, g, gm1);
+    rownorm_f32_kernel<<<dim3((d_out + 3) / 4), dim3(256), 0, st>>>(W, c, terms, d_out, d_in, squared);
     return hipGetLastError();
 }
 

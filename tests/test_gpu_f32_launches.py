@@ -1,0 +1,43 @@
+"""fp32 work that shares launches: 32-row and 64-row tiles in each layout, the norm in slices of its columns, and a backward
+that leaves pieces out (each gradient alone, the magnitude frozen, the norm given or formed)."""
+import numpy as np
+import pytest
+
+from oracle import dora_oracle as O
+from paper_2603_22276_amd import binding as D
+from paper_2603_22276_amd import inputs as I
+
+import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # d_out, d_in, r, tokens
+    (1000, 772, 36, 1500),      # 384 and 312 tiles of 64 x 64 become 752 and 611 of 32 x 64
+    (68, 4100, 300, 37),        # the same for dA, both operands K-strided; norm of 45 steps in slices
+    (4100, 68, 300, 101),       # and for dB, whose rows are scaled
+    (2052, 1028, 20, 1030),     # 64 x 64
+    (20, 2052, 132, 3),         # two row blocks, norm in five slices
+]
+
+
+@pytest.mark.parametrize("d_out,d_in,r,tokens", SHAPES)
+def test_pieces_of_the_backward(d_out, d_in, r, tokens):
+    cfg = I.stress(I.DoraConfig(f"f32_launch_{d_out}_{d_in}_{r}_{tokens}", d_out, d_in, r, tokens, "f32", 16.0, 1e-3, seed_offset=9300))
+    mod = G.Module(cfg)
+    tol = G.TOL["f32"]["tensor"]
+    oi = dict(x=mod.f64("x"), W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=mod.inp["m"].astype(np.float64),
+              s=float(mod.inp["s"]), eps=cfg.eps)
+    f, b = O.forward(**oi), O.backward(mod.f64("dy"), **oi)
+    out = mod.forward()
+    G.assert_norm_close(G.to_f64(out["c"]), f["c"], 3e-6)
+    for k in ("y", "h", "inner"):
+        G.assert_close(k, G.to_f64(out[k]), f[k], tol)
+    ws = G.workspace(mod.desc, D.PHASE_BACKWARD_RECOMPUTE)
+    for want in (("dx", "dA", "dB", "dm"), ("dx", "dA", "dB"), ("dx",), ("dA",), ("dB",), ("dm",), ("dB", "dm")):
+        for c in (out["c"], None):
+            got = {"dx": G.empty((tokens, d_in), "f32"), "dA": G.empty_f32(r, d_in), "dB": G.empty_f32(d_out, r), "dm": G.empty_f32(d_out)}
+            got = {k: v if k in want else None for k, v in got.items()}
+            D.dora_backward(mod.desc, mod.dy, mod.x, mod.W, mod.A, mod.B, mod.m, c, out["h"], out["inner"], got["dx"], got["dA"],
+                            got["dB"], got["dm"], ws)
+            for k in want:
+                G.assert_close(k, G.to_f64(got[k]), b[k], tol)
