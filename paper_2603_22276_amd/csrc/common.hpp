@@ -154,7 +154,9 @@ struct GemmPair {
 // number of N tiles the ROWDOT epilogue will produce partials for (depends on the tile chosen)
 int gemm_bf16_tiles_n(const GemmArgs& a);
 hipError_t launch_gemm_bf16(const GemmArgs& a, int trace_id, hipStream_t stream);
-// two independent problems of the same kind (layouts, epilogue) in one launch
+// two independent problems of the same kind (layouts, epilogue) in one launch; gemm_bf16_pairs: whether that is the cheaper way
+// (their tiles share rounds of workgroups, and a launch is saved)
+bool gemm_bf16_pairs(const GemmArgs& a, const GemmArgs& b);
 hipError_t launch_gemm_bf16_pair(const GemmArgs& a, const GemmArgs& b, int trace_id, hipStream_t stream);
 
 // ---- forward of a few tokens (16-bit storage) ----------------------------------------------------

@@ -251,19 +251,23 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 }
 
 // Split of K for the products with a 16-bit output whose 128 x 128 tiles leave at least half the CUs without work: h = x A^T
-// and dh = s dz B over [tokens, r] (96 workgroups at 4096 tokens, r 384), x W^T and dz W of short batches (32 at 512 tokens,
-// 1024 x 4096).  K is cut into slices (fp32 partials in the workspace, summed in slice order by a small reduce launch) so
-// that the launch approaches one workgroup per CU, each slice keeping at least 16 K steps.  (x W^T + s h B^T of 512 tokens,
-// 1024 x 4096: 29 us in one piece, 13.6 + 4 in four slices; the step of that module 107 -> 93 us.)
+// and dh = s dz B over [tokens, r], x W^T and dz W of short batches.  K is cut into slices (fp32 partials in the workspace,
+// summed in slice order by a small reduce launch), as many as are cheapest in tenths of a microsecond: 4 for each K step of 64
+// of a slice, 50 for the reduce launch, and the partials written and read at 4 TB/s.  At most one workgroup per CU, 16 slices,
+// and two K steps to a slice at least.  (Against at most four slices of 16 K steps: x A^T of 512 tokens, K 4096, r 64 11.9 ->
+// 7.2 us in 16 slices; of 1501 tokens, K 3000, r 72 16.3 -> 8.7 in eight; steps of 128 tokens through 4096 x 14336 206 -> 173,
+// through 14336 x 4096 165 -> 145.)
 inline int product_ksplit(int dtype, int64_t M, int64_t N, int64_t K)
 {
     if (!is16(dtype) || M <= 0) return 1;
-    const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE);
+    const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), steps = (K + 63) / 64;
     if (tiles * 2 > 256) return 1;
-    int64_t ks = 256 / tiles;
-    if (ks > 4) ks = 4;
-    if (ks > K / 1024) ks = K / 1024;
-    return ks < 1 ? 1 : (int)ks;
+    int64_t best = 1, least = 4 * steps;
+    for (int64_t ks = 2; ks <= std::min<int64_t>({256 / tiles, 16, steps / 2}); ++ks) {
+        const int64_t cost = 4 * ((steps + ks - 1) / ks) + 50 + ks * M * N * 8 / 400000;
+        if (cost < least) { least = cost; best = ks; }
+    }
+    return (int)best;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -829,6 +833,22 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     }
     // base lands in y and lora in the inner buffer; the compose pass then runs in place on both
     void* lora = saved_inner ? saved_inner : p.lora;
+    Seg sx{x, d_in, W, d_in, d_in}, sa{x_lora, d_in, W, d_in, d_in};
+    if (dropout && is16(desc->dtype) && product_ksplit(desc->dtype, T, d_out, d_in) == 1) {
+        // x W^T and x_lora W^T in one launch where their tiles fill rounds better together (2056 x 3000, 1501 tokens: 204 of 128 x
+        // 128 each, one to a CU: 69 us in two launches, 56 in one)
+        const int dt = dt_of(desc->dtype);
+        const GemmArgs g0 = bf16_args(dt, true, true, T, d_out, &sx, 1, 1.f, y, d_out, false, 0);
+        const GemmArgs g1 = bf16_args(dt, true, true, T, d_out, &sa, 1, 1.f, p.base_a, d_out, false, 0);
+        if (gemm_bf16_pairs(g0, g1)) {
+            DORA_HIP(launch_gemm_bf16_pair(g0, g1, DORA_K_GEMM_BASE, s));
+            Seg s1{x_lora, d_in, A, d_in, d_in}, s2{h, r, B, r, r};
+            DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp));
+            DORA_HIP(contract(desc->dtype, true, true, T, d_out, &s2, 1, 1.f, lora, d_out, false, DORA_K_GEMM_LORA, s));
+            DORA_HIP(launch_compose_fwd(desc->dtype, p.base_a, lora, p.g, p.gm1, bias, desc->s, y, 2, saved_inner, T, d_out, s));
+            return DORA_OK;
+        }
+    }
     if ((st = forward_contractions(desc, x, W, A, B, y, h, lora, s, x_lora, p.skp)) != DORA_OK) return st;
     if (!dropout) {
         DORA_HIP(launch_compose_fwd(desc->dtype, y, lora, p.g, p.gm1, bias, desc->s, y, 0, saved_inner, T, d_out, s));
@@ -836,7 +856,6 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     }
     // LoRA dropout: the compose runs on the adapter branch's own base x_lora W^T and its delta is added to
     // the frozen layer's output already in y
-    Seg sa{x_lora, d_in, W, d_in, d_in};
     DORA_HIP(contract(desc->dtype, true, true, T, d_out, &sa, 1, 1.f, p.base_a, d_out, false, DORA_K_GEMM_BASE, s, p.skp));
     DORA_HIP(launch_compose_fwd(desc->dtype, p.base_a, lora, p.g, p.gm1, bias, desc->s, y, 2, saved_inner, T, d_out, s));
     return DORA_OK;
@@ -1008,13 +1027,21 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
             DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
         }
     } else {
-        if (dx) {  // frozen path: dx = dy W
-            Seg sx{dy, d_out, W, d_in, d_out};
+        Seg sx{dy, d_out, W, d_in, d_out};                                       // frozen path: dx = dy W
+        Seg sl[2] = {{p.dzb, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};     // adapter path: dx_lora = ((g-1) dy) W + dh A
+        bool paired = false;
+        if (dx && dx_lora && T > 0 && is16(dt) && product_ksplit(dt, T, d_in, d_out) == 1) {
+            // in one launch where their tiles fill rounds better together (2056 x 3000, 1501 tokens: 288 of 128 x 128 each, one
+            // and an eighth to a CU; together 144 of 256 x 256: 77 us in two launches, 59 in one)
+            const GemmArgs g0 = bf16_args(dt_of(dt), true, false, T, d_in, &sx, 1, 1.f, dx, d_in, false, 0);
+            const GemmArgs g1 = bf16_args(dt_of(dt), true, false, T, d_in, sl, 2, 1.f, dx_lora, d_in, false, 0);
+            if ((paired = gemm_bf16_pairs(g0, g1))) DORA_HIP(launch_gemm_bf16_pair(g0, g1, DORA_K_GEMM_DX, s));
+        }
+        if (dx && !paired) {
             DORA_HIP(contract(dt, true, false, T, d_in, &sx, 1, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
         }
-        if (dx_lora) {  // adapter path: dx_lora = ((g-1) dy) W + dh A
-            Seg sx[2] = {{p.dzb, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};
-            DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx_lora, d_in, false, DORA_K_GEMM_DX, s, p.skp));
+        if (dx_lora && !paired) {
+            DORA_HIP(contract(dt, true, false, T, d_in, sl, 2, 1.f, dx_lora, d_in, false, DORA_K_GEMM_DX, s, p.skp));
         }
     }
     Seg sa{p.dh, r, xa, d_in, T};  // dA = dh^T xa

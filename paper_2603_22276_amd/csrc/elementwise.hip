@@ -185,12 +185,21 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, in
     float acc[N];
 #pragma unroll
     for (int e = 0; e < N; ++e) acc[e] = 0.f;
-    for (int z = 0; z < ksplit; ++z) {
+    constexpr int U = 4;                               // slices in flight
+    for (int z = 0; z < ksplit; z += U) {
+        float4 v[U][N / 4];
 #pragma unroll
-        for (int e = 0; e < N; e += 4) {
-            const float4 v = *reinterpret_cast<const float4*>(p + (int64_t)z * n + i + e);
-            acc[e] += v.x; acc[e + 1] += v.y; acc[e + 2] += v.z; acc[e + 3] += v.w;
-        }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < N / 4; ++e)
+                v[u][e] = *reinterpret_cast<const float4*>(p + (int64_t)(z + u < ksplit ? z + u : ksplit - 1) * n + i + e * 4);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (z + u < ksplit)
+#pragma unroll
+                for (int e = 0; e < N / 4; ++e) {
+                    acc[4 * e] += v[u][e].x; acc[4 * e + 1] += v[u][e].y; acc[4 * e + 2] += v[u][e].z; acc[4 * e + 3] += v[u][e].w;
+                }
     }
     if (colscale) {
         const int col = (int)(i % cols);

@@ -881,23 +881,81 @@ hipError_t launch_one(const GemmArgs& a, const GemmArgs* b, hipStream_t stream)
     return hipGetLastError();
 }
 
-bool use_big(const GemmArgs& a)
+// What a K step costs a launch of so many tiles, in hundredths of a microsecond: 128 x 128 tiles run two to a CU (one, with
+// the deep ring, where they are at most 256), 256 x 256 ones one to a CU, in rounds.  Measured on x W^T and dz W of 512 to 8192
+// tokens at 4096 x 4096, 14336 x 4096, 4096 x 14336, 3000 x 2056 and 5120 x 27648: one round of 128 x 128 tiles 0.5 us a step up
+// to 256 tiles, 1.0 up to 512; of 256 x 256 ones 1.15 with few of them to 1.5 with 256.
+int64_t med_cost(int64_t tiles) { return tiles / 512 * 100 + (tiles % 512 == 0 ? 0 : tiles % 512 <= 256 ? 55 : 100); }
+int64_t big_cost(int64_t tiles) { return tiles / 256 * 150 + (tiles % 256 == 0 ? 0 : 115 + 35 * (tiles % 256) / 256); }
+
+int64_t tiles_of(int64_t M, int64_t N, int64_t tile) { return ((M + tile - 1) / tile) * ((N + tile - 1) / tile); }
+
+// The large tile from a full round of them on, and below where its one round is the cheaper one.  (512 tiles of 128 x 128 are
+// one round of 1.0, 576 two, and 144 of 256 x 256 one of 1.35: 4096 x 4096, 2304 tokens 120 -> 102 us, 5120 x 27648, 2048
+// tokens 819 -> 511.  From 260 large tiles on the two are within 5 % of each other at K 4096 and less, and at larger K the
+// large tile is faster by up to half.)  A short K, where the epilogue is most of a tile, keeps the line at the full round.
+bool use_big(const GemmArgs& a, const GemmArgs* b)
 {
-    // the large tile pays off once it still yields a few tiles per CU
-    int64_t big_tiles = (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256);
-    return (a.epilogue == EPI_STORE_BF16 || a.epilogue == EPI_COMPOSE) && a.ksplit == 1 && big_tiles >= 256;
+    if ((a.epilogue != EPI_STORE_BF16 && a.epilogue != EPI_COMPOSE) || a.ksplit != 1) return false;
+    const int64_t big = tiles_of(a.M, a.N, 256) + (b ? tiles_of(b->M, b->N, 256) : 0);
+    const int64_t med = tiles_of(a.M, a.N, 128) + (b ? tiles_of(b->M, b->N, 128) : 0);
+    return big >= 256 || (a.seg[0].K >= 1024 && big_cost(big) < med_cost(med));
+}
+
+// Columns (or, if `rows`, rows) that go to whole rounds of large tiles where what is left over goes to one round of 128 x 128
+// ones with a CU each, or 0: the few large tiles of a last round cost three quarters of a full one.  (272 tiles, 4096 x 4096,
+// 4352 tokens: 192 us for two rounds, 150 this way.  Half a round left over is no slower in large tiles, the power limit being what it is.)
+// The second launch costs 6 us.
+int big_part(const GemmArgs& a, bool& rows)
+{
+    const int64_t tm = (a.M + 255) / 256, tn = (a.N + 255) / 256, steps = (a.seg[0].K + 63) / 64;
+    int64_t best = big_cost(tm * tn) * steps - 600;
+    int part = 0;
+    for (int along = 0; along < 2; ++along) {
+        const int64_t n = along ? tm : tn, other = along ? tn : tm, k = tm * tn / 256 * 256 / other;
+        if (k <= 0 || k >= n) continue;
+        const int64_t rest = along ? tiles_of(a.M - k * 256, a.N, 128) : tiles_of(a.M, a.N - k * 256, 128);
+        const int64_t cost = (big_cost(k * other) + med_cost(rest)) * steps;
+        if (rest <= 256 && cost < best) { best = cost; part = (int)(k * 256); rows = along != 0; }
+    }
+    return part;
+}
+
+template <bool A_KC, bool B_KC, int EPI>
+hipError_t launch_parts(const GemmArgs& a, int part, bool rows, hipStream_t stream)
+{
+    GemmArgs first = a, second = a;
+    for (int i = 0; i < a.nseg; ++i) {
+        GemmSeg& sg = second.seg[i];
+        if (rows) sg.a += A_KC ? part * sg.lda : part;
+        else sg.b += B_KC ? part * sg.ldb : part;
+    }
+    if (rows) { first.M = part; second.M = a.M - part; }
+    else {
+        first.N = part; second.N = a.N - part;
+        if (a.colscale) second.colscale = a.colscale + part;
+        if (a.colbias) second.colbias = a.colbias + part;
+    }
+    const int64_t out = rows ? part * a.ldc : part;
+    second.c = (bf16_t*)a.c + out;
+    if (a.c2) second.c2 = (bf16_t*)a.c2 + out;
+    hipError_t e = launch_one<TileBig, A_KC, B_KC, EPI>(first, nullptr, stream);
+    return e != hipSuccess ? e : launch_one<TileMedDeep, A_KC, B_KC, EPI>(second, nullptr, stream);
 }
 
 hipError_t dispatch(const GemmArgs& a, const GemmArgs* b, hipStream_t stream)
 {
-    const bool big = use_big(a);
+    const bool big = use_big(a, b);
+    bool rows = false;
+    const int part = big && !b && a.seg[0].K >= 1024 ? big_part(a, rows) : 0;
     // at most one 128x128-tile workgroup per CU: give it the deep ring
     const bool deep = !big && (grid_of<TileMed>(a) + (b ? grid_of<TileMed>(*b) : 0)) <= 256;
 #define DORA_GEMM_MED(AKC, BKC, E) \
     (deep ? launch_one<TileMedDeep, AKC, BKC, E>(a, b, stream) : launch_one<TileMed, AKC, BKC, E>(a, b, stream))
 #define DORA_GEMM_CASE(AKC, BKC, E)                                                     \
     if (a.a_kcontig == (AKC) && a.b_kcontig == (BKC) && a.epilogue == (E))              \
-        return big ? launch_one<TileBig, AKC, BKC, E>(a, b, stream) : DORA_GEMM_MED(AKC, BKC, E);
+        return part ? launch_parts<AKC, BKC, E>(a, part, rows, stream)                  \
+             : big ? launch_one<TileBig, AKC, BKC, E>(a, b, stream) : DORA_GEMM_MED(AKC, BKC, E);
     DORA_GEMM_CASE(true, true, EPI_STORE_BF16)
     DORA_GEMM_CASE(true, false, EPI_STORE_BF16)
     DORA_GEMM_CASE(true, true, EPI_COMPOSE)
@@ -923,6 +981,17 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int trace_id, hipStream_t stream)
     if (a.M == 0 || a.N == 0) return hipSuccess;
     TraceScope ts(trace_id, stream);
     return dispatch(a, nullptr, stream);
+}
+
+bool gemm_bf16_pairs(const GemmArgs& a, const GemmArgs& b)
+{
+    auto cost = [](const GemmArgs& p, const GemmArgs* q) {
+        const int64_t big = tiles_of(p.M, p.N, 256) + (q ? tiles_of(q->M, q->N, 256) : 0);
+        const int64_t med = tiles_of(p.M, p.N, 128) + (q ? tiles_of(q->M, q->N, 128) : 0);
+        return use_big(p, q) ? big_cost(big) : med_cost(med);
+    };
+    const int64_t steps = (a.seg[0].K + 63) / 64;
+    return cost(a, &b) * steps < (cost(a, nullptr) + cost(b, nullptr)) * steps + 600;
 }
 
 hipError_t launch_gemm_bf16_pair(const GemmArgs& a, const GemmArgs& b, int trace_id, hipStream_t stream)
