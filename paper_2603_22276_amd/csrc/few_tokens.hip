@@ -38,9 +38,12 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     constexpr int RED_LD = ROWS + 4;
     constexpr int RING_BYTES = WAVES * DEPTH * SLOT_BYTES, RED_BYTES = WAVES * TOK * RED_LD * 4;
     constexpr int LDS_BYTES = RING_BYTES > RED_BYTES ? RING_BYTES : RED_BYTES;
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
+    // one block of tokens and of rows: h comes through LDS, H_RANKS of it at a time
+    constexpr bool STAGE_H = FINAL && TB == 1 && MR == 1;
+    constexpr int H_RANKS = 512, H_BYTES = STAGE_H ? 16 * H_RANKS * 2 : 0;
+    static_assert(LDS_BYTES + H_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
     static_assert((DEPTH - 1) * LPS <= 63, "vmcnt is a 6-bit counter");
-    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
+    __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES + H_BYTES];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -94,40 +97,121 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
 #pragma unroll
             for (int e = 0; e < 4; ++e) { acc[i][j][e] = 0.f; accl[i][j][e] = 0.f; }
 
+    typedef __attribute__((address_space(3))) const char* lds_cptr_t;
+    constexpr int PAIRS = ROWS / 2;
+    static_assert(64 * WAVES % PAIRS == 0, "a thread keeps its columns");
+    const int c_own = (int)threadIdx.x % PAIRS * 2, n_own = n0 + c_own;     // the two columns this thread stores in the end
+    float2 cj = make_float2(1.f, 1.f), mj = make_float2(0.f, 0.f);
+    uint32_t bias = 0u;
+    // Everything the low-rank part and the end need is asked for ahead of the first weight rows: loads complete in order, and
+    // one latency covers them all.  (Each slice of h waited for the one before, k-step after k-step, behind the first weight
+    // rows, and g's norm and magnitude for the end: 4096 x 4096, r 384, 1 token 14.7 us, 9.0 now, 3.9 TB/s; with 16 tokens the
+    // forward 22.4 -> 16.1, with 64, whose h stays out of LDS, 33.7 -> 28.3.)
+    constexpr int SLICES = 8 / TB;                     // slices of h at most (few_tokens_h_slices)
+    float4 hs[TB][SLICES][2];                          // of the k-step or item under way
+    auto load_h = [&](int t, int l, float4 (&v)[SLICES][2]) {
+#pragma unroll
+        for (int z = 0; z < SLICES; ++z) {
+            const int zz = z < p.h_slices ? z : p.h_slices - 1;
+            const float4* hp = reinterpret_cast<const float4*>(p.h_part + ((int64_t)zz * T + t) * p.r + l);
+            v[z][0] = hp[0]; v[z][1] = hp[1];
+        }
+    };
+    // summed in slice order, rounded once to the storage type, as the saved tensor is
+    auto sum_h = [&](const float4 (&v)[SLICES][2]) {
+        float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int z = 0; z < SLICES; ++z)
+            if (z < p.h_slices) {
+                a[0] += v[z][0].x; a[1] += v[z][0].y; a[2] += v[z][0].z; a[3] += v[z][0].w;
+                a[4] += v[z][1].x; a[5] += v[z][1].y; a[6] += v[z][1].z; a[7] += v[z][1].w;
+            }
+        uint4 o;
+        o.x = E::pack2(a[0], a[1]); o.y = E::pack2(a[2], a[3]); o.z = E::pack2(a[4], a[5]); o.w = E::pack2(a[6], a[7]);
+        return o;
+    };
+    auto load_b = [&](int i, int l) {
+        const int n = n0 + i * 16 + l16;
+        uint4 b = make_uint4(0u, 0u, 0u, 0u);
+        if (l < p.r && n < N) b = *reinterpret_cast<const uint4*>(p.b + (int64_t)n * p.r + l);
+        return b;
+    };
+    constexpr int PRE = H_RANKS / 32 / WAVES;          // k-steps of a wave in H_RANKS
+    uint4 bpre[STAGE_H ? PRE : 1];
+    // item of h: eight ranks of one token; `per` of them to a token, ranks past r among them as far as a k-step reaches
+    const int per0 = ((p.r < H_RANKS ? p.r : H_RANKS) + 31) / 32 * 4;
+    if constexpr (FINAL) {
+        if (n_own < N) {
+            cj = *reinterpret_cast<const float2*>(p.c + n_own);
+            mj = *reinterpret_cast<const float2*>(p.m + n_own);
+            if (p.bias) bias = *reinterpret_cast<const uint32_t*>(p.bias + n_own);
+        }
+        if constexpr (STAGE_H) {
+            const int t = (int)threadIdx.x / per0, l = (int)threadIdx.x % per0 * 8;
+            load_h(t < T ? t : T - 1, l < p.r ? l : 0, hs[0]);
+#pragma unroll
+            for (int q = 0; q < PRE; ++q) bpre[q] = load_b(0, (wave + q * WAVES) * 32 + lq * 8);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) issue(s_begin + d, d);
+    __builtin_amdgcn_sched_barrier(0);
 
-    if constexpr (FINAL) {
-        // low-rank part while the first weight rows are on their way: h from its slices (summed in order, rounded once to
-        // the storage type, as the saved tensor is), B straight from memory; the waves share the k-steps of 32
-        const int r = p.r;
-        for (int st = wave; st * 32 < r; st += WAVES) {
+    if constexpr (STAGE_H) {
+        const uint32_t hbuf = (uint32_t)(uintptr_t)(lds_cptr_t)(smem + LDS_BYTES);
+        for (int c0 = 0; c0 < p.r; c0 += H_RANKS) {
+            const int left = p.r - c0, per = ((left < H_RANKS ? left : H_RANKS) + 31) / 32 * 4;
+            if (c0 > 0) {
+#pragma unroll
+                for (int q = 0; q < PRE; ++q) bpre[q] = load_b(0, c0 + (wave + q * WAVES) * 32 + lq * 8);
+            }
+            for (int i = threadIdx.x; i < T * per; i += 64 * WAVES) {
+                const int t = i / per, k = i % per * 8, l = c0 + k;
+                if (c0 > 0 || i >= 64 * WAVES) load_h(t, l < p.r ? l : 0, hs[0]);
+                uint4 o = sum_h(hs[0]);
+                if (l >= p.r) o = make_uint4(0u, 0u, 0u, 0u);
+                if (p.h_out && blockIdx.x == 0 && l < p.r) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * p.r + l) = o;
+                const uint32_t at = hbuf + (uint32_t)(t * (H_RANKS * 2) + (((k >> 3) ^ t) << 4));
+                asm volatile("ds_write_b128 %0, %1" ::"v"(at), "v"(__builtin_bit_cast(bf16x8_t, o)) : "memory");
+            }
+            wait_lgkmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < PRE; ++q) {
+                const int st = wave + q * WAVES;
+                if (st * 32 >= left) continue;
+                // (tokens past T: whatever is there reaches only columns that are not stored)
+                bf16x8_t hf = lds_read_b128<0>(hbuf + (uint32_t)(l16 * (H_RANKS * 2) + (((st * 4 + lq) ^ l16) << 4)));
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(hf));
+                accl[0][0] = E::mfma16(__builtin_bit_cast(bf16x8_t, bpre[q]), hf, accl[0][0]);
+            }
+            __builtin_amdgcn_s_barrier();              // read by all: the next ranks, or the ring, may follow
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else if constexpr (FINAL) {
+        // low-rank part while the first weight rows are on their way: h and B straight from memory, the waves share the
+        // k-steps of 32
+        for (int st = wave; st * 32 < p.r; st += WAVES) {
             const int l = st * 32 + lq * 8;
-            const bool ok = l < r;
+            const bool ok = l < p.r;
             bf16x8_t hf[TB], bfr[MR];
 #pragma unroll
             for (int j = 0; j < TB; ++j) {
                 const int t = j * 16 + l16;
-                const int tc = t < T ? t : T - 1;
-                float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                if (ok)
-                    for (int zz = 0; zz < p.h_slices; ++zz) {
-                        const float4* hp = reinterpret_cast<const float4*>(p.h_part + ((int64_t)zz * T + tc) * r + l);
-                        const float4 u = hp[0], v = hp[1];
-                        a[0] += u.x; a[1] += u.y; a[2] += u.z; a[3] += u.w;
-                        a[4] += v.x; a[5] += v.y; a[6] += v.z; a[7] += v.w;
-                    }
-                uint4 o;
-                o.x = E::pack2(a[0], a[1]); o.y = E::pack2(a[2], a[3]); o.z = E::pack2(a[4], a[5]); o.w = E::pack2(a[6], a[7]);
-                hf[j] = __builtin_bit_cast(bf16x8_t, o);
-                if (p.h_out && blockIdx.x == 0 && ok && t < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * r + l) = o;
+                load_h(t < T ? t : T - 1, ok ? l : 0, hs[j]);
             }
 #pragma unroll
-            for (int i = 0; i < MR; ++i) {
-                const int n = n0 + i * 16 + l16;
-                uint4 b = make_uint4(0u, 0u, 0u, 0u);
-                if (ok && n < N) b = *reinterpret_cast<const uint4*>(p.b + (int64_t)n * r + l);
-                bfr[i] = __builtin_bit_cast(bf16x8_t, b);
+            for (int i = 0; i < MR; ++i) bfr[i] = __builtin_bit_cast(bf16x8_t, load_b(i, l));
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                const int t = j * 16 + l16;
+                uint4 o = sum_h(hs[j]);
+                if (!ok) o = make_uint4(0u, 0u, 0u, 0u);
+                hf[j] = __builtin_bit_cast(bf16x8_t, o);
+                if (p.h_out && blockIdx.x == 0 && ok && t < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * p.r + l) = o;
             }
 #pragma unroll
             for (int i = 0; i < MR; ++i)
@@ -136,7 +220,6 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
         }
     }
 
-    typedef __attribute__((address_space(3))) const char* lds_cptr_t;
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_cptr_t)ring;
     uint32_t rd[KSTEPS];
 #pragma unroll
@@ -181,26 +264,22 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
             *reinterpret_cast<float4*>(red + (wave * TOK + j * 16 + l16) * RED_LD + i * 16 + lq * 4) = v;
         }
     __syncthreads();
-    constexpr int PAIRS = ROWS / 2;
     for (int e = threadIdx.x; e < TOK * PAIRS; e += 64 * WAVES) {
-        const int t = e / PAIRS, c = (e % PAIRS) * 2, n = n0 + c;
-        if (t >= T || n >= N) continue;                // N is a multiple of 8
+        const int t = e / PAIRS;
+        if (t >= T || n_own >= N) continue;            // N is a multiple of 8
         float v0 = 0.f, v1 = 0.f;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
-            const float2 u = *reinterpret_cast<const float2*>(red + (w * TOK + t) * RED_LD + c);
+            const float2 u = *reinterpret_cast<const float2*>(red + (w * TOK + t) * RED_LD + c_own);
             v0 += u.x; v1 += u.y;
         }
         if constexpr (FINAL) {
-            const float2 cj = *reinterpret_cast<const float2*>(p.c + n), mj = *reinterpret_cast<const float2*>(p.m + n);
             const float g0 = mj.x / ((cj.x < p.eps) ? p.eps : cj.x), g1 = mj.y / ((cj.y < p.eps) ? p.eps : cj.y);
-            uint32_t bias = 0u;
-            if (p.bias) bias = *reinterpret_cast<const uint32_t*>(p.bias + n);
-            const int64_t at = (int64_t)t * N + n;
+            const int64_t at = (int64_t)t * N + n_own;
             *reinterpret_cast<uint32_t*>(p.y + at) = E::pack2(fmaf(g0, v0, E::lo(bias)), fmaf(g1, v1, E::hi(bias)));
             if (p.inner) *reinterpret_cast<uint32_t*>(p.inner + at) = E::pack2(v0, v1);
         } else {
-            *reinterpret_cast<float2*>(p.part + ((int64_t)z * T + t) * N + n) = make_float2(v0, v1);
+            *reinterpret_cast<float2*>(p.part + ((int64_t)z * T + t) * N + n_own) = make_float2(v0, v1);
         }
     }
 }
