@@ -277,15 +277,46 @@ int compose_bwd_slabs(int64_t tokens, int d_out, int dtype);
 hipError_t launch_compose_bwd(int dtype, const void* dy, const void* inner, const float* g, const float* gm1, void* dz,
                               void* dzb, float* partial /* [slabs][d_out] or nullptr */, int64_t tokens, int d_out,
                               hipStream_t st, const float* m = nullptr, float eps = 0.f);
-hipError_t launch_dm_final(const float* partial, int slabs, const float* c, float eps, float* dm, int d_out, hipStream_t st);
+struct DmFinalArgs {          // dm[j] = sum of the slabs' partials / max(c[j], eps)
+    const float* partial;
+    int slabs;
+    const float* c;
+    float eps;
+    float* dm;
+    int d_out;
+};
+hipError_t launch_dm_final(const DmFinalArgs& a, hipStream_t st);
 // G = sum of partials; Ghi + Glo ~ G as two 16-bit terms of element type dt (both may be nullptr)
 hipError_t launch_gram_reduce(const float* partials, int ksplit, int r, float* G, bf16_t* Ghi, bf16_t* Glo, int dt,
                               hipStream_t st);
-// c and / or terms ([3, d_out]: the summed base_sq, cross, ba_sq) may be nullptr
+// Eq. 5 from partial sums.  c and / or terms ([3, d_out]: the summed base_sq, cross, ba_sq) may be nullptr
 // m != nullptr: Eq. 6 in the same launch (g and / or gm1 from m, the norm just formed and eps)
-hipError_t launch_norm_final(const float* base_sq_p, int n_base, const float* cross_p, int n_cross, const float* ba_p,
-                             int n_ba, double s, float* c, float* terms, int d_out, hipStream_t st,
-                             const float* m = nullptr, float eps = 0.f, float* g = nullptr, float* gm1 = nullptr);
+struct NormFinalArgs {
+    const float* base_p; int n_base;
+    const float* cross_p; int n_cross;
+    const float* ba_p; int n_ba;
+    float two_s, s2;          // formed in double and rounded once (App. C item 3)
+    float *c, *terms;
+    int d_out;
+    const float* m;
+    float eps;
+    float *g, *gm1;
+};
+inline NormFinalArgs norm_final_args(const float* base_p, int n_base, const float* cross_p, int n_cross, const float* ba_p, int n_ba,
+                                     double s, float* c, float* terms, int d_out, const float* m = nullptr, float eps = 0.f,
+                                     float* g = nullptr, float* gm1 = nullptr)
+{
+    return NormFinalArgs{base_p, n_base, cross_p, n_cross, ba_p, n_ba, (float)(2.0 * s), (float)(s * s), c, terms, d_out, m, eps, g, gm1};
+}
+hipError_t launch_norm_final(const NormFinalArgs& a, hipStream_t st);
+// Small launches that nothing waits for yet: they ride in the next reduce launch of a split product, or are launched by
+// launch_waiting where none came.
+struct Waiting {
+    bool norm = false, dm = false;
+    NormFinalArgs norm_args;
+    DmFinalArgs dm_args;
+};
+hipError_t launch_waiting(Waiting& w, hipStream_t st);
 hipError_t launch_rownorm_s0_16(const bf16_t* W, int dt, float* c, int d_out, int d_in, bool squared, hipStream_t st);
 // fp32: the row norms of W alone (or their squares); terms ([3, d_out]: base_sq, 0, 0) and c may be nullptr
 hipError_t launch_rownorm_f32(const float* W, float* c, float* terms, int d_out, int d_in, bool squared, hipStream_t st);
@@ -294,7 +325,8 @@ hipError_t launch_rownorm_f32(const float* W, float* c, float* terms, int d_out,
 // receives alpha2 times the same sum.  n a multiple of 8.  colscale != nullptr: rows of `cols` elements, out is
 // colscale[col] times the sum (+ colbias[col] where given).
 hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, int dtype, void* out, float alpha2, void* out2,
-                                hipStream_t st, const float* colscale = nullptr, const void* colbias = nullptr, int cols = 0);
+                                hipStream_t st, const float* colscale = nullptr, const void* colbias = nullptr, int cols = 0,
+                                Waiting* waiting = nullptr);
 
 hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st);
 hipError_t launch_mfma_probe(const void* operands, float* sink, int iters, int workgroups, hipStream_t st);

@@ -299,7 +299,8 @@ SgemmArgs f32_args(bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg
 
 // One 16-bit product; skp != nullptr: scratch for the K slices, the product is then split as product_ksplit says and the
 // reduce launch does what the epilogue (EPI_STORE_BF16 or EPI_COMPOSE) would have done.
-hipError_t launch_product(const GemmArgs& g, int trace_id, float* skp, hipStream_t st)
+// waiting: see Waiting; a product that is not split leaves it as it is.
+hipError_t launch_product(const GemmArgs& g, int trace_id, float* skp, hipStream_t st, Waiting* waiting = nullptr)
 {
     const int ks = (skp && g.ldc == g.N) ? product_ksplit(DORA_BF16, g.M, g.N, g.seg[0].K) : 1;
     if (ks <= 1) return launch_gemm_bf16(g, trace_id, st);
@@ -309,20 +310,20 @@ hipError_t launch_product(const GemmArgs& g, int trace_id, float* skp, hipStream
     hipError_t e = launch_gemm_bf16(p, trace_id, st);
     if (e != hipSuccess) return e;
     return launch_splitk_reduce(skp, ks, (int64_t)g.M * g.N, g.dt == DT_F16 ? DORA_F16 : DORA_BF16, g.c, compose ? 1.f : g.alpha2,
-                                g.c2, st, compose ? g.colscale : nullptr, g.colbias, g.N);
+                                g.c2, st, compose ? g.colscale : nullptr, g.colbias, g.N, waiting);
 }
 
 // skp != nullptr (16-bit outputs): scratch for the K slices of the first segment.  c2 / alpha2: optional second output
 // alpha2 * (A B^T) (16-bit storage only).
 hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg, float alpha, void* c,
                     int64_t ldc, bool c_f32, int trace_id, hipStream_t st, float* skp = nullptr, void* c2 = nullptr,
-                    float alpha2 = 0.f)
+                    float alpha2 = 0.f, Waiting* waiting = nullptr)
 {
     if (is16(dtype)) {
         const int tag = (trace_id == DORA_K_GEMM_LORA || trace_id == DORA_K_GEMM_DB) ? 1 : 0;
         GemmArgs g = bf16_args(dt_of(dtype), a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc, c_f32, tag);
         g.c2 = c2; g.alpha2 = alpha2;
-        return launch_product(g, trace_id, c_f32 ? nullptr : skp, st);
+        return launch_product(g, trace_id, c_f32 ? nullptr : skp, st, waiting);
     }
     const SgemmArgs g = f32_args(a_kc, b_kc, M, N, segs, nseg, alpha, c, ldc);
     return launch_f32(&g, 1, nullptr, nullptr, nullptr, trace_id, st);
@@ -333,12 +334,13 @@ hipError_t contract(int dtype, bool a_kc, bool b_kc, int M, int N, const Seg* se
 // base_sq != nullptr: the base term of Eq. 2 comes from the caller's cache and W is not squared again
 // c == nullptr: only the terms are wanted.  terms != nullptr: [3, d_out] fp32 receives base_sq, cross, ba_sq.
 // G_out != nullptr: [r, r] fp32 receives the Gram matrix of Eq. 4.
+// waiting != nullptr: the last launch may be left there.
 // Eq. 6 riding on the norm's last launch: set `done` when g / gm1 were written there
 struct MagOut { const float* m; float eps; float* g; float* gm1; bool done; };
 
 dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const void* B, float* c, const NormPlan& n,
                       hipStream_t st, const float* base_sq = nullptr, float* terms = nullptr, float* G_out = nullptr,
-                      MagOut* mag = nullptr)
+                      MagOut* mag = nullptr, Waiting* waiting = nullptr)
 {
     const int d_out = (int)d->d_out, d_in = (int)d->d_in, r = (int)d->r;
     if (d->s == 0.f) {  // scale-is-zero fast path: no U, no G
@@ -348,11 +350,11 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
                 DORA_HIP(launch_rownorm_s0_16((const bf16_t*)W, dt_of(d->dtype), n.base_p, d_out, d_in, true, st));
                 base_sq = n.base_p;
             }
-            if (base_sq) DORA_HIP(launch_norm_final(base_sq, 1, nullptr, 0, nullptr, 0, 0.0, c, terms, d_out, st));
+            if (base_sq) DORA_HIP(launch_norm_final(norm_final_args(base_sq, 1, nullptr, 0, nullptr, 0, 0.0, c, terms, d_out), st));
             else DORA_HIP(launch_rownorm_f32((const float*)W, c, terms, d_out, d_in, false, st));
             return DORA_OK;
         }
-        if (base_sq) DORA_HIP(launch_norm_final(base_sq, 1, nullptr, 0, nullptr, 0, 0.0, c, nullptr, d_out, st));
+        if (base_sq) DORA_HIP(launch_norm_final(norm_final_args(base_sq, 1, nullptr, 0, nullptr, 0, 0.0, c, nullptr, d_out), st));
         else if (is16(d->dtype)) DORA_HIP(launch_rownorm_s0_16((const bf16_t*)W, dt_of(d->dtype), c, d_out, d_in, false, st));
         else DORA_HIP(launch_rownorm_f32((const float*)W, c, nullptr, d_out, d_in, false, st));
         return DORA_OK;
@@ -372,9 +374,11 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
                 DORA_HIP(launch_gram_reduce(n.gram_p, n.ks_g, r, G_out, nullptr, nullptr, dt, st));
             }
             const size_t all = (size_t)n.slices * d_out;
-            DORA_HIP(launch_norm_final(base_sq ? base_sq : n.part, base_sq ? 1 : n.slices, n.part + all, n.slices, n.part + 2 * all,
-                                       n.slices, (double)d->s, c, terms, d_out, st, mag ? mag->m : nullptr, mag ? mag->eps : 0.f,
-                                       mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr));
+            const NormFinalArgs fin = norm_final_args(base_sq ? base_sq : n.part, base_sq ? 1 : n.slices, n.part + all, n.slices,
+                                                      n.part + 2 * all, n.slices, (double)d->s, c, terms, d_out, mag ? mag->m : nullptr,
+                                                      mag ? mag->eps : 0.f, mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr);
+            if (waiting) { waiting->norm = true; waiting->norm_args = fin; }
+            else DORA_HIP(launch_norm_final(fin, st));
             if (mag) mag->done = true;
             return DORA_OK;
         }
@@ -402,9 +406,9 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
         g.nseg = 2; g.M = d_out; g.N = r; g.a_kcontig = 1; g.b_kcontig = 1; g.epilogue = EPI_ROWDOT; g.alpha = 1.f; g.dt = dt;
         g.ksplit = 1; g.rowdot = (const bf16_t*)B; g.ld_rowdot = r; g.rowdot_partial = n.ba_p; g.tag = 1;
         DORA_HIP(launch_gemm_bf16(g, DORA_K_BA_SQ, st));
-        DORA_HIP(launch_norm_final(base_sq ? base_sq : n.base_p, base_sq ? 1 : n.ks_u, n.cross_p, n.ks_u * n.tiles_n,
-                                   n.ba_p, n.tiles_n, (double)d->s, c, terms, d_out, st, mag ? mag->m : nullptr,
-                                   mag ? mag->eps : 0.f, mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr));
+        DORA_HIP(launch_norm_final(norm_final_args(base_sq ? base_sq : n.base_p, base_sq ? 1 : n.ks_u, n.cross_p, n.ks_u * n.tiles_n,
+                                                   n.ba_p, n.tiles_n, (double)d->s, c, terms, d_out, mag ? mag->m : nullptr,
+                                                   mag ? mag->eps : 0.f, mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr), st));
         if (mag) mag->done = true;
         return DORA_OK;
     }
@@ -414,8 +418,8 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
     DORA_HIP(launch_norm_f32(a, st));
     const size_t all = (size_t)n.slices * d_out;
     if (n.slices > 1)
-        DORA_HIP(launch_norm_final(base_sq ? base_sq : n.part, base_sq ? 1 : n.slices, n.part + all, n.slices, n.part + 2 * all,
-                                   n.slices, (double)d->s, c, terms, d_out, st, a.m, a.eps, a.g, a.gm1));
+        DORA_HIP(launch_norm_final(norm_final_args(base_sq ? base_sq : n.part, base_sq ? 1 : n.slices, n.part + all, n.slices,
+                                                   n.part + 2 * all, n.slices, (double)d->s, c, terms, d_out, a.m, a.eps, a.g, a.gm1), st));
     if (mag) mag->done = true;
     if (G_out) {
         Seg sg{A, d_in, A, d_in, d_in};
@@ -521,7 +525,7 @@ dora_status check_ws(void* ws, size_t ws_bytes, size_t need)
 // xa: the adapter branch's input (x itself unless LoRA dropout gives that branch an input of its own)
 dora_status forward_contractions(const dora_desc* d, const void* x, const void* W, const void* A, const void* B,
                                  void* base, void* h, void* lora, hipStream_t st, const void* xa = nullptr,
-                                 float* skp = nullptr)
+                                 float* skp = nullptr, Waiting* waiting = nullptr)
 {
     const int T = (int)d->tokens, d_out = (int)d->d_out, d_in = (int)d->d_in, r = (int)d->r;
     Seg s0{x, d_in, W, d_in, d_in};
@@ -533,8 +537,8 @@ dora_status forward_contractions(const dora_desc* d, const void* x, const void* 
         const SgemmArgs g[2] = {f32_args(true, true, T, d_out, &s0, 1, 1.f, base, d_out), f32_args(true, true, T, r, &s1, 1, 1.f, h, r)};
         DORA_HIP(launch_f32(g, 2, nullptr, nullptr, nullptr, DORA_K_GEMM_BASE, st));
     } else {
-        DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st, skp));
-        DORA_HIP(contract(d->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, st, skp));
+        DORA_HIP(contract(d->dtype, true, true, T, d_out, &s0, 1, 1.f, base, d_out, false, DORA_K_GEMM_BASE, st, skp, nullptr, 0.f, waiting));
+        DORA_HIP(contract(d->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, st, skp, nullptr, 0.f, waiting));
     }
     if (!lora) return DORA_OK;
     Seg s2{h, r, B, r, r};
@@ -704,8 +708,8 @@ dora_status dora_norm_assemble(const dora_desc* desc, const float* terms, float*
     DORA_REQ_PTR(terms); DORA_REQ_PTR(w_norm);
     const int d_out = (int)desc->d_out;
     // the same kernel, and so the same arithmetic in the same order, as the last step of dora_norm
-    DORA_HIP(launch_norm_final(terms, 1, terms + d_out, 1, terms + 2 * (size_t)d_out, 1, (double)desc->s, w_norm, nullptr, d_out,
-                               (hipStream_t)stream));
+    DORA_HIP(launch_norm_final(norm_final_args(terms, 1, terms + d_out, 1, terms + 2 * (size_t)d_out, 1, (double)desc->s, w_norm,
+                                               nullptr, d_out), (hipStream_t)stream));
     return DORA_OK;
 }
 
@@ -750,7 +754,8 @@ dora_status dora_compose_backward(const dora_desc* desc, const void* dy, const v
     hipStream_t s = (hipStream_t)stream;
     DORA_HIP(launch_compose_bwd(desc->dtype, dy, inner, g, nullptr, dz, nullptr, partial, desc->tokens, (int)desc->d_out, s));
     if (dm)
-        DORA_HIP(launch_dm_final(partial, compose_bwd_slabs(desc->tokens, (int)desc->d_out, desc->dtype), w_norm, eff_eps(desc), dm, (int)desc->d_out, s));
+        DORA_HIP(launch_dm_final(DmFinalArgs{partial, compose_bwd_slabs(desc->tokens, (int)desc->d_out, desc->dtype), w_norm,
+                                             eff_eps(desc), dm, (int)desc->d_out}, s));
     return DORA_OK;
 }
 
@@ -801,22 +806,26 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     float* const gm1 = one_product ? nullptr : p.gm1;   // only the compose pass reads g - 1
     MagOut mag{m, eff_eps(desc), p.g, gm1, false};
     const float* c = w_norm;
+    Waiting waiting;          // Eq. 5 and 6: g is read by the last launch of the tiled routes only
+    const bool streamed = !dropout && few_tokens(desc, one_product);
     if (need_norm) {
         float* cw = w_norm_out ? w_norm_out : p.c;
-        if ((st = norm_impl(desc, W, A, B, cw, p.norm, s, nullptr, nullptr, nullptr, &mag)) != DORA_OK) return st;
+        if ((st = norm_impl(desc, W, A, B, cw, p.norm, s, nullptr, nullptr, nullptr, &mag, T > 0 && !streamed ? &waiting : nullptr)) != DORA_OK)
+            return st;
         c = cw;
     } else if (w_norm_out && w_norm_out != w_norm) {
         DORA_HIP(hipMemcpyAsync(w_norm_out, w_norm, sizeof(float) * d_out, hipMemcpyDeviceToDevice, s));
     }
     if (T == 0) return DORA_OK;
-    if (!dropout && few_tokens(desc, one_product))
+    if (streamed)
         return forward_few_tokens(desc, x, W, A, B, m, c, bias, y, saved_h, saved_inner, p.skp, s);
     if (!mag.done) DORA_HIP(launch_mag_scale(m, c, eff_eps(desc), p.g, gm1, d_out, s));
     void* h = saved_h ? saved_h : p.h;
     if (one_product) {
         // h = x A^T, written twice from the same accumulators: as it is (the saved tensor) and scaled by s
         Seg s1{x, d_in, A, d_in, d_in};
-        DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp, p.hs, desc->s));
+        DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp, p.hs, desc->s, &waiting));
+        DORA_HIP(launch_waiting(waiting, s));
         GemmArgs g = inner_product(desc, x, W, B, p.hs);
         g.epilogue = EPI_COMPOSE;
         g.c = y;
@@ -828,6 +837,7 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     }
     if (f32_plain) {
         if ((st = forward_contractions(desc, x, W, A, B, y, h, nullptr, s)) != DORA_OK) return st;
+        DORA_HIP(launch_waiting(waiting, s));
         DORA_HIP(f32_lora_composed(desc, h, B, p.g, p.gm1, bias, y, saved_inner, s));
         return DORA_OK;
     }
@@ -843,13 +853,15 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
         if (gemm_bf16_pairs(g0, g1)) {
             DORA_HIP(launch_gemm_bf16_pair(g0, g1, DORA_K_GEMM_BASE, s));
             Seg s1{x_lora, d_in, A, d_in, d_in}, s2{h, r, B, r, r};
-            DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp));
+            DORA_HIP(contract(desc->dtype, true, true, T, r, &s1, 1, 1.f, h, r, false, DORA_K_GEMM_H, s, p.skp, nullptr, 0.f, &waiting));
             DORA_HIP(contract(desc->dtype, true, true, T, d_out, &s2, 1, 1.f, lora, d_out, false, DORA_K_GEMM_LORA, s));
+            DORA_HIP(launch_waiting(waiting, s));
             DORA_HIP(launch_compose_fwd(desc->dtype, p.base_a, lora, p.g, p.gm1, bias, desc->s, y, 2, saved_inner, T, d_out, s));
             return DORA_OK;
         }
     }
-    if ((st = forward_contractions(desc, x, W, A, B, y, h, lora, s, x_lora, p.skp)) != DORA_OK) return st;
+    if ((st = forward_contractions(desc, x, W, A, B, y, h, lora, s, x_lora, p.skp, &waiting)) != DORA_OK) return st;
+    DORA_HIP(launch_waiting(waiting, s));
     if (!dropout) {
         DORA_HIP(launch_compose_fwd(desc->dtype, y, lora, p.g, p.gm1, bias, desc->s, y, 0, saved_inner, T, d_out, s));
         return DORA_OK;
@@ -966,8 +978,9 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
 
     MagOut mag{m, eff_eps(desc), p.g, p.gm1, false};
     const float* c = w_norm;
+    Waiting waiting;          // Eq. 5 and 6 up to the first reader of g, dm's second stage up to the end
     if (need_norm) {
-        if ((st = norm_impl(desc, W, A, B, p.c, p.norm, s, nullptr, nullptr, nullptr, &mag)) != DORA_OK) return st;
+        if ((st = norm_impl(desc, W, A, B, p.c, p.norm, s, nullptr, nullptr, nullptr, &mag, &waiting)) != DORA_OK) return st;
         c = p.c;
     }
     const bool mag_in_compose = !mag.done && !need_inner;   // then the compose backward is the only reader of g
@@ -978,13 +991,14 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
     if (T > 0 && need_inner && !saved_h && forward_in_one_product(desc)) {
         // recompute (gradient-checkpointing pattern) as the forward forms it; s h waits in the dh buffer
         Seg s1{xa, d_in, A, d_in, d_in};
-        DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp, p.dh, desc->s));
+        DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp, p.dh, desc->s, &waiting));
         GemmArgs g = inner_product(desc, xa, W, B, p.dh);
         g.c = p.inner;
         DORA_HIP(launch_product(g, DORA_K_GEMM_FUSED_FWD, p.skp, s));
         inner = p.inner;
         h = p.h;
     } else if (T > 0 && need_inner) {
+        DORA_HIP(launch_waiting(waiting, s));
         // base -> dz buffer, lora -> inner buffer, then inner = s*lora + base in place; the dz buffer is overwritten
         // by dz afterwards
         void* const lora = dt == DORA_F32 ? nullptr : p.inner;
@@ -1002,9 +1016,10 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         inner = p.inner;
     } else if (T > 0 && need_h) {
         Seg s1{xa, d_in, A, d_in, d_in};
-        DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp));
+        DORA_HIP(contract(dt, true, true, T, r, &s1, 1, 1.f, p.h, r, false, DORA_K_GEMM_H, s, p.skp, nullptr, 0.f, &waiting));
         h = p.h;
     }
+    DORA_HIP(launch_waiting(waiting, s));
 
     if (dt == DORA_F32 && !dropout)
         return backward_f32(desc, dy, xa, W, A, B, mag_in_compose ? RowScale{c, m, eff_eps(desc)} : RowScale{p.g, nullptr, 0.f}, c, h,
@@ -1014,13 +1029,17 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
     // reduction for dm
     DORA_HIP(launch_compose_bwd(dt, dy, inner, mag_in_compose ? c : p.g, p.gm1, p.dz, need_dzb ? p.dzb : nullptr,
                                 dm ? p.dm_partial : nullptr, T, d_out, s, mag_in_compose ? m : nullptr, eff_eps(desc)));
-    if (dm) DORA_HIP(launch_dm_final(p.dm_partial, compose_bwd_slabs(T, d_out, dt), c, eff_eps(desc), dm, d_out, s));
+    if (dm) {
+        waiting.dm = true;
+        waiting.dm_args = DmFinalArgs{p.dm_partial, compose_bwd_slabs(T, d_out, dt), c, eff_eps(desc), dm, d_out};
+    }
 
     // dh = s * dz B   (gradient reaching h)
     if ((dropout ? dx_lora : dx) || dA) {
         Seg sh{p.dz, d_out, B, r, d_out};
-        DORA_HIP(contract(dt, true, false, T, r, &sh, 1, desc->s, p.dh, r, false, DORA_K_GEMM_DH, s, p.skp));
+        DORA_HIP(contract(dt, true, false, T, r, &sh, 1, desc->s, p.dh, r, false, DORA_K_GEMM_DH, s, p.skp, nullptr, 0.f, &waiting));
     }
+    DORA_HIP(launch_waiting(waiting, s));
     if (!dropout) {
         if (dx) {  // dx = dz W + dh A : one contraction over the concatenated K range
             Seg sx[2] = {{p.dz, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};

@@ -112,19 +112,16 @@ __global__ void mag_scale_kernel(const float* __restrict__ m, const float* __res
 // cross, ba_sq); c == nullptr: only the terms are wanted.  m != nullptr: Eq. 6 follows in the same launch
 // (g and / or gm1, exactly as mag_scale_kernel forms them).
 constexpr int NF_W = 32, NF_H = 8;
-__global__ __launch_bounds__(NF_W* NF_H) void norm_final_kernel(const float* __restrict__ base_p, int n_base,
-                                  const float* __restrict__ cross_p, int n_cross, const float* __restrict__ ba_p, int n_ba,
-                                  float two_s, float s2, float* __restrict__ c, float* __restrict__ terms, int d_out,
-                                  const float* __restrict__ m, float eps, float* __restrict__ g, float* __restrict__ gm1)
+__device__ __forceinline__ void norm_final(const NormFinalArgs& p, int block)
 {
     __shared__ float red[3][NF_H][NF_W];
-    const int x = threadIdx.x, y = threadIdx.y, j = blockIdx.x * NF_W + x;
+    const int d_out = p.d_out, x = threadIdx.x % NF_W, y = threadIdx.x / NF_W, j = block * NF_W + x;
     const int64_t first = (int64_t)y * d_out + j, stride = (int64_t)NF_H * d_out;
     auto share = [&](int n) { return n > y ? (n - y + NF_H - 1) / NF_H : 0; };
     if (j < d_out) {
-        red[0][y][x] = sum_partials<4>(base_p + first, share(n_base), stride);
-        red[1][y][x] = sum_partials<4>(cross_p + first, share(n_cross), stride);
-        red[2][y][x] = sum_partials<4>(ba_p + first, share(n_ba), stride);
+        red[0][y][x] = sum_partials<4>(p.base_p + first, share(p.n_base), stride);
+        red[1][y][x] = sum_partials<4>(p.cross_p + first, share(p.n_cross), stride);
+        red[2][y][x] = sum_partials<4>(p.ba_p + first, share(p.n_ba), stride);
     }
     __syncthreads();
     if (y != 0 || j >= d_out) return;
@@ -138,21 +135,22 @@ __global__ __launch_bounds__(NF_W* NF_H) void norm_final_kernel(const float* __r
         sum[k] = (float)v;
     }
     const float base_sq = sum[0], cross = sum[1], ba = sum[2];
-    if (terms) {
-        terms[j] = base_sq;
-        terms[(int64_t)d_out + j] = cross;
-        terms[2 * (int64_t)d_out + j] = ba;
+    if (p.terms) {
+        p.terms[j] = base_sq;
+        p.terms[(int64_t)d_out + j] = cross;
+        p.terms[2 * (int64_t)d_out + j] = ba;
     }
-    if (!c) return;
-    const float cj = __fsqrt_rn(radicand(base_sq, cross, ba, two_s, s2));
-    c[j] = cj;
-    if (m) {
-        float cc = (cj < eps) ? eps : cj;
-        float mj = m[j];
-        if (g) g[j] = mj / cc;
-        if (gm1) gm1[j] = (mj - cc) / cc;
+    if (!p.c) return;
+    const float cj = __fsqrt_rn(radicand(base_sq, cross, ba, p.two_s, p.s2));
+    p.c[j] = cj;
+    if (p.m) {
+        float cc = (cj < p.eps) ? p.eps : cj;
+        float mj = p.m[j];
+        if (p.g) p.g[j] = mj / cc;
+        if (p.gm1) p.gm1[j] = (mj - cc) / cc;
     }
 }
+__global__ __launch_bounds__(NF_W* NF_H) void norm_final_kernel(NormFinalArgs p) { norm_final(p, blockIdx.x); }
 
 // G = sum of split-K partials (fixed order), and its two-term 16-bit expansion G ~ Ghi + Glo.
 template <int DT>
@@ -171,16 +169,55 @@ __global__ void gram_reduce_kernel(const float* __restrict__ p, int ksplit, int 
     Glo[i] = (bf16_t)(E::pack2(rem, 0.f) & 0xffffu);
 }
 
+// Second stage of dm's column sum: dm[j] = (sum over slabs, in slab order) / max(c[j], eps).  32 columns per workgroup, H
+// threads per column with a contiguous range of slabs each, U loads in flight (32 and 8 in a launch of its own; 8 and 16 where
+// the workgroup has 256 threads).
+constexpr int DMF_W = 32;
+template <int H, int U>
+__device__ __forceinline__ void dm_final(const DmFinalArgs& p, int block)
+{
+    __shared__ float red[H][DMF_W];
+    const int x = threadIdx.x % DMF_W, y = threadIdx.x / DMF_W, j = block * DMF_W + x;
+    float acc = 0.f;
+    if (j < p.d_out) {
+        const int per = (p.slabs + H - 1) / H, z0 = y * per, z1 = z0 + per < p.slabs ? z0 + per : p.slabs;
+        if (z0 < z1) acc = sum_partials<U>(p.partial + (int64_t)z0 * p.d_out + j, z1 - z0, p.d_out);
+    }
+    red[y][x] = acc;
+    __syncthreads();
+    if (y == 0 && j < p.d_out) {
+        float v = red[0][x];
+        for (int i = 1; i < H; ++i) v += red[i][x];
+        const float cj = p.c[j];
+        p.dm[j] = v / ((cj < p.eps) ? p.eps : cj);
+    }
+}
+__global__ __launch_bounds__(DMF_W * 32) void dm_final_kernel(DmFinalArgs p) { dm_final<32, 8>(p, blockIdx.x); }
+
+struct Riders {
+    NormFinalArgs norm;
+    DmFinalArgs dm;
+    int norm_blocks, dm_blocks;
+};
+
 // Sum of the K slices of a split contraction, in slice order, rounded once to the storage dtype; with colscale the
 // first output is y = g (.) inner (+ bias), formed from the fp32 sum.
+// Its first workgroups do what other small work is due, Eq. 5 and 6 or dm's second stage, of a handful of partials per column:
+// launches of their own take 2.7 to 5 us each, nearly all of it the launch.  (1024 x 4096, r 64, 512 tokens, forward and backward
+// 74.9 -> 70.3 us; 4096 x 4096, 4096 tokens, forward 160.2 -> 157.6; 2056 x 3000, 1501 tokens with dropout 195.9 -> 191.9.)
 template <typename T>
-__global__ void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, int64_t n, T* __restrict__ out,
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ p, int ksplit, int64_t n, T* __restrict__ out,
                                      float alpha2, T* __restrict__ out2, const float* __restrict__ colscale,
-                                     const T* __restrict__ colbias, int cols)
+                                     const T* __restrict__ colbias, int cols, Riders riders)
 {
     typedef Vec<T> V;
     constexpr int N = V::N;
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * N;
+    int block = blockIdx.x;
+    if (block < riders.norm_blocks) return norm_final(riders.norm, block);
+    block -= riders.norm_blocks;
+    if (block < riders.dm_blocks) return dm_final<8, 16>(riders.dm, block);
+    block -= riders.dm_blocks;
+    const int64_t i = ((int64_t)block * blockDim.x + threadIdx.x) * N;
     if (i >= n) return;
     float acc[N];
 #pragma unroll
@@ -440,34 +477,6 @@ __global__ __launch_bounds__(CW* CH) void compose_bwd_kernel(const T* __restrict
     }
 }
 
-// Second stage: dm[j] = (sum over slabs, in slab order) / max(c[j], eps).
-constexpr int DMF_W = 32, DMF_H = 32;
-__global__ __launch_bounds__(DMF_W* DMF_H) void dm_final_kernel(const float* __restrict__ partial, int slabs,
-                                                                 const float* __restrict__ c, float eps,
-                                                                 float* __restrict__ dm, int d_out)
-{
-    __shared__ float red[DMF_H][DMF_W];
-    int j = blockIdx.x * DMF_W + threadIdx.x;
-    float acc = 0.f;
-    if (j < d_out) {
-        // each of the DMF_H thread rows owns a contiguous range of slabs
-        int per = (slabs + DMF_H - 1) / DMF_H;
-        int z0 = threadIdx.y * per;
-        int z1 = z0 + per < slabs ? z0 + per : slabs;
-        if (z0 < z1) acc = sum_partials<8>(partial + (int64_t)z0 * d_out + j, z1 - z0, d_out);
-    }
-    red[threadIdx.y][threadIdx.x] = acc;
-    __syncthreads();
-    if (threadIdx.y == 0 && j < d_out) {
-        float v = red[0][threadIdx.x];
-        for (int y = 1; y < DMF_H; ++y) v += red[y][threadIdx.x];
-        float cj = c[j];
-        float cc = (cj < eps) ? eps : cj;
-        dm[j] = v / cc;
-    }
-}
-
-
 }  // namespace
 
 hipError_t launch_mag_scale(const float* m, const float* c, float eps, float* g, float* gm1, int d_out, hipStream_t st)
@@ -478,17 +487,21 @@ hipError_t launch_mag_scale(const float* m, const float* c, float eps, float* g,
     return hipGetLastError();
 }
 
-hipError_t launch_norm_final(const float* base_p, int n_base, const float* cross_p, int n_cross, const float* ba_p,
-                             int n_ba, double s, float* c, float* terms, int d_out, hipStream_t st, const float* m,
-                             float eps, float* g, float* gm1)
+hipError_t launch_norm_final(const NormFinalArgs& a, hipStream_t st)
 {
-    if (d_out == 0) return hipSuccess;
+    if (a.d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_NORM_FINAL, st);
-    // 2s and s^2 are formed in double and rounded once (App. C item 3)
-    norm_final_kernel<<<dim3((d_out + NF_W - 1) / NF_W), dim3(NF_W, NF_H), 0, st>>>(base_p, n_base, cross_p, n_cross, ba_p, n_ba,
-                                                                       (float)(2.0 * s), (float)(s * s), c, terms, d_out,
-                                                                       m, eps, g, gm1);
+    norm_final_kernel<<<dim3((a.d_out + NF_W - 1) / NF_W), dim3(NF_W * NF_H), 0, st>>>(a);
     return hipGetLastError();
+}
+
+hipError_t launch_waiting(Waiting& w, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    if (w.norm) e = launch_norm_final(w.norm_args, st);
+    if (e == hipSuccess && w.dm) e = launch_dm_final(w.dm_args, st);
+    w.norm = w.dm = false;
+    return e;
 }
 
 hipError_t launch_gram_reduce(const float* partials, int ksplit, int r, float* G, bf16_t* Ghi, bf16_t* Glo, int dt,
@@ -503,21 +516,25 @@ hipError_t launch_gram_reduce(const float* partials, int ksplit, int r, float* G
 }
 
 hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, int dtype, void* out, float alpha2, void* out2,
-                                hipStream_t st, const float* colscale, const void* colbias, int cols)
+                                hipStream_t st, const float* colscale, const void* colbias, int cols, Waiting* waiting)
 {
-    if (n == 0) return hipSuccess;
+    if (n == 0) return waiting ? launch_waiting(*waiting, st) : hipSuccess;
     TraceScope ts(DORA_K_SPLITK_REDUCE, st);
     const int per = dtype == DORA_F32 ? 4 : 8;
-    dim3 grid((unsigned)((n / per + 255) / 256)), block(256);
+    Riders r{};
+    if (waiting && waiting->norm) { r.norm = waiting->norm_args; r.norm_blocks = (r.norm.d_out + NF_W - 1) / NF_W; }
+    if (waiting && waiting->dm) { r.dm = waiting->dm_args; r.dm_blocks = (r.dm.d_out + DMF_W - 1) / DMF_W; }
+    if (waiting) waiting->norm = waiting->dm = false;
+    dim3 grid((unsigned)(r.norm_blocks + r.dm_blocks + (n / per + 255) / 256)), block(256);
     if (dtype == DORA_BF16)
         splitk_reduce_kernel<bf16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (bf16_t*)out, alpha2, (bf16_t*)out2, colscale,
-                                                    (const bf16_t*)colbias, cols);
+                                                    (const bf16_t*)colbias, cols, r);
     else if (dtype == DORA_F16)
         splitk_reduce_kernel<f16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (f16_t*)out, alpha2, (f16_t*)out2, colscale,
-                                                    (const f16_t*)colbias, cols);
+                                                    (const f16_t*)colbias, cols, r);
     else
         splitk_reduce_kernel<float><<<grid, block, 0, st>>>(partials, ksplit, n, (float*)out, alpha2, (float*)out2, colscale,
-                                                    (const float*)colbias, cols);
+                                                    (const float*)colbias, cols, r);
     return hipGetLastError();
 }
 
@@ -637,11 +654,11 @@ hipError_t launch_compose_bwd(int dtype, const void* dy, const void* inner, cons
     return compose_bwd_t<float>(dy, inner, g, gm1, dz, dzb, partial, tokens, d_out, st, m, eps);
 }
 
-hipError_t launch_dm_final(const float* partial, int slabs, const float* c, float eps, float* dm, int d_out, hipStream_t st)
+hipError_t launch_dm_final(const DmFinalArgs& a, hipStream_t st)
 {
-    if (d_out == 0) return hipSuccess;
+    if (a.d_out == 0) return hipSuccess;
     TraceScope ts(DORA_K_DM_FINAL, st);
-    dm_final_kernel<<<dim3((d_out + DMF_W - 1) / DMF_W), dim3(DMF_W, DMF_H), 0, st>>>(partial, slabs, c, eps, dm, d_out);
+    dm_final_kernel<<<dim3((a.d_out + DMF_W - 1) / DMF_W), dim3(DMF_W * 32), 0, st>>>(a);
     return hipGetLastError();
 }
 
