@@ -158,6 +158,10 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int trace_id, hipStream_t stream)
 // (their tiles share rounds of workgroups, and a launch is saved)
 bool gemm_bf16_pairs(const GemmArgs& a, const GemmArgs& b);
 hipError_t launch_gemm_bf16_pair(const GemmArgs& a, const GemmArgs& b, int trace_id, hipStream_t stream);
+// n input gradients and m weight gradients (one or two of each) in one launch; gemm_bf16_grads_together: whether that is the
+// cheaper way, and the only case that is taken
+bool gemm_bf16_grads_together(const GemmArgs* dx, int n, const GemmArgs* w, int m);
+hipError_t launch_gemm_bf16_grads(const GemmArgs* dx, int n, const GemmArgs* w, int m, int trace_id, hipStream_t stream);
 
 // ---- forward of a few tokens (16-bit storage) ----------------------------------------------------
 constexpr int64_t FEW_TOKENS_MAX = 64;

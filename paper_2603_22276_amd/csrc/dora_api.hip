@@ -1040,31 +1040,34 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         DORA_HIP(contract(dt, true, false, T, r, &sh, 1, desc->s, p.dh, r, false, DORA_K_GEMM_DH, s, p.skp, nullptr, 0.f, &waiting));
     }
     DORA_HIP(launch_waiting(waiting, s));
-    if (!dropout) {
-        if (dx) {  // dx = dz W + dh A : one contraction over the concatenated K range
-            Seg sx[2] = {{p.dz, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};
-            DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
-        }
-    } else {
-        Seg sx{dy, d_out, W, d_in, d_out};                                       // frozen path: dx = dy W
-        Seg sl[2] = {{p.dzb, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};     // adapter path: dx_lora = ((g-1) dy) W + dh A
-        bool paired = false;
-        if (dx && dx_lora && T > 0 && is16(dt) && product_ksplit(dt, T, d_in, d_out) == 1) {
-            // in one launch where their tiles fill rounds better together (2056 x 3000, 1501 tokens: 288 of 128 x 128 each, one
-            // and an eighth to a CU; together 144 of 256 x 256: 77 us in two launches, 59 in one)
-            const GemmArgs g0 = bf16_args(dt_of(dt), true, false, T, d_in, &sx, 1, 1.f, dx, d_in, false, 0);
-            const GemmArgs g1 = bf16_args(dt_of(dt), true, false, T, d_in, sl, 2, 1.f, dx_lora, d_in, false, 0);
-            if ((paired = gemm_bf16_pairs(g0, g1))) DORA_HIP(launch_gemm_bf16_pair(g0, g1, DORA_K_GEMM_DX, s));
-        }
-        if (dx && !paired) {
-            DORA_HIP(contract(dt, true, false, T, d_in, &sx, 1, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
-        }
-        if (dx_lora && !paired) {
-            DORA_HIP(contract(dt, true, false, T, d_in, sl, 2, 1.f, dx_lora, d_in, false, DORA_K_GEMM_DX, s, p.skp));
-        }
-    }
+    Seg sx[2] = {{p.dz, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};          // dx = dz W + dh A : one contraction over the concatenated K range
+    Seg sf{dy, d_out, W, d_in, d_out};                                           // with dropout: the frozen path, dx = dy W
+    if (dropout) sx[0].a = p.dzb;                                                // and the adapter path, dx_lora = ((g-1) dy) W + dh A
+    void* const dx_sum = dropout ? dx_lora : dx;
     Seg sa{p.dh, r, xa, d_in, T};  // dA = dh^T xa
     Seg sb{p.dz, d_out, h, r, T};  // dB = s * dz^T h
+    // 16-bit, x W^T and h split over K aside: input gradients in one launch where their tiles fill rounds better together (2056 x
+    // 3000, 1501 tokens: 288 of 128 x 128 each, one and an eighth to a CU; together 144 of 256 x 256: 77 us in two launches, 59
+    // in one), and with them the weight gradients where CUs are left for those
+    bool paired = false;
+    if (is16(dt) && T > 0 && product_ksplit(dt, T, d_in, d_out) == 1) {
+        GemmArgs in[2], wg[2];
+        int n = 0, nw = 0;
+        if (dropout && dx) in[n++] = bf16_args(dt_of(dt), true, false, T, d_in, &sf, 1, 1.f, dx, d_in, false, 0);
+        if (dx_sum) in[n++] = bf16_args(dt_of(dt), true, false, T, d_in, sx, 2, 1.f, dx_sum, d_in, false, 0);
+        if (dA) wg[nw++] = bf16_args(dt_of(dt), false, false, r, d_in, &sa, 1, 1.f, dA, d_in, true, 0);
+        if (dB) wg[nw++] = bf16_args(dt_of(dt), false, false, d_out, r, &sb, 1, desc->s, dB, r, true, 0);
+        paired = n == 2 && gemm_bf16_pairs(in[0], in[1]);
+        if ((n == 1 || paired) && gemm_bf16_grads_together(in, n, wg, nw)) {
+            DORA_HIP(launch_gemm_bf16_grads(in, n, wg, nw, DORA_K_GEMM_DX, s));
+            return DORA_OK;
+        }
+        if (paired) DORA_HIP(launch_gemm_bf16_pair(in[0], in[1], DORA_K_GEMM_DX, s));
+    }
+    if (!paired) {
+        if (dropout && dx) DORA_HIP(contract(dt, true, false, T, d_in, &sf, 1, 1.f, dx, d_in, false, DORA_K_GEMM_DX, s, p.skp));
+        if (dx_sum) DORA_HIP(contract(dt, true, false, T, d_in, sx, 2, 1.f, dx_sum, d_in, false, DORA_K_GEMM_DX, s, p.skp));
+    }
     if (dA && dB && is16(dt)) {
         // the two weight gradients are independent and individually too small to fill the chip: one launch
         GemmArgs ga = bf16_args(dt_of(dt), false, false, r, d_in, &sa, 1, 1.f, dA, d_in, true, 0);
