@@ -250,21 +250,23 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
     }
 }
 
-// Split of K for the products with a 16-bit output whose 128 x 128 tiles leave at least half the CUs without work: h = x A^T
-// and dh = s dz B over [tokens, r], x W^T and dz W of short batches.  K is cut into slices (fp32 partials in the workspace,
-// summed in slice order by a small reduce launch), as many as are cheapest in tenths of a microsecond: 4 for each K step of 64
-// of a slice, 50 for the reduce launch, and the partials written and read at 4 TB/s.  At most one workgroup per CU, 16 slices,
-// and two K steps to a slice at least.  (Against at most four slices of 16 K steps: x A^T of 512 tokens, K 4096, r 64 11.9 ->
-// 7.2 us in 16 slices; of 1501 tokens, K 3000, r 72 16.3 -> 8.7 in eight; steps of 128 tokens through 4096 x 14336 206 -> 173,
-// through 14336 x 4096 165 -> 145.)
+// Split of K for the products with a 16-bit output of at most 256 tiles of 128 x 128: h = x A^T and dh = s dz B over [tokens,
+// r], x W^T and dz W of short batches.  K is cut into slices (fp32 partials in the workspace, summed in slice order by a small
+// reduce launch), as many as are cheapest in tenths of a microsecond: for each K step of 64 of a slice 4 while every workgroup
+// has a CU to itself and 7.5 where two share one, 50 for the reduce launch, and the partials written and read at 4 TB/s.  At most
+// two workgroups per CU, 16 slices, and two K steps to a slice at least.  (Against at most four slices of 16 K steps: x A^T of
+// 512 tokens, K 4096, r 64 11.9 -> 7.2 us in 16 slices; of 1501 tokens, K 3000, r 72 16.3 -> 8.7 in eight; steps of 128 tokens
+// through 4096 x 14336 206 -> 173, through 14336 x 4096 165 -> 145.  Two workgroups to a CU pay where K is long: x A^T of 4096
+// tokens, r 384, in two slices and in five, K 4096 42 and 48 us, 14336 106 and 94, 27648 181 and 156; r 640, in one and three, K
+// 4096 49 and 55, 8192 93 and 84, 27648 286 and 207.)
 inline int product_ksplit(int dtype, int64_t M, int64_t N, int64_t K)
 {
     if (!is16(dtype) || M <= 0) return 1;
     const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), steps = (K + 63) / 64;
-    if (tiles * 2 > 256) return 1;
-    int64_t best = 1, least = 4 * steps;
-    for (int64_t ks = 2; ks <= std::min<int64_t>({256 / tiles, 16, steps / 2}); ++ks) {
-        const int64_t cost = 4 * ((steps + ks - 1) / ks) + 50 + ks * M * N * 8 / 400000;
+    if (tiles > 256) return 1;
+    int64_t best = 1, least = 8 * steps;   // (in twentieths)
+    for (int64_t ks = 2; ks <= std::min<int64_t>({512 / tiles, 16, steps / 2}); ++ks) {
+        const int64_t cost = (tiles * ks > 256 ? 15 : 8) * ((steps + ks - 1) / ks) + 100 + ks * M * N * 8 / 200000;
         if (cost < least) { least = cost; best = ks; }
     }
     return (int)best;

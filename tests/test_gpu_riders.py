@@ -17,6 +17,8 @@ SHAPES = [  # d_out, d_in, r, tokens
     (136, 136, 16, 300),        # neither
     (2056, 3000, 24, 16000),    # 125 tiles each: two slices, and as many slabs of dm as there are
     (512, 1024, 392, 100),      # rank past the norm of one launch
+    (8, 12040, 264, 6000),      # h of 141 tiles in three slices: two workgroups to a CU
+    (12040, 16, 264, 6000),     # dh the same
 ]
 
 
