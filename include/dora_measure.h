@@ -24,20 +24,20 @@ extern "C" {
  * that a throughput measurement can carry the events of its dominant kernel only.  Not thread-safe.
  */
 enum {
-    DORA_K_NORM_CROSS = 0,   /* U = W A^T tile + base_sq + rowdot(B, U) partials      */
+    DORA_K_NORM_CROSS = 0,   /* base_sq, cross and ba_sq partials (rank > 384: no ba_sq)*/
     DORA_K_GRAM = 1,         /* G = A A^T split-K partials                             */
     DORA_K_GRAM_REDUCE = 2,  /* fixed-order sum of Gram partials, hi/lo split          */
     DORA_K_BA_SQ = 3,        /* rowdot(B, B G) partials                                */
-    DORA_K_NORM_FINAL = 4,   /* Eq. 5 assembly                                         */
+    DORA_K_NORM_FINAL = 4,   /* Eq. 5 assembly (or inside SPLITK_REDUCE)               */
     DORA_K_MAG_SCALE = 5,    /* Eq. 6                                                  */
     DORA_K_GEMM_BASE = 6,    /* base = x W^T                                           */
     DORA_K_GEMM_H = 7,       /* h = x A^T                                              */
     DORA_K_GEMM_LORA = 8,    /* lora = h B^T                                           */
     DORA_K_COMPOSE_FWD = 9,
     DORA_K_COMPOSE_BWD = 10,
-    DORA_K_DM_FINAL = 11,    /* second stage of the dm column reduction                */
+    DORA_K_DM_FINAL = 11,    /* second stage of dm's column sum (or in SPLITK_REDUCE)  */
     DORA_K_GEMM_DH = 12,     /* dh = s dz B                                            */
-    DORA_K_GEMM_DX = 13,     /* dx = dz W + dh A                                       */
+    DORA_K_GEMM_DX = 13,     /* dx = dz W + dh A (few tiles: dA and dB in the same launch)*/
     DORA_K_GEMM_DA = 14,     /* dA = dh^T x (16-bit, small fp32: dB in the same launch)*/
     DORA_K_GEMM_DB = 15,     /* dB = s dz^T h                                          */
     DORA_K_PROBE_COPY = 16,  /* dora_probe_copy                                        */

@@ -1042,15 +1042,16 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         DORA_HIP(contract(dt, true, false, T, r, &sh, 1, desc->s, p.dh, r, false, DORA_K_GEMM_DH, s, p.skp, nullptr, 0.f, &waiting));
     }
     DORA_HIP(launch_waiting(waiting, s));
-    Seg sx[2] = {{p.dz, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};          // dx = dz W + dh A : one contraction over the concatenated K range
-    Seg sf{dy, d_out, W, d_in, d_out};                                           // with dropout: the frozen path, dx = dy W
-    if (dropout) sx[0].a = p.dzb;                                                // and the adapter path, dx_lora = ((g-1) dy) W + dh A
+    // dx = dz W + dh A : one contraction over the concatenated K range.  With dropout the frozen path, dx = dy W, and the adapter
+    // path, dx_lora = ((g-1) dy) W + dh A
+    Seg sx[2] = {{dropout ? p.dzb : p.dz, d_out, W, d_in, d_out}, {p.dh, r, A, d_in, r}};
+    Seg sf{dy, d_out, W, d_in, d_out};
     void* const dx_sum = dropout ? dx_lora : dx;
     Seg sa{p.dh, r, xa, d_in, T};  // dA = dh^T xa
     Seg sb{p.dz, d_out, h, r, T};  // dB = s * dz^T h
-    // 16-bit, x W^T and h split over K aside: input gradients in one launch where their tiles fill rounds better together (2056 x
-    // 3000, 1501 tokens: 288 of 128 x 128 each, one and an eighth to a CU; together 144 of 256 x 256: 77 us in two launches, 59
-    // in one), and with them the weight gradients where CUs are left for those
+    // 16-bit, K not in slices: both input gradients in one launch where their tiles fill rounds better together (2056 x 3000,
+    // 1501 tokens: 288 of 128 x 128 each, one and an eighth to a CU; together 144 of 256 x 256: 77 us in two launches, 59 in
+    // one), and the weight gradients with them where CUs are left for those
     bool paired = false;
     if (is16(dt) && T > 0 && product_ksplit(dt, T, d_in, d_out) == 1) {
         GemmArgs in[2], wg[2];
