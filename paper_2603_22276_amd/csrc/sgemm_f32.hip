@@ -100,11 +100,14 @@ __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float*
     const int M = p.M, N = p.N;
     const int tiles_n = (N + 31) / 32;                 // one-dimensional grid: no 65535 limit on the row-tile count
     const int m0 = wg / tiles_n * 32, n0 = wg % tiles_n * 32;
-    f32x4_t acc[2][2];
+    // Where four waves share K, a sum of its own for every 64 k: a quarter of K in one chain of additions has up to 1.8 times the
+    // error of a sixteenth (704 x 1760, r 20, 1509 tokens, dB 5.2e-7 against 2.9e-7; in short sums 2.5e-7 and no slower).
+    constexpr bool APART = WK == 4;
+    f32x4_t acc[2][2], total[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 2; ++j) acc[i][j] = total[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     for (int sidx = 0; sidx < p.nseg; ++sidx) {
         const SgemmSeg sg = p.seg[sidx];
@@ -149,7 +152,22 @@ __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float*
                             for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(get(b[d][j], e), get(a[d][i], e), acc[i][j]);
                 }
             if (scaled) __builtin_amdgcn_wave_barrier();
+            if constexpr (APART) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        total[i][j] += acc[i][j];
+                        acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
         }
+    }
+    if constexpr (APART) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = total[i][j];
     }
     // lane: columns 4 lq .. +3 of block j, row l16 of block i
 #pragma unroll
