@@ -101,7 +101,7 @@ __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float*
     const int tiles_n = (N + 31) / 32;                 // one-dimensional grid: no 65535 limit on the row-tile count
     const int m0 = wg / tiles_n * 32, n0 = wg % tiles_n * 32;
     // Where four waves share K, a sum of its own for every 64 k: a quarter of K in one chain of additions has up to 1.8 times the
-    // error of a sixteenth (704 x 1760, r 20, 1509 tokens, dB 5.2e-7 against 2.9e-7; in short sums 2.5e-7 and no slower).
+    // error of a sixteenth (704 x 1760, r 20, 1509 tokens, dB 5.2e-7 against 2.9e-7; in short sums 2.3e-7 and no slower).
     constexpr bool APART = WK == 4;
     f32x4_t acc[2][2], total[2][2];
 #pragma unroll

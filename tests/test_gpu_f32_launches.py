@@ -45,7 +45,8 @@ def test_pieces_of_the_backward(d_out, d_in, r, tokens):
 
 def test_weight_gradients_in_short_sums():
     """dA and dB of few tiles share the launch of dx and its workgroups of four waves: a quarter of K in one chain of additions
-    had an error of 3.9e-7 and 5.2e-7 here, in sums of 64 k it is that of sixteen waves, 2.5e-7 and 2.9e-7; the bound lies between."""
+    had an error of 3.9e-7 and 5.2e-7 here, in sums of 64 k 2.2e-7 and 2.3e-7 (sixteen waves: 2.5e-7 and 2.9e-7); the bound lies
+    between."""
     cfg = I.DoraConfig("f32_short_sums", 704, 1760, 20, 1509, "f32", 16.0, 1e-3, seed_offset=9400)
     mod = G.Module(cfg)
     oi = dict(x=mod.f64("x"), W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=mod.inp["m"].astype(np.float64),
