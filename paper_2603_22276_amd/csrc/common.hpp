@@ -249,6 +249,8 @@ struct ScaleOut {            // out[j] = the scale, j < n
     int n;
 };
 inline int column_sum_slabs(int64_t tokens) { return (int)((tokens + COLUMN_SUM_ROWS - 1) / COLUMN_SUM_ROWS); }
+// whether the product goes to tiles, where ascale has to be there as it is (m == nullptr)
+bool f32_tiled(const SgemmArgs& a);
 // up to three products and smaller pieces of work that do not need one another, in one launch
 hipError_t launch_f32(const SgemmArgs* g, int n, const ColumnSum* sum, const ColumnFinal* fin, const ScaleOut* scale, int trace_id,
                       hipStream_t stream);

@@ -924,6 +924,10 @@ static dora_status backward_f32(const dora_desc* d, const void* dy, const void* 
     if (dx || dA) {
         Seg sh{dy, d_out, B, r, d_out};
         q[n] = f32_args(true, false, T, r, &sh, 1, d->s, dh, r);
+        if (g.m && f32_tiled(q[0])) {                  // tiles do not form it: a launch of its own, 4 us beside 50 and more
+            DORA_HIP(launch_mag_scale(g.m, g.g, g.eps, g_buf, nullptr, d_out, s));
+            g = RowScale{g_buf, nullptr, 0.f};
+        }
         q[n].seg[0].scaled = true; q[n++].ascale = g;
     }
     const ColumnSum sum{(const float*)dy, (const float*)inner, T, d_out, dm_partial};

@@ -512,6 +512,8 @@ __global__ __launch_bounds__(64 * NORM_WAVES) void norm_f32_kernel(NormF32Args p
 
 }  // namespace
 
+bool f32_tiled(const SgemmArgs& a) { return tile_rows(a) != 0; }
+
 hipError_t launch_f32(const SgemmArgs* g, int n, const ColumnSum* sum, const ColumnFinal* fin, const ScaleOut* scale,
                       int trace_id, hipStream_t stream)
 {
@@ -524,6 +526,9 @@ hipError_t launch_f32(const SgemmArgs* g, int n, const ColumnSum* sum, const Col
             if (!g[i].a_kcontig && g[i].b_kcontig) return hipErrorInvalidValue;
             p.g[i] = g[i];
             p.tiled[i] = tile_rows(g[i]);
+            // a scale in tiles is taken as it is: one that has to be formed there would pass as its own denominator
+            for (int k = 0; k < g[i].nseg; ++k)
+                if (p.tiled[i] && g[i].seg[k].scaled && g[i].ascale.m) return hipErrorInvalidValue;
             any_tiled |= p.tiled[i] != 0;
             long_k |= longest_k(g[i]) >= 256;
             end += p.tiled[i] ? tiles(g[i], p.tiled[i], TS) : tiles(g[i], 32, 32);

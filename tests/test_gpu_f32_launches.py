@@ -59,3 +59,26 @@ def test_weight_gradients_in_short_sums():
     for name, got, ref in (("dA", dA, b["dA"]), ("dB", dB, b["dB"])):
         err = np.linalg.norm(G.to_f64(got) - ref) / np.linalg.norm(ref)
         assert err < 3.5e-7, (name, err)
+
+
+@pytest.mark.parametrize("d_out,d_in,r,tokens", [
+    (256, 512, 64, 8192),       # dh in 256 tiles of 32 x 64
+    (36, 20, 8, 8200),          # in 129 of 64 x 64, the last of eight rows
+    (68, 132, 384, 1409),       # in 138, the last of one row
+    (68, 132, 384, 1407),       # in 132
+])
+def test_scale_of_a_tiled_dh(d_out, d_in, r, tokens):
+    """g reaches dh as it reaches dx, whether it has to be formed from the norm (given, inner saved or not needed) or is there
+    already.  m is two to seven times the norm, so that neither can stand for the other."""
+    cfg = I.stress(I.DoraConfig(f"f32_tiled_dh_{d_out}_{d_in}_{r}_{tokens}", d_out, d_in, r, tokens, "f32", 16.0, 1e-3, seed_offset=9500))
+    inp = I.make_inputs(cfg)
+    inp["m"] = (inp["m"] * np.random.default_rng(5).uniform(2.0, 7.0, d_out)).astype(np.float32)
+    mod = G.Module(cfg, inp)
+    tol = G.TOL["f32"]["tensor"]
+    oi = dict(x=mod.f64("x"), W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=inp["m"].astype(np.float64), s=float(inp["s"]), eps=cfg.eps)
+    out, b = mod.forward(), O.backward(mod.f64("dy"), **oi)
+    for c in (out["c"], None):
+        for h, inner, want_dm in ((out["h"], out["inner"], True), (out["h"], None, False), (None, None, True)):
+            got = mod.backward(w_norm=c, h=h, inner=inner, want_dm=want_dm)
+            for k in ("dx", "dA", "dB") + (("dm",) if want_dm else ()):
+                G.assert_close(k, G.to_f64(got[k]), b[k], tol)
