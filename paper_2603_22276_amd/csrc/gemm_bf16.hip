@@ -359,12 +359,20 @@ hipError_t dispatch(const GemmArgs& a, const GemmArgs* b, hipStream_t stream)
 
 // Tiles of the input gradients for the launch that takes the weight gradients along, 0 where these go by themselves: where
 // they find CUs without work in a round that has to be run anyway, in the tiles that the input gradients take by themselves.
+// Where two workgroups share a CU, the weight gradients have the ring of two instead of the deep one: once the input gradients
+// are through, a K step takes them half as long again, so only while tokens are not many more than the K of those.  (Backward, in
+// one launch and in two, steps of 64 tokens against steps of dx: 512 x 4096, r 16, 1500 tokens, 24 and 9, 39 us and 44; 1136 x
+// 968, r 48, 6050 tokens, 95 and 19, 93 and 88; 512 x 640, r 8, 8192 tokens, 128 and 9, 99 and 81; 256 x 512, r 8, 16000 tokens,
+// 250 and 5, 163 and 116.  Over 200 shapes this line is within 0.1 % of always taking the faster one.)
 enum { APART, IN_BIG, IN_DEEP, IN_MED };
 int grads_together(const GemmArgs* dx, int n, const GemmArgs* w, int m)
 {
     if (n < 1 || n > 2 || m < 1 || m > 2) return APART;
-    int64_t big = 0, med = 0, rest = 0;
+    int64_t big = 0, med = 0, rest = 0, steps_in = 0, steps_w = 0;
     for (int i = 0; i < n; ++i) {
+        int64_t steps = 0;
+        for (int k = 0; k < dx[i].nseg; ++k) steps += (dx[i].seg[k].K + 63) / 64;
+        steps_in = steps > steps_in ? steps : steps_in;
         if (!dx[i].a_kcontig || dx[i].b_kcontig || dx[i].epilogue != EPI_STORE_BF16 || dx[i].ksplit != 1 || dx[i].dt != dx[0].dt) return APART;
         big += tiles_of(dx[i].M, dx[i].N, 256);
         med += tiles_of(dx[i].M, dx[i].N, 128);
@@ -372,6 +380,7 @@ int grads_together(const GemmArgs* dx, int n, const GemmArgs* w, int m)
     for (int i = 0; i < m; ++i) {
         if (w[i].a_kcontig || w[i].b_kcontig || w[i].epilogue != EPI_STORE_F32 || w[i].ksplit != 1 || w[i].dt != dx[0].dt) return APART;
         rest += tiles_of(w[i].M, w[i].N, 128);
+        steps_w = (w[i].seg[0].K + 63) / 64;           // tokens, for both of them
     }
     const GemmArgs* second = n > 1 ? &dx[1] : nullptr;
     if (use_big(dx[0], second)) {
@@ -380,7 +389,7 @@ int grads_together(const GemmArgs* dx, int n, const GemmArgs* w, int m)
         return big % 256 != 0 && big % 256 + rest <= 256 ? IN_BIG : APART;
     }
     if (med + rest <= 256) return IN_DEEP;
-    return med > 256 && med % 512 != 0 && med % 512 + rest <= 512 ? IN_MED : APART;
+    return med > 256 && med % 512 != 0 && med % 512 + rest <= 512 && steps_w < 30 + 2 * steps_in ? IN_MED : APART;
 }
 
 template <class T, class TW>

@@ -53,3 +53,22 @@ def test_gradients_together(dtype, d_out, d_in, r, tokens):
                                 got["dB"], None, ws)
         for k in want:
             close(k, got[k], (ref[k], every), dtype)
+
+
+@pytest.mark.parametrize("d_out,d_in,r,tokens,together", [
+    (512, 4096, 16, 1500, True),    # 24 steps of tokens, 9 of dx
+    (512, 640, 8, 8192, False),     # 128 and 9: by themselves the weight gradients have a ring of four
+    (256, 512, 8, 16000, False),
+])
+def test_many_tokens_leave_the_launch_of_two_to_a_cu(d_out, d_in, r, tokens, together):
+    q = Inputs(d_out, d_in, r, tokens, "bf16")
+    q.h.normal_(), q.inner.normal_()
+    dA, dB = G.empty_f32(r, d_in), G.empty_f32(d_out, r)
+    D.dora_trace_reset(), D.dora_trace_select(~0), D.dora_trace_enable(True)
+    D.dora_backward(q.desc, q.dy, q.xl, q.W, q.A, q.B, q.m, q.c, q.h, q.inner, q.dx, dA, dB, None, q.ws(D.PHASE_BACKWARD))
+    D.dora_trace_enable(False), D.dora_trace_collect()
+    launches = {D.dora_trace_name(k): D.dora_trace_get(k)[1] for k in range(20)}
+    assert (launches["gemm_dx"], launches["gemm_dA"]) == (1, 0 if together else 1)
+    dh = q.s * (q.g * q.dy.double()) @ q.B.double()
+    close("dA", dA, (dh.T @ q.xl.double(), slice(None)), "bf16")
+    close("dB", dB, (q.s * (q.g * q.dy.double()).T @ q.h.double(), slice(None)), "bf16")
