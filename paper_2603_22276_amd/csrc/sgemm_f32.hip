@@ -14,6 +14,7 @@
 // product and pass, 49), of 1000 x 772, r 36, 1500 tokens 117 us (171); 43 shapes 1.02 to 1.66 times faster.
 #include "common.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace dora {
@@ -90,7 +91,7 @@ __device__ __forceinline__ void finish(const SgemmArgs& p, int m, int n, float4 
 // the latency of a serial K loop, not by arithmetic, so the fragments come straight from memory into registers, DEPTH
 // groups of 16 k in flight per wave, and no wave waits for another before the end.
 constexpr int SPLIT_LD = 36;
-template <int WK, bool A_KC, bool B_KC>
+template <int WK, bool SHORT, bool A_KC, bool B_KC>
 __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float* red)
 {
     constexpr bool MAY_SCALE = A_KC && !B_KC;
@@ -100,9 +101,9 @@ __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float*
     const int M = p.M, N = p.N;
     const int tiles_n = (N + 31) / 32;                 // one-dimensional grid: no 65535 limit on the row-tile count
     const int m0 = wg / tiles_n * 32, n0 = wg % tiles_n * 32;
-    // Where four waves share K, a sum of its own for every 64 k: a quarter of K in one chain of additions has up to 1.8 times the
-    // error of a sixteenth (704 x 1760, r 20, 1509 tokens, dB 5.2e-7 against 2.9e-7; in short sums 2.3e-7 and no slower).
-    constexpr bool APART = WK == 4;
+    // SHORT: a sum of its own for every 64 k of a wave.  As one chain of additions a wave's share of K has up to twice the error (four
+    // waves, 704 x 1760, r 20, 1509 tokens, dB 5.2e-7, in short sums 2.3e-7; sixteen, 64 x 64, r 4, 20000 tokens 7.2e-7 and 2.4e-7).
+    // Four waves always take them, sixteen (3 % slower with them over a K of 10000) where they stand in for four.
     f32x4_t acc[2][2], total[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -152,7 +153,7 @@ __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float*
                             for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(get(b[d][j], e), get(a[d][i], e), acc[i][j]);
                 }
             if (scaled) __builtin_amdgcn_wave_barrier();
-            if constexpr (APART) {
+            if constexpr (SHORT) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -163,18 +164,12 @@ __device__ __forceinline__ void split_product(const SgemmArgs& p, int wg, float*
             }
         }
     }
-    if constexpr (APART) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = total[i][j];
-    }
     // lane: columns 4 lq .. +3 of block j, row l16 of block i
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            *reinterpret_cast<f32x4_t*>(red + wave * 32 * LD + (i * 16 + l16) * LD + j * 16 + lq * 4) = acc[i][j];
+            *reinterpret_cast<f32x4_t*>(red + wave * 32 * LD + (i * 16 + l16) * LD + j * 16 + lq * 4) = SHORT ? total[i][j] : acc[i][j];
     __syncthreads();
     for (int e = threadIdx.x; e < 256; e += 64 * WK) {
         const int m = e / 8, n = e % 8 * 4;
@@ -379,7 +374,7 @@ struct F32Launch {
     int tiled[3];            // rows of a tile: 64 x 64 or 32 x 64, or 0: split 32 x 32 ones
 };
 
-template <int WK>
+template <int WK, bool SHORT>
 __global__ __launch_bounds__(64 * WK, 4) void f32_kernel(F32Launch p)
 {
     constexpr int FLOATS = WK * 32 * SPLIT_LD > 2 * 2 * TS * TK ? WK * 32 * SPLIT_LD : 2 * 2 * TS * TK;
@@ -404,9 +399,9 @@ __global__ __launch_bounds__(64 * WK, 4) void f32_kernel(F32Launch p)
         if (p.tiled[q] == 64) return tile(std::integral_constant<int, 64>{});
         if (p.tiled[q] == 32) return tile(std::integral_constant<int, 32>{});
     }
-    if (!g.a_kcontig) split_product<WK, false, false>(g, wg, lds);
-    else if (g.b_kcontig) split_product<WK, true, true>(g, wg, lds);
-    else split_product<WK, true, false>(g, wg, lds);
+    if (!g.a_kcontig) split_product<WK, SHORT, false, false>(g, wg, lds);
+    else if (g.b_kcontig) split_product<WK, SHORT, true, true>(g, wg, lds);
+    else split_product<WK, SHORT, true, false>(g, wg, lds);
 }
 
 int64_t tiles(const SgemmArgs& a, int tm, int tn) { return a.M <= 0 || a.N <= 0 ? 0 : (int64_t)((a.N + tn - 1) / tn) * ((a.M + tm - 1) / tm); }
@@ -420,6 +415,68 @@ int tile_rows(const SgemmArgs& a)
     const int64_t t64 = tiles(a, 64, TS), t32 = tiles(a, 32, TS);
     if (t64 < 128) return 0;
     return (t32 + 255) / 256 * 11 < (t64 + 255) / 256 * 20 ? 32 : 64;
+}
+
+int64_t sum_of_k(const SgemmArgs& a) { return a.seg[0].K + (a.nseg > 1 ? (int64_t)a.seg[1].K : 0); }
+
+// Time of a workgroup in tenths of a microsecond: 5 for a step of 32 k in tiles, 10 for 256 k of a split product in four waves.
+int64_t wg_cost(const SgemmArgs& a) { return tile_rows(a) ? sum_of_k(a) / 32 * 5 : sum_of_k(a) / 256 * 10; }
+
+// Beside tiles a split product has four waves to a workgroup instead of sixteen.  Where its K is so long that it would end well
+// after the tiles (steps of 32 k: a CU's share of them, or a tile's own), it goes to a launch of its own.  (Backward, in one launch
+// and in two: 84 x 12, r 4, 29613 tokens 329 us and 253; 14876 x 548, r 20, 2 tokens 292 and 235; 8 x 464, r 20, 20141 tokens 229
+// and 198; 56 x 900, r 44, 666 tokens 15.5 and 23; 76 x 3904, r 16, 1180 tokens 36 and 44.  Over 200 mixed shapes the line is
+// within 0.1 % of always taking the faster one; always one launch 3.5 %, always two 9.7 %.)
+bool split_apart(const SgemmArgs* g, int n)
+{
+    int64_t share = 0, longest = 0, k = 0;
+    for (int i = 0; i < n; ++i) {
+        if (g[i].M <= 0 || g[i].N <= 0) continue;
+        const int64_t steps = (sum_of_k(g[i]) + 31) / 32;
+        if (tile_rows(g[i])) { share += tiles(g[i], 64, TS) * steps; longest = std::max(longest, steps); }
+        else k = std::max(k, sum_of_k(g[i]));
+    }
+    return share > 0 && k > 1000 + 400 * std::max(share / 256, longest);
+}
+
+hipError_t launch_one(const SgemmArgs* g, int n, const ColumnSum* sum, const ColumnFinal* fin, const ScaleOut* scale, int trace_id,
+                      hipStream_t stream, bool short_sums)
+{
+    F32Launch p{};
+    int64_t end = 0;
+    bool any_tiled = false, long_k = false;
+    for (int i = 0; i < n; ++i) {
+        if (!g[i].a_kcontig && g[i].b_kcontig) return hipErrorInvalidValue;
+        const int rows = tile_rows(g[i]);
+        // a scale in tiles is taken as it is: one that has to be formed there would pass as its own denominator
+        for (int k = 0; k < g[i].nseg; ++k)
+            if (rows && g[i].seg[k].scaled && g[i].ascale.m) return hipErrorInvalidValue;
+        any_tiled |= rows != 0;
+        long_k |= longest_k(g[i]) >= 256;
+        // the one whose workgroups take longest first: a split one of many k behind rounds of tiles would end alone
+        int at = i;
+        for (; at > 0 && wg_cost(g[i]) > wg_cost(p.g[at - 1]); --at) { p.g[at] = p.g[at - 1]; p.tiled[at] = p.tiled[at - 1]; }
+        p.g[at] = g[i];
+        p.tiled[at] = rows;
+    }
+    for (int i = 0; i < 3; ++i) {
+        if (i < n) end += p.tiled[i] ? tiles(p.g[i], p.tiled[i], TS) : tiles(p.g[i], 32, 32);
+        p.first[i] = (int)end;
+    }
+    if (sum) { p.sum = *sum; end += (int64_t)((sum->d_out + 255) / 256) * column_sum_slabs(sum->tokens); }
+    p.first[3] = (int)end;
+    if (fin) { p.fin = *fin; end += (fin->d_out + 63) / 64; }
+    p.first[4] = (int)end;
+    const bool sixteen = long_k && !any_tiled;
+    if (scale) { p.scale = *scale; end += (scale->n + (sixteen ? 1023 : 255)) / (sixteen ? 1024 : 256); }
+    if (end == 0) return hipSuccess;
+    TraceScope ts(trace_id, stream);
+    // sixteen waves to a workgroup where a product's K gives each of them a group of 16, four beside tiles and for the
+    // products over the rank
+    if (sixteen && short_sums) f32_kernel<16, true><<<dim3((unsigned)end), dim3(64 * 16), 0, stream>>>(p);
+    else if (sixteen) f32_kernel<16, false><<<dim3((unsigned)end), dim3(64 * 16), 0, stream>>>(p);
+    else f32_kernel<4, true><<<dim3((unsigned)end), dim3(64 * 4), 0, stream>>>(p);
+    return hipGetLastError();
 }
 
 // Norm: 16 rows per workgroup, its sixteen waves take 32 columns in turn.  V = B A of 16 x 32 stays in registers and meets W
@@ -518,36 +575,15 @@ hipError_t launch_f32(const SgemmArgs* g, int n, const ColumnSum* sum, const Col
                       int trace_id, hipStream_t stream)
 {
     if (n < 0 || n > 3) return hipErrorInvalidValue;
-    F32Launch p{};
-    int64_t end = 0;
-    bool any_tiled = false, long_k = false;
-    for (int i = 0; i < 3; ++i) {
-        if (i < n) {
-            if (!g[i].a_kcontig && g[i].b_kcontig) return hipErrorInvalidValue;
-            p.g[i] = g[i];
-            p.tiled[i] = tile_rows(g[i]);
-            // a scale in tiles is taken as it is: one that has to be formed there would pass as its own denominator
-            for (int k = 0; k < g[i].nseg; ++k)
-                if (p.tiled[i] && g[i].seg[k].scaled && g[i].ascale.m) return hipErrorInvalidValue;
-            any_tiled |= p.tiled[i] != 0;
-            long_k |= longest_k(g[i]) >= 256;
-            end += p.tiled[i] ? tiles(g[i], p.tiled[i], TS) : tiles(g[i], 32, 32);
-        }
-        p.first[i] = (int)end;
+    if (!split_apart(g, n)) return launch_one(g, n, sum, fin, scale, trace_id, stream, false);
+    SgemmArgs part[2][3];
+    int m[2] = {0, 0};
+    for (int i = 0; i < n; ++i) {
+        const int t = tile_rows(g[i]) != 0;
+        part[t][m[t]++] = g[i];
     }
-    if (sum) { p.sum = *sum; end += (int64_t)((sum->d_out + 255) / 256) * column_sum_slabs(sum->tokens); }
-    p.first[3] = (int)end;
-    if (fin) { p.fin = *fin; end += (fin->d_out + 63) / 64; }
-    p.first[4] = (int)end;
-    const bool sixteen = long_k && !any_tiled;
-    if (scale) { p.scale = *scale; end += (scale->n + (sixteen ? 1023 : 255)) / (sixteen ? 1024 : 256); }
-    if (end == 0) return hipSuccess;
-    TraceScope ts(trace_id, stream);
-    // sixteen waves to a workgroup where a product's K gives each of them a group of 16, four beside tiles and for the
-    // products over the rank
-    if (sixteen) f32_kernel<16><<<dim3((unsigned)end), dim3(64 * 16), 0, stream>>>(p);
-    else f32_kernel<4><<<dim3((unsigned)end), dim3(64 * 4), 0, stream>>>(p);
-    return hipGetLastError();
+    const hipError_t e = launch_one(part[0], m[0], sum, fin, scale, trace_id, stream, true);
+    return e != hipSuccess ? e : launch_one(part[1], m[1], nullptr, nullptr, nullptr, trace_id, stream, false);
 }
 
 hipError_t launch_norm_f32(const NormF32Args& a, hipStream_t stream)

@@ -82,3 +82,24 @@ def test_scale_of_a_tiled_dh(d_out, d_in, r, tokens):
             got = mod.backward(w_norm=c, h=h, inner=inner, want_dm=want_dm)
             for k in ("dx", "dA", "dB") + (("dm",) if want_dm else ()):
                 G.assert_close(k, G.to_f64(got[k]), b[k], tol)
+
+
+@pytest.mark.parametrize("d_out,d_in,r,tokens,launches", [
+    (84, 12, 4, 29613, 2),      # dx in tiles, dA and dB over all tokens: by themselves, sixteen waves to a workgroup
+    (8196, 20, 12, 90, 2),      # dB in tiles, dx over 8208 k
+    (56, 900, 44, 666, 1),      # dx in tiles, dA and dB short enough beside them
+    (140, 940, 224, 3001, 1),   # the longer dA and dB ahead of many tiles of dx
+])
+def test_long_sums_beside_tiles(d_out, d_in, r, tokens, launches):
+    cfg = I.stress(I.DoraConfig(f"f32_long_{d_out}_{d_in}_{r}_{tokens}", d_out, d_in, r, tokens, "f32", 16.0, 1e-3, seed_offset=9600))
+    mod = G.Module(cfg)
+    oi = dict(x=mod.f64("x"), W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=mod.inp["m"].astype(np.float64),
+              s=float(mod.inp["s"]), eps=cfg.eps)
+    out, b = mod.forward(), O.backward(mod.f64("dy"), **oi)
+    D.dora_trace_reset(), D.dora_trace_select(~0), D.dora_trace_enable(True)
+    got = mod.backward(w_norm=out["c"], h=out["h"], inner=out["inner"])
+    D.dora_trace_enable(False), D.dora_trace_collect()
+    counts = {D.dora_trace_name(k): D.dora_trace_get(k)[1] for k in range(20)}
+    assert counts["gemm_dx"] == launches
+    for k in ("dx", "dA", "dB", "dm"):
+        G.assert_close(k, G.to_f64(got[k]), b[k], G.TOL["f32"]["tensor"])
