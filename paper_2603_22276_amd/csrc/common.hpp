@@ -268,6 +268,7 @@ struct NormF32Args {
     float *g, *gm1;
     int slices;
     float* part;
+    int row_blocks;         // of 16 rows to a workgroup: 1 or 2
 };
 hipError_t launch_norm_f32(const NormF32Args& a, hipStream_t stream);
 

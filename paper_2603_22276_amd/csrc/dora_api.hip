@@ -154,6 +154,7 @@ struct NormPlan {
     bf16_t *Ghi, *Glo;
     // where the three sums come from one launch (16-bit up to NORM_ROWS_MAX_RANK, fp32)
     int slices, tiles_per_slice;   // of the columns
+    int row_blocks;                // fp32: of 16 rows to a workgroup
     float* part;                   // [3][slices][d_out]
 };
 
@@ -216,6 +217,30 @@ void norm_slices(int64_t d_out, int64_t d_in, int64_t r, size_t fixed_bytes, siz
     }
 }
 
+// fp32 norm: rows of a workgroup (one or two blocks of 16) and slices of the columns, the cheapest in tenths of a microsecond.  A
+// CU has one workgroup of sixteen waves; a wave takes groups of 32 columns, and 64 of the rank take it 1 us (1.6 with 32 rows) with
+// a SIMD to itself and 3.5 (5.9) where four share one; with 16 rows it takes the rank in pieces of 64, whose last one costs two
+// thirds where it holds 32 or less, with 32 rows in pieces of 32.  A round of workgroups costs 1.9 more, and 5 where the slices
+// have to be added.  (16 rows, and slices only where they filled CUs without any: 5120 x 27648, r 768 4764 us, 320 workgroups in
+// two rounds, 2464 now, 1280 in five; 8192 x 8192, r 384 711 -> 595, where 16 rows read A from the L2 twice as often; 512 x 512, r
+// 512 32 -> 16; 2048 x 2048, r 128 26 -> 23; 1000 x 772, r 36 stays at 10.  88 shapes: 0.6 % from the best of 22 choices.)
+void norm_f32_shape(int64_t d_out, int64_t d_in, int64_t r, int& row_blocks, int& slices)
+{
+    static const int cost_of[2][5] = {{0, 10, 18, 27, 35}, {0, 16, 29, 43, 59}};   // of 64 ranks, by waves on a SIMD
+    const uint32_t groups = (uint32_t)(d_in + 31) / 32, blocks = (uint32_t)(d_out + 15) / 16;   // (each below 2^31 / 4)
+    const uint32_t most = std::max<uint32_t>(1, std::min<uint32_t>({(uint32_t)r / 3, groups, 32}));   // r / 3: the scratch
+    int64_t best = -1;
+    for (uint32_t rb = 1; rb <= 2; ++rb) {
+        const int64_t sixths = rb == 2 ? (r + 31) / 32 * 3 : r / 64 * 6 + (r % 64 == 0 ? 0 : r % 64 <= 32 ? 4 : 6);
+        for (uint32_t n = 1; n <= most; ++n) {
+            const uint32_t per = (groups + n - 1) / n, rounds = ((blocks + rb - 1) / rb * n + 255) / 256;
+            const int64_t walk = (int64_t)(per / 16) * cost_of[rb - 1][4] + cost_of[rb - 1][(per % 16 + 3) / 4];
+            const int64_t cost = rounds * (walk * sixths / 6 + 19) + (n > 1 ? 50 : 0);
+            if (best < 0 || cost < best) { best = cost; row_blocks = (int)rb; slices = (int)n; }
+        }
+    }
+}
+
 void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 {
     memset(&n, 0, sizeof(n));
@@ -239,11 +264,8 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
         n.gram_p = o.take<float>((size_t)n.ks_g * d->r * d->r);
         b.off = std::max(b.off, o.off);
     } else {
-        // Slices of the columns: a workgroup takes 16 rows, and 512 columns by 64 of the rank in a step of about 3.4 us.  More
-        // than one slice costs a launch (4 us), so only for work of more than three steps that leaves CUs without any: 64 x
-        // 2048, r 128 35 us in one slice, 14 in four; 2048 x 2048, r 128 37, and 23 in two.  (The scratch is that of U, G and B G, which decides what fits the static array.)
-        const int64_t steps = (int64_t)cdiv(d->d_in, 512) * cdiv(d->r, 64), blocks = cdiv(d->d_out, 16);
-        n.slices = steps <= 3 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>({256 / blocks, cdiv(d->d_in, 512), d->r / 3, 32}));
+        norm_f32_shape(d->d_out, d->d_in, d->r, n.row_blocks, n.slices);
+        // (the scratch is that of U, G and B G, which decides what fits the static array)
         n.part = b.take<float>((size_t)d->d_out * d->r);
         b.take<float>((size_t)d->r * d->r);
         b.take<float>((size_t)d->d_out * d->r);
@@ -416,7 +438,7 @@ dora_status norm_impl(const dora_desc* d, const void* W, const void* A, const vo
     }
     const NormF32Args a{(const float*)W, (const float*)A, (const float*)B, d_out, d_in, r, base_sq, (float)(2.0 * d->s),
                         (float)((double)d->s * d->s), c, terms, mag ? mag->m : nullptr, mag ? mag->eps : 0.f,
-                        mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr, n.slices, n.part};
+                        mag ? mag->g : nullptr, mag ? mag->gm1 : nullptr, n.slices, n.part, n.row_blocks};
     DORA_HIP(launch_norm_f32(a, st));
     const size_t all = (size_t)n.slices * d_out;
     if (n.slices > 1)

@@ -479,34 +479,48 @@ hipError_t launch_one(const SgemmArgs* g, int n, const ColumnSum* sum, const Col
     return hipGetLastError();
 }
 
-// Norm: 16 rows per workgroup, its sixteen waves take 32 columns in turn.  V = B A of 16 x 32 stays in registers and meets W
-// there (U = W A^T, A A^T, B G and the row sums as four pieces of work in three launches: 1000 x 772, r 36 18 us, this one 9;
-// 2048 x 2048, r 128 60, 23; error against 64 bits 4.7e-8, 4.4e-8); the three sums of Eq. 2 of whole rows end in one workgroup, which finishes Eq. 5 and 6.  Where few rows leave most CUs
-// without one, the columns are cut into slices and the sums go to memory.
+// Norm: 16 or 32 rows per workgroup, its sixteen waves take 32 columns in turn.  V = B A of those stays in registers and meets W
+// there; the three sums of Eq. 2 of whole rows end in one workgroup, which finishes Eq. 5 and 6.  Where few rows leave CUs without
+// one, or a round of workgroups is badly filled, the columns are cut into slices and the sums go to memory.  Bound by the
+// matrix cores (8192 x 8192, r 384 at 87 TFLOP/s of 157) and, with 16 rows, by reading A from the L2 (72).  (U = W A^T, A A^T, B G
+// and the row sums as four pieces of work in three launches: 1000 x 772, r 36 17 us, this one 10; 2048 x 2048, r 128 61, 22; 8192 x
+// 8192, r 384 646, 595; 27648 x 5120, r 384 1352, 1323; error against 64 bits 4.7e-8, 4.4e-8.)
 constexpr int NORM_WAVES = 16;
+template <int RB>   // blocks of 16 rows
 __global__ __launch_bounds__(64 * NORM_WAVES) void norm_f32_kernel(NormF32Args p)
 {
-    constexpr int DEPTH = 4;
-    __shared__ float red[NORM_WAVES][3][16];
+    constexpr int DEPTH = 4 / RB, ROWS = 16 * RB;
+    __shared__ float red[NORM_WAVES][3][ROWS];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
-    const int slice = blockIdx.x % p.slices, m0 = blockIdx.x / p.slices * 16, row = m0 + l16 < p.d_out ? m0 + l16 : p.d_out - 1;
+    const int slice = blockIdx.x % p.slices, m0 = blockIdx.x / p.slices * ROWS;
     const int d_in = p.d_in, r = p.r, groups = (r + 15) / 16;
-    float sum[3] = {0.f, 0.f, 0.f};
-    for (int n0 = (slice * NORM_WAVES + wave) * 32; n0 < d_in; n0 += p.slices * NORM_WAVES * 32) {
-        float4 w[2];
+    int row[RB];
+    float sum[RB][3];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + j * 16 + lq * 4;
-            w[j] = *reinterpret_cast<const float4*>(p.w + (int64_t)row * d_in + (n < d_in ? n : d_in - 4));
-        }
-        f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+    for (int i = 0; i < RB; ++i) {
+        const int m = m0 + i * 16 + l16;
+        row[i] = m < p.d_out ? m : p.d_out - 1;
+        sum[i][0] = sum[i][1] = sum[i][2] = 0.f;
+    }
+    for (int n0 = (wave * p.slices + slice) * 32; n0 < d_in; n0 += p.slices * NORM_WAVES * 32) {
+        float4 w[RB][2];
+        f32x4_t acc[RB][2];
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int n = n0 + j * 16 + lq * 4;
+                w[i][j] = *reinterpret_cast<const float4*>(p.w + (int64_t)row[i] * d_in + (n < d_in ? n : d_in - 4));
+                acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
         for (int g = 0; g < groups; g += DEPTH) {
-            float4 b[DEPTH], a[DEPTH][2];
+            float4 b[DEPTH][RB], a[DEPTH][2];
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {          // groups past the end bring zeros
                 const int k = (g + d) * 16 + lq * 4;
-                b[d] = load_k4<true>(p.b, r, p.d_out, r, row, k);
+#pragma unroll
+                for (int i = 0; i < RB; ++i) b[d][i] = load_k4<true>(p.b, r, p.d_out, r, row[i], k);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) a[d][j] = load_k4<false>(p.a, d_in, d_in, r, n0 + j * 16 + l16, k);
             }
@@ -516,49 +530,56 @@ __global__ __launch_bounds__(64 * NORM_WAVES) void norm_f32_kernel(NormF32Args p
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j) acc[j] = mfma_f32(get(a[d][j], e), get(b[d], e), acc[j]);
+                        for (int i = 0; i < RB; ++i)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32(get(a[d][j], e), get(b[d][i], e), acc[i][j]);
         }
-        // lane: columns 4 lq .. +3 of block j, row l16
+        // lane: columns 4 lq .. +3 of block j, row l16 of block i
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            if (n0 + j * 16 + lq * 4 < d_in) {
-                float t[3] = {0.f, 0.f, 0.f};
+            if (n0 + j * 16 + lq * 4 < d_in)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float wv = get(w[j], e), v = acc[j][e];
-                    t[0] = fmaf(wv, wv, t[0]); t[1] = fmaf(wv, v, t[1]); t[2] = fmaf(v, v, t[2]);
+                for (int i = 0; i < RB; ++i) {
+                    float t[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float wv = get(w[i][j], e), v = acc[i][j][e];
+                        t[0] = fmaf(wv, wv, t[0]); t[1] = fmaf(wv, v, t[1]); t[2] = fmaf(v, v, t[2]);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) sum[i][k] += t[k];
                 }
-#pragma unroll
-                for (int k = 0; k < 3; ++k) sum[k] += t[k];
-            }
     }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        sum[k] += __shfl_xor(sum[k], 16);
-        sum[k] += __shfl_xor(sum[k], 32);
-        if (lq == 0) red[wave][k][l16] = sum[k];
-    }
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            sum[i][k] += __shfl_xor(sum[i][k], 16);
+            sum[i][k] += __shfl_xor(sum[i][k], 32);
+            if (lq == 0) red[wave][k][i * 16 + l16] = sum[i][k];
+        }
     __syncthreads();
     const int j = m0 + (int)threadIdx.x;
-    if (threadIdx.x >= 16 || j >= p.d_out) return;
+    if (threadIdx.x >= ROWS || j >= p.d_out) return;
+    float all[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         double v = 0.;
 #pragma unroll
         for (int i = 0; i < NORM_WAVES; ++i) v += red[i][k][threadIdx.x];
-        sum[k] = (float)v;
+        all[k] = (float)v;
     }
     if (p.slices > 1) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) p.part[((int64_t)k * p.slices + slice) * p.d_out + j] = sum[k];
+        for (int k = 0; k < 3; ++k) p.part[((int64_t)k * p.slices + slice) * p.d_out + j] = all[k];
         return;
     }
-    if (p.base_in) sum[0] = p.base_in[j];
+    if (p.base_in) all[0] = p.base_in[j];
     if (p.terms)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) p.terms[(int64_t)k * p.d_out + j] = sum[k];
+        for (int k = 0; k < 3; ++k) p.terms[(int64_t)k * p.d_out + j] = all[k];
     if (!p.c) return;
-    const float cj = __fsqrt_rn(radicand(sum[0], sum[1], sum[2], p.two_s, p.s2));
+    const float cj = __fsqrt_rn(radicand(all[0], all[1], all[2], p.two_s, p.s2));
     p.c[j] = cj;
     if (p.m) {
         const float cc = (cj < p.eps) ? p.eps : cj, mj = p.m[j];
@@ -589,7 +610,8 @@ hipError_t launch_f32(const SgemmArgs* g, int n, const ColumnSum* sum, const Col
 hipError_t launch_norm_f32(const NormF32Args& a, hipStream_t stream)
 {
     TraceScope ts(DORA_K_NORM_CROSS, stream);
-    norm_f32_kernel<<<dim3((unsigned)((a.d_out + 15) / 16 * a.slices)), dim3(64 * NORM_WAVES), 0, stream>>>(a);
+    if (a.row_blocks == 2) norm_f32_kernel<2><<<dim3((unsigned)((a.d_out + 31) / 32 * a.slices)), dim3(64 * NORM_WAVES), 0, stream>>>(a);
+    else norm_f32_kernel<1><<<dim3((unsigned)((a.d_out + 15) / 16 * a.slices)), dim3(64 * NORM_WAVES), 0, stream>>>(a);
     return hipGetLastError();
 }
 

@@ -13,10 +13,10 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [  # d_out, d_in, r, tokens
     (1000, 772, 36, 1500),      # 384 and 312 tiles of 64 x 64 become 752 and 611 of 32 x 64
-    (68, 4100, 300, 37),        # the same for dA, both operands K-strided; norm of 45 steps in slices
+    (68, 4100, 300, 37),        # the same for dA, both operands K-strided; norm in 17 slices
     (4100, 68, 300, 101),       # and for dB, whose rows are scaled
     (2052, 1028, 20, 1030),     # 64 x 64
-    (20, 2052, 132, 3),         # two row blocks, norm in five slices
+    (20, 2052, 132, 3),         # two row blocks, norm in 17 slices
 ]
 
 
@@ -103,3 +103,34 @@ def test_long_sums_beside_tiles(d_out, d_in, r, tokens, launches):
     assert counts["gemm_dx"] == launches
     for k in ("dx", "dA", "dB", "dm"):
         G.assert_close(k, G.to_f64(got[k]), b[k], G.TOL["f32"]["tensor"])
+
+
+@pytest.mark.parametrize("d_out,d_in,r", [
+    (36, 20, 4),                # three blocks of 16 rows or two of 32, one group of columns
+    (1000, 772, 36),            # one slice, the last group of four columns
+    (260, 4100, 132),           # slices, the last of them with fewer groups
+    (4100, 260, 68),            # 32 rows, the last block of four
+    (5124, 1028, 164),          # 32 rows in slices
+    (20, 504, 860),             # more slices than row blocks, ranks far past the columns of a wave
+])
+def test_norm_in_row_blocks_and_slices(d_out, d_in, r):
+    cfg = I.stress(I.DoraConfig(f"f32_norm_{d_out}_{d_in}_{r}", d_out, d_in, r, 1, "f32", 16.0, 1e-3, seed_offset=9700))
+    mod = G.Module(cfg)
+    ref = O.dense_row_norm(mod.f64("W"), mod.f64("A"), mod.f64("B"), float(mod.inp["s"]))
+    c = G.to_f64(mod.norm())
+    # a product's own sum over r, then at most 9 groups, 8 lanes and 32 slices one after the other at 2^-24 each, half for the root
+    G.assert_norm_close(c, ref, 3e-6)
+    # the terms, the cached base term and a row that is not finite beside its neighbours
+    terms, base, again = G.empty_f32(3, d_out), G.empty_f32(d_out), G.empty_f32(d_out)
+    ws = G.workspace(mod.desc, D.PHASE_NORM)
+    D.dora_norm_terms(mod.desc, mod.W, mod.A, mod.B, terms, None, ws)
+    D.dora_norm_assemble(mod.desc, terms, again)
+    np.testing.assert_array_equal(G.to_f64(again), c)
+    D.dora_base_sq(mod.desc, mod.W, base)
+    D.dora_norm_cached(mod.desc, base, mod.W, mod.A, mod.B, again, ws)
+    G.assert_norm_close(G.to_f64(again), ref, 3e-6)
+    row = d_out // 2 + 1
+    mod.W[row, 1] = float("nan")
+    bad = G.to_f64(mod.norm())
+    assert np.isnan(bad[row])
+    np.testing.assert_array_equal(np.delete(bad, row), np.delete(c, row))
