@@ -1049,7 +1049,20 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
     }
     DORA_HIP(launch_waiting(waiting, s));
 
-    if (dt == DORA_F32 && !dropout)
+    // Launches that share the outputs' writes with the reads of dy, W and A are left to callers who keep those apart: dx, dx_lora
+    // or a gradient may lie over dy (or a weight that is not needed again) where each is written after its last reader.
+    struct Span { const void* p; size_t bytes; };
+    const size_t e = esize(dt), grad_dA = (size_t)r * d_in * 4, grad_dB = (size_t)d_out * r * 4;
+    const Span in_dy{dy, (size_t)T * d_out * e}, in_W{W, (size_t)d_out * d_in * e}, in_A{A, (size_t)r * d_in * e};
+    const Span out_dx{dx, (size_t)T * d_in * e}, out_dxl{dx_lora, (size_t)T * d_in * e}, out_dA{dA, grad_dA}, out_dB{dB, grad_dB},
+        out_dm{dm, (size_t)d_out * 4};
+    auto over = [](const Span& o, const Span& i) {
+        const uintptr_t a = (uintptr_t)o.p, b = (uintptr_t)i.p;
+        return a && b && a < b + i.bytes && b < a + o.bytes;
+    };
+    auto over_inputs = [&](const Span& o) { return over(o, in_dy) || over(o, in_W) || over(o, in_A); };
+    const bool weights_apart = !over_inputs(out_dA) && !over_inputs(out_dB);
+    if (dt == DORA_F32 && !dropout && weights_apart && !over_inputs(out_dx) && !over_inputs(out_dm))
         return backward_f32(desc, dy, xa, W, A, B, mag_in_compose ? RowScale{c, m, eff_eps(desc)} : RowScale{p.g, nullptr, 0.f}, c, h,
                             inner, dx, dA, dB, dm, p.dm_partial, p.g, p.dh, s);
 
@@ -1086,8 +1099,8 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
         if (dx_sum) in[n++] = bf16_args(dt_of(dt), true, false, T, d_in, sx, 2, 1.f, dx_sum, d_in, false, 0);
         if (dA) wg[nw++] = bf16_args(dt_of(dt), false, false, r, d_in, &sa, 1, 1.f, dA, d_in, true, 0);
         if (dB) wg[nw++] = bf16_args(dt_of(dt), false, false, d_out, r, &sb, 1, desc->s, dB, r, true, 0);
-        paired = n == 2 && gemm_bf16_pairs(in[0], in[1]);
-        if ((n == 1 || paired) && gemm_bf16_grads_together(in, n, wg, nw)) {
+        paired = n == 2 && !over_inputs(out_dxl) && gemm_bf16_pairs(in[0], in[1]);
+        if ((n == 1 || paired) && weights_apart && gemm_bf16_grads_together(in, n, wg, nw)) {
             DORA_HIP(launch_gemm_bf16_grads(in, n, wg, nw, DORA_K_GEMM_DX, s));
             return DORA_OK;
         }
