@@ -133,7 +133,7 @@ def test_no_mfma_reads_a_fragment_before_its_wait(tmp_path):
     assert proc.returncode == 0, proc.stdout[-2000:]
     kernels, current = {}, None
     for line in asm.read_text().split("\n"):
-        m = re.match(r"^(_ZN\S*gemm_bf16_kernel\S*):", line)
+        m = re.match(r"^(_ZN\S*(?:gemm_bf16_kernel|gradients_kernel)\S*):", line)
         if m:
             current = m.group(1)
             kernels[current] = []
@@ -143,11 +143,18 @@ def test_no_mfma_reads_a_fragment_before_its_wait(tmp_path):
                 current = None
             else:
                 kernels[current].append(line)
-    assert len(kernels) >= 20, "expected every GEMM instantiation in the assembly"
+    assert sum("gemm_bf16_kernel" in k for k in kernels) >= 20, "expected every GEMM instantiation in the assembly"
+    assert sum("gradients_kernel" in k for k in kernels) == 6, "three pairs of tiles in each of the two 16-bit types"
+    assert all(sum("v_mfma" in l for l in ls) >= 16 for ls in kernels.values())
     assert sum("v_mfma" in l for ls in kernels.values() for l in ls) > 500
     bad = {k: h for k, h in ((k, lint_kernel(v)) for k, v in kernels.items()) if h}
     assert not bad, "MFMA issued before the LDS read feeding it is covered by a wait: %r" % (
         {k[-60:]: h[:3] for k, h in bad.items()},)
+    # no 128 x 128 tile spills; the 256 x 256 one keeps up to six registers in scratch, by itself and beside the weight gradients
+    scratch = dict(re.findall(r"^(_ZN\S*(?:gemm_bf16_kernel|gradients_kernel)\S*):.*?; ScratchSize: (\d+)", asm.read_text(),
+                              flags=re.S | re.M))
+    assert scratch.keys() == kernels.keys()
+    assert not {k[-60:]: v for k, v in scratch.items() if int(v) > (24 if "TileILi256E" in k else 0)}
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
