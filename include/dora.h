@@ -23,7 +23,10 @@
  *     keeps no state between calls, enqueues everything on `stream` (a
  *     hipStream_t passed as void*; NULL is the default stream) and returns
  *     without synchronising.  Results are deterministic run to run (no
- *     floating-point atomics anywhere).  (The measurement hooks declared in
+ *     floating-point atomics anywhere).  Which of a backward's outputs are asked for
+ *     may change the last bits of the others (fp32: the order in which partial sums of
+ *     dx, dA and dB are added; 16-bit dropout: the tiles of dx and dx_lora), never those
+ *     of dm.  (The measurement hooks declared in
  *     dora_measure.h are the one exception: they keep process-global timing
  *     records and are not part of the method.)
  *   - Errors are returned, never thrown; on error nothing has been enqueued

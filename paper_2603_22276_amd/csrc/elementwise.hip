@@ -169,30 +169,46 @@ __global__ void gram_reduce_kernel(const float* __restrict__ p, int ksplit, int 
     Glo[i] = (bf16_t)(E::pack2(rem, 0.f) & 0xffffu);
 }
 
-// Second stage of dm's column sum: dm[j] = (sum over slabs, in slab order) / max(c[j], eps).  32 columns per workgroup, H
-// threads per column with a contiguous range of slabs each, U loads in flight (32 and 8 in a launch of its own; 8 and 16 where
-// the workgroup has 256 threads).
-constexpr int DMF_W = 32;
-template <int H, int U>
+// Second stage of dm's column sum: dm[j] = (sum over slabs, in slab order) / max(c[j], eps).  32 columns per workgroup, H threads
+// per column; the slabs go in 32 contiguous ranges whose sums are added in order, 32 / H of them to a thread, so that dm does not
+// depend on which launch forms it.
+constexpr int DMF_W = 32, DMF_RANGES = 32;
+template <int H>
 __device__ __forceinline__ void dm_final(const DmFinalArgs& p, int block)
 {
-    __shared__ float red[H][DMF_W];
+    constexpr int PER = DMF_RANGES / H, U = PER == 1 ? 8 : 4;      // loads of a range in flight
+    __shared__ float red[DMF_RANGES][DMF_W];
     const int x = threadIdx.x % DMF_W, y = threadIdx.x / DMF_W, j = block * DMF_W + x;
-    float acc = 0.f;
-    if (j < p.d_out) {
-        const int per = (p.slabs + H - 1) / H, z0 = y * per, z1 = z0 + per < p.slabs ? z0 + per : p.slabs;
-        if (z0 < z1) acc = sum_partials<U>(p.partial + (int64_t)z0 * p.d_out + j, z1 - z0, p.d_out);
-    }
-    red[y][x] = acc;
+    const int length = (p.slabs + DMF_RANGES - 1) / DMF_RANGES;
+    float acc[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) acc[q] = 0.f;
+    if (j < p.d_out)
+        for (int k = 0; k < length; k += U) {
+            float v[PER][U];
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int z = (y * PER + q) * length + k + u;
+                    v[q][u] = p.partial[(int64_t)(z < p.slabs ? z : p.slabs - 1) * p.d_out + j];
+                }
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u) acc[q] += k + u < length && (y * PER + q) * length + k + u < p.slabs ? v[q][u] : 0.f;
+        }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) red[y * PER + q][x] = acc[q];
     __syncthreads();
     if (y == 0 && j < p.d_out) {
         float v = red[0][x];
-        for (int i = 1; i < H; ++i) v += red[i][x];
+        for (int i = 1; i < DMF_RANGES; ++i) v += red[i][x];
         const float cj = p.c[j];
         p.dm[j] = v / ((cj < p.eps) ? p.eps : cj);
     }
 }
-__global__ __launch_bounds__(DMF_W * 32) void dm_final_kernel(DmFinalArgs p) { dm_final<32, 8>(p, blockIdx.x); }
+__global__ __launch_bounds__(DMF_W * 32) void dm_final_kernel(DmFinalArgs p) { dm_final<32>(p, blockIdx.x); }
 
 struct Riders {
     NormFinalArgs norm;
@@ -215,7 +231,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     int block = blockIdx.x;
     if (block < riders.norm_blocks) return norm_final(riders.norm, block);
     block -= riders.norm_blocks;
-    if (block < riders.dm_blocks) return dm_final<8, 16>(riders.dm, block);
+    if (block < riders.dm_blocks) return dm_final<8>(riders.dm, block);
     block -= riders.dm_blocks;
     const int64_t i = ((int64_t)block * blockDim.x + threadIdx.x) * N;
     if (i >= n) return;

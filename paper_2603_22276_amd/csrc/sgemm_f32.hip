@@ -303,63 +303,77 @@ __device__ __forceinline__ void tile_product(const SgemmArgs& p, int wg, float* 
     }
 }
 
-// First stage of dm's column sum: 256 columns of COLUMN_SUM_ROWS tokens, a float4 per lane, the waves take rows in turn.
+// First stage of dm's column sum: 256 columns of COLUMN_SUM_ROWS tokens, a float4 per lane.  Sixteen sums take rows in turn and are
+// added in order, 16 / WK of them to a wave, so that dm does not depend on how many waves the launch has.
+constexpr int SUMS = 16;
 template <int WK>
 __device__ __forceinline__ void column_sum(const ColumnSum& p, int wg, float* red)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col_blocks = (p.d_out + 255) / 256, slab = wg / col_blocks, col = (wg % col_blocks) * 256 + lane * 4;
     const int64_t row0 = (int64_t)slab * COLUMN_SUM_ROWS;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (col < p.d_out) {
-        constexpr int PER = COLUMN_SUM_ROWS / WK, U = PER < 4 ? PER : 4;
-        for (int b = 0; b < PER; b += U) {
+    for (int q = wave; q < SUMS; q += WK) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (col < p.d_out) {
+            constexpr int U = COLUMN_SUM_ROWS / SUMS;
             float4 d[U], n[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t row = row0 + wave + (b + u) * WK, at = (row < p.tokens ? row : p.tokens - 1) * p.d_out + col;
+                const int64_t row = row0 + q + u * SUMS, at = (row < p.tokens ? row : p.tokens - 1) * p.d_out + col;
                 d[u] = *reinterpret_cast<const float4*>(p.dy + at);
                 n[u] = *reinterpret_cast<const float4*>(p.inner + at);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (row0 + wave + (b + u) * WK < p.tokens) {
+                if (row0 + q + u * SUMS < p.tokens) {
                     acc.x = fmaf(d[u].x, n[u].x, acc.x); acc.y = fmaf(d[u].y, n[u].y, acc.y);
                     acc.z = fmaf(d[u].z, n[u].z, acc.z); acc.w = fmaf(d[u].w, n[u].w, acc.w);
                 }
         }
+        *reinterpret_cast<float4*>(red + q * 256 + lane * 4) = acc;
     }
-    *reinterpret_cast<float4*>(red + wave * 256 + lane * 4) = acc;
     __syncthreads();
     const int j = (wg % col_blocks) * 256 + (int)threadIdx.x;
     if (threadIdx.x < 256 && j < p.d_out) {
         float v = 0.f;
 #pragma unroll
-        for (int w = 0; w < WK; ++w) v += red[w * 256 + threadIdx.x];
+        for (int w = 0; w < SUMS; ++w) v += red[w * 256 + threadIdx.x];
         p.partial[(int64_t)slab * p.d_out + j] = v;
     }
 }
 
-// Second stage: 64 columns per workgroup, the waves take slabs in turn.
+// Second stage: 64 columns per workgroup, sixteen sums take slabs in turn.
 template <int WK>
 __device__ __forceinline__ void column_final(const ColumnFinal& p, int wg, float* red)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = wg * 64 + lane;
-    float v = 0.f;
+    constexpr int PER = SUMS / WK, U = PER == 1 ? 4 : 2;
+    float v[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) v[q] = 0.f;
     if (j < p.d_out)
-        for (int z = wave; z < p.slabs; z += 4 * WK) {
-            float e[4];
+        for (int z = 0; z < p.slabs; z += U * SUMS) {
+            float e[PER][U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) e[u] = p.partial[(int64_t)(z + u * WK < p.slabs ? z + u * WK : p.slabs - 1) * p.d_out + j];
+            for (int q = 0; q < PER; ++q)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v += z + u * WK < p.slabs ? e[u] : 0.f;
+                for (int u = 0; u < U; ++u) {
+                    const int at = z + u * SUMS + wave * PER + q;
+                    e[q][u] = p.partial[(int64_t)(at < p.slabs ? at : p.slabs - 1) * p.d_out + j];
+                }
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[q] += z + u * SUMS + wave * PER + q < p.slabs ? e[q][u] : 0.f;
         }
-    red[wave * 64 + lane] = v;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) red[(wave * PER + q) * 64 + lane] = v[q];
     __syncthreads();
     if (wave == 0 && j < p.d_out) {
-        for (int w = 1; w < WK; ++w) v += red[w * 64 + lane];
+        float sum = red[lane];
+        for (int w = 1; w < SUMS; ++w) sum += red[w * 64 + lane];
         const float cc = (p.c[j] < p.eps) ? p.eps : p.c[j];
-        p.dm[j] = v / cc;
+        p.dm[j] = sum / cc;
     }
 }
 

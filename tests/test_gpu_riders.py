@@ -6,9 +6,10 @@ import torch
 from paper_2603_22276_amd import binding as D
 
 import gpu_util as G
-from test_gpu_rounds import Inputs, close
+from test_gpu_rounds import DT, Inputs, close
 
 pytestmark = pytest.mark.gpu
+DT["f32"] = torch.float32
 
 SHAPES = [  # d_out, d_in, r, tokens
     (1000, 4104, 72, 77),       # h and dh split, the last block of 32 rows not full
@@ -62,3 +63,27 @@ def test_norm_formed_on_the_way(dtype, d_out, d_in, r, tokens):
     alone = G.empty_f32(d_out)
     D.dora_backward(q.desc, q.dy, q.xl, q.W, q.A, q.B, q.m, None, None, None, None, None, None, alone, q.ws(D.PHASE_BACKWARD_RECOMPUTE))
     close("dm alone", alone, ((q.dy.double() * inner).sum(0) / c.double(), slice(None)), dtype)
+
+
+@pytest.mark.parametrize("d_out,d_in,r,tokens,dtype", [
+    (1000, 4104, 72, 77, "bf16"),     # dm's second stage in the reduce of dh: as many slabs as tokens / 16
+    (2056, 3000, 24, 16000, "f16"),   # the same, of several slabs to a range
+    (4104, 72, 8, 200, "bf16"),
+    (136, 136, 16, 300, "f32"),       # fp32 launches of sixteen waves, and of four where dm is alone
+    (1000, 772, 36, 1500, "f32"),     # of four beside tiles
+    (516, 260, 12, 12000, "f32"),     # 188 slabs
+])
+def test_dm_does_not_depend_on_what_else_is_wanted(d_out, d_in, r, tokens, dtype):
+    q = Inputs(d_out, d_in, r, tokens, dtype)
+    q.h.normal_(), q.inner.normal_()
+    ws = q.ws(D.PHASE_BACKWARD)
+    got = []
+    for want in (("dx", "dA", "dB"), ("dB",), ()):
+        dm = G.empty_f32(d_out)
+        out = {"dx": q.dx, "dA": G.empty_f32(r, d_in), "dB": G.empty_f32(d_out, r)}
+        out = [v if k in want else None for k, v in out.items()]
+        D.dora_backward(q.desc, q.dy, q.xl, q.W, q.A, q.B, q.m, q.c, q.h, q.inner, *out, dm, ws)
+        got.append(dm)
+    same("dm", got[0], got[1])
+    same("dm", got[0], got[2])
+    close("dm", got[0], ((q.dy.double() * q.inner.double()).sum(0) / q.c.double(), slice(None)), dtype)
