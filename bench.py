@@ -70,6 +70,25 @@ def kernel_work(cfg, inner_saved=True):
     }
 
 
+def shared_launches(launches, work):
+    """`work` (kernel -> (flops, bytes)) for the launches that were made: one that carries several contractions is priced with the
+    work of all of them.  launches: kernel -> launches of one module's forward or backward."""
+    w = dict(work)
+
+    def carries(name, *others):
+        w[name] = (w[name][0] + sum(w[o][0] for o in others), w[name][1] + sum(w[o][1] for o in others))
+
+    if launches["gemm_dA"] > 0 and launches["gemm_dB"] == 0:
+        carries("gemm_dA", "gemm_dB")
+    if launches["gemm_dx"] > 0 and launches["gemm_dA"] == 0 and launches["gemm_dB"] == 0:   # the last launch takes all gradients
+        carries("gemm_dx", "gemm_dA", "gemm_dB")
+    if launches["norm_cross_WAt"] > 0 and launches["gram_AAt"] == 0 and launches["ba_sq_BGB"] > 0:   # the Gram tiles ride in the cross term's launch
+        carries("norm_cross_WAt", "gram_AAt")
+    if launches["gemm_base_xWt"] > 0 and launches["gemm_h_xAt"] == 0:   # small fp32 module: h in the launch of the base product
+        carries("gemm_base_xWt", "gemm_h_xAt")
+    return w
+
+
 def kernel_sources_sha256():
     """Hash of the kernel sources: counter summaries under profiles/ record the one they were taken at."""
     h = hashlib.sha256()
@@ -249,14 +268,7 @@ def kernel_table(D, torch, wl, reps, dominant_live):
         return {n: D.dora_trace_get(k) for k, n in enumerate(names)}
 
     def price(got, work):
-        w = dict(work)
-        # launches that carry two contractions at once are priced with the work of both
-        if got["gemm_dA"][1] > 0 and got["gemm_dB"][1] == 0:
-            w["gemm_dA"] = (w["gemm_dA"][0] + w["gemm_dB"][0], w["gemm_dA"][1] + w["gemm_dB"][1])
-        if got["norm_cross_WAt"][1] > 0 and got["gram_AAt"][1] == 0 and got["ba_sq_BGB"][1] > 0:   # the Gram tiles ride in the cross term's launch
-            w["norm_cross_WAt"] = (w["norm_cross_WAt"][0] + w["gram_AAt"][0], w["norm_cross_WAt"][1] + w["gram_AAt"][1])
-        if got["gemm_base_xWt"][1] > 0 and got["gemm_h_xAt"][1] == 0:   # small fp32 module: h in the launch of the base product
-            w["gemm_base_xWt"] = (w["gemm_base_xWt"][0] + w["gemm_h_xAt"][0], w["gemm_base_xWt"][1] + w["gemm_h_xAt"][1])
+        w = shared_launches({n: cnt for n, (_, cnt) in got.items()}, work)
         for n, (_, cnt) in got.items():
             if cnt and n in w:
                 tot[n]["flops"] += w[n][0] * cnt
