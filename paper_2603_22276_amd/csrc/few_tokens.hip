@@ -25,7 +25,7 @@ __device__ __forceinline__ void load_1k(char* lds, __amdgpu_buffer_rsrc_t rs, ui
 }
 
 // TB: blocks of 16 tokens; MR: blocks of 16 weight rows; DEPTH: ring slots of a wave
-template <int TB, int MR, int DEPTH, bool FINAL, int DT>
+template <int TB, int MR, int DEPTH, bool FINAL, int DT, bool LOW_RANK = false>
 __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
 {
     typedef Elem16<DT> E;
@@ -38,8 +38,12 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     constexpr int RED_LD = ROWS + 4;
     constexpr int RING_BYTES = WAVES * DEPTH * SLOT_BYTES, RED_BYTES = WAVES * TOK * RED_LD * 4;
     constexpr int LDS_BYTES = RING_BYTES > RED_BYTES ? RING_BYTES : RED_BYTES;
-    // one block of tokens and of rows: h comes through LDS, H_RANKS of it at a time
-    constexpr bool STAGE_H = FINAL && TB == 1 && MR == 1;
+    // One block of tokens and of rows: h comes through LDS, H_RANKS of it at a time.  Up to one k-step of it to a wave (LOW_RANK) the
+    // waves take their own as they are: six shapes of 512 x 512 to 8192 x 2048, forward of 1 to 16 tokens, r 8 1.07 times faster than
+    // through LDS, r 64 1.05, r 128 1.00 to 1.04, r 256 1.05 to 1.10.  (512 x 512, r 8, 1 token 6.6 us through LDS, whose loads are
+    // issued for all slices by every wave, 5.8 this way; 4096 x 4096, r 384 in LDS 14.1, from memory 20.3, weights from HBM.)
+    constexpr bool STAGE_H = FINAL && TB == 1 && MR == 1 && !LOW_RANK, DIRECT_H = FINAL && LOW_RANK;
+    static_assert(!LOW_RANK || (TB == 1 && MR == 1), "a wave's own k-step of one block");
     constexpr int H_RANKS = 512, H_BYTES = STAGE_H ? 16 * H_RANKS * 2 : 0;
     static_assert(LDS_BYTES + H_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
     static_assert((DEPTH - 1) * LPS <= 63, "vmcnt is a 6-bit counter");
@@ -112,6 +116,7 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     auto load_h = [&](int t, int l, float4 (&v)[SLICES][2]) {
 #pragma unroll
         for (int z = 0; z < SLICES; ++z) {
+            if (DIRECT_H && z >= p.h_slices) continue;
             const int zz = z < p.h_slices ? z : p.h_slices - 1;
             const float4* hp = reinterpret_cast<const float4*>(p.h_part + ((int64_t)zz * T + t) * p.r + l);
             v[z][0] = hp[0]; v[z][1] = hp[1];
@@ -138,6 +143,7 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     };
     constexpr int PRE = H_RANKS / 32 / WAVES;          // k-steps of a wave in H_RANKS
     uint4 bpre[STAGE_H ? PRE : 1];
+    const bool own_step = wave * 32 < p.r;             // DIRECT_H: this wave's
     // item of h: eight ranks of one token; `per` of them to a token, ranks past r among them as far as a k-step reaches
     const int per0 = ((p.r < H_RANKS ? p.r : H_RANKS) + 31) / 32 * 4;
     if constexpr (FINAL) {
@@ -151,6 +157,11 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
             load_h(t < T ? t : T - 1, l < p.r ? l : 0, hs[0]);
 #pragma unroll
             for (int q = 0; q < PRE; ++q) bpre[q] = load_b(0, (wave + q * WAVES) * 32 + lq * 8);
+        }
+        if constexpr (DIRECT_H) {
+            const int l = wave * 32 + lq * 8;
+            if (own_step && l16 < T) load_h(l16, l < p.r ? l : 0, hs[0]);
+            if (own_step) bpre[0] = load_b(0, l);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -190,6 +201,14 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
             }
             __builtin_amdgcn_s_barrier();              // read by all: the next ranks, or the ring, may follow
             __builtin_amdgcn_sched_barrier(0);
+        }
+    } else if constexpr (DIRECT_H) {
+        const int l = wave * 32 + lq * 8;
+        if (own_step) {
+            uint4 o = sum_h(hs[0]);                    // (tokens past T: whatever is there reaches only columns that are not stored)
+            if (l >= p.r) o = make_uint4(0u, 0u, 0u, 0u);
+            if (p.h_out && blockIdx.x == 0 && l < p.r && l16 < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)l16 * p.r + l) = o;
+            accl[0][0] = E::mfma16(__builtin_bit_cast(bf16x8_t, bpre[0]), __builtin_bit_cast(bf16x8_t, o), accl[0][0]);
         }
     } else if constexpr (FINAL) {
         // low-rank part while the first weight rows are on their way: h and B straight from memory, the waves share the
@@ -300,7 +319,9 @@ hipError_t launch_y(const FewTokensArgs& a, hipStream_t st)
     const bool narrow = a.N <= 4096, wide = a.N > 8192;
 #define DORA_FEW(TB, MR, DEPTH) \
     few_tokens_kernel<TB, MR, DEPTH, true, DT><<<dim3((unsigned)((a.N + MR * 16 - 1) / (MR * 16))), dim3(64 * WAVES), 0, st>>>(a)
-    if (a.T <= 16) { if (wide) DORA_FEW(1, 4, 2); else DORA_FEW(1, 1, 4); }
+    if (a.T <= 16 && !wide && a.r <= 32 * WAVES)
+        few_tokens_kernel<1, 1, 4, true, DT, true><<<dim3((unsigned)((a.N + 15) / 16)), dim3(64 * WAVES), 0, st>>>(a);
+    else if (a.T <= 16) { if (wide) DORA_FEW(1, 4, 2); else DORA_FEW(1, 1, 4); }
     else if (a.T <= 32) { if (wide) DORA_FEW(2, 4, 2); else DORA_FEW(2, 1, 3); }
     else if (wide) DORA_FEW(4, 4, 2);
     else if (narrow) DORA_FEW(4, 1, 2);

@@ -1,5 +1,6 @@
 """Few tokens, one block of them and of weight rows: h comes through LDS, 512 ranks at a time, and B ahead of the weights.  One
-item of h per thread and several, ranks that end at, inside and past a piece, tokens that end inside the block, slices 1 to 8."""
+item of h per thread and several, ranks that end at, inside and past a piece, tokens that end inside the block, slices 1 to 8.
+Ranks up to 256: every wave takes its own 32 of them."""
 import numpy as np
 import pytest
 
@@ -24,3 +25,19 @@ def test_h_through_lds(dtype, d_out, d_in, r, tokens):
     out = mod.forward(fused=True)
     for k in ("y", "h", "inner"):
         G.assert_close(k, G.to_f64(out[k]), f[k], tol)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d_out,d_in,r,tokens", [(72, 4104, 8, 1), (264, 520, 40, 16), (8192, 72, 32, 15), (136, 8200, 72, 3),
+                                                 (520, 2056, 256, 16), (1032, 264, 248, 1), (136, 4104, 264, 5)])
+def test_each_wave_its_own_ranks(dtype, d_out, d_in, r, tokens):
+    cfg = I.stress(I.DoraConfig(f"few_own_{d_out}_{d_in}_{r}_{tokens}", d_out, d_in, r, tokens, dtype, 32.0, 1e-3, seed_offset=9450))
+    mod = G.Module(cfg)
+    tol = G.TOL[dtype]["tensor"]
+    f = O.forward(x=mod.f64("x"), W=mod.f64("W"), A=mod.f64("A"), B=mod.f64("B"), m=mod.inp["m"].astype(np.float64),
+                  s=float(mod.inp["s"]), eps=cfg.eps)
+    out = mod.forward(fused=True)
+    for k in ("y", "h", "inner"):
+        G.assert_close(k, G.to_f64(out[k]), f[k], tol)
+    # nothing saved: the same y
+    np.testing.assert_array_equal(G.to_f64(mod.forward(fused=True, save=False)["y"]), G.to_f64(out["y"]))

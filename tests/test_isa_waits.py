@@ -165,7 +165,7 @@ def test_no_mfma_of_the_few_token_kernel_reads_a_fragment_before_its_wait(tmp_pa
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert proc.returncode == 0, proc.stdout[-2000:]
     kernels = dict(re.findall(r"^(_ZN\S*few_tokens_kernel\S*):[^\n]*\n(.*?)^\.Lfunc_end", asm.read_text(), flags=re.S | re.M))
-    assert len(kernels) == 20, "ten tiles in each of the two 16-bit types"
+    assert len(kernels) == 22, "eleven tiles in each of the two 16-bit types"
     for name, text in kernels.items():
         lines = text.split("\n")
         assert any("v_mfma" in l for l in lines) and sum("ds_read_b128" in l for l in lines) >= 4, name
