@@ -151,8 +151,6 @@ struct GemmPair {
     int count0;  // workgroups of g[0]; the rest of the grid belongs to g[1]
 };
 
-// number of N tiles the ROWDOT epilogue will produce partials for (depends on the tile chosen)
-int gemm_bf16_tiles_n(const GemmArgs& a);
 hipError_t launch_gemm_bf16(const GemmArgs& a, int trace_id, hipStream_t stream);
 // two independent problems of the same kind (layouts, epilogue) in one launch; gemm_bf16_pairs: whether that is the cheaper way
 // (their tiles share rounds of workgroups, and a launch is saved)
@@ -328,7 +326,7 @@ hipError_t launch_rownorm_s0_16(const bf16_t* W, int dt, float* c, int d_out, in
 // fp32: the row norms of W alone (or their squares); terms ([3, d_out]: base_sq, 0, 0) and c may be nullptr
 hipError_t launch_rownorm_f32(const float* W, float* c, float* terms, int d_out, int d_in, bool squared, hipStream_t st);
 
-// out[i] = sum over z (in order) of partials[z * n + i], written in the storage dtype; out2 (may be nullptr)
+// out[i] = sum over z (in order) of partials[z * n + i], written in the 16-bit storage dtype; out2 (may be nullptr)
 // receives alpha2 times the same sum.  n a multiple of 8.  colscale != nullptr: rows of `cols` elements, out is
 // colscale[col] times the sum (+ colbias[col] where given).
 hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, int dtype, void* out, float alpha2, void* out2,

@@ -265,10 +265,10 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
         b.off = std::max(b.off, o.off);
     } else {
         norm_f32_shape(d->d_out, d->d_in, d->r, n.row_blocks, n.slices);
-        // (the scratch is that of U, G and B G, which decides what fits the static array)
+        // Scratch of d_out (2 r) + r^2 floats, three blocks, whatever the sums need of it (3 slices d_out): which shapes fit the static
+        // array does not change with the slices.
         n.part = b.take<float>((size_t)d->d_out * d->r);
-        b.take<float>((size_t)d->r * d->r);
-        b.take<float>((size_t)d->d_out * d->r);
+        b.off += up256((size_t)d->r * d->r * 4) + up256((size_t)d->d_out * d->r * 4);
     }
 }
 

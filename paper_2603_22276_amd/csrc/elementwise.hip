@@ -536,7 +536,7 @@ hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, in
 {
     if (n == 0) return waiting ? launch_waiting(*waiting, st) : hipSuccess;
     TraceScope ts(DORA_K_SPLITK_REDUCE, st);
-    const int per = dtype == DORA_F32 ? 4 : 8;
+    constexpr int per = 8;
     Riders r{};
     if (waiting && waiting->norm) { r.norm = waiting->norm_args; r.norm_blocks = (r.norm.d_out + NF_W - 1) / NF_W; }
     if (waiting && waiting->dm) { r.dm = waiting->dm_args; r.dm_blocks = (r.dm.d_out + DMF_W - 1) / DMF_W; }
@@ -545,12 +545,9 @@ hipError_t launch_splitk_reduce(const float* partials, int ksplit, int64_t n, in
     if (dtype == DORA_BF16)
         splitk_reduce_kernel<bf16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (bf16_t*)out, alpha2, (bf16_t*)out2, colscale,
                                                     (const bf16_t*)colbias, cols, r);
-    else if (dtype == DORA_F16)
+    else
         splitk_reduce_kernel<f16_t><<<grid, block, 0, st>>>(partials, ksplit, n, (f16_t*)out, alpha2, (f16_t*)out2, colscale,
                                                     (const f16_t*)colbias, cols, r);
-    else
-        splitk_reduce_kernel<float><<<grid, block, 0, st>>>(partials, ksplit, n, (float*)out, alpha2, (float*)out2, colscale,
-                                                    (const float*)colbias, cols, r);
     return hipGetLastError();
 }
 
@@ -609,7 +606,10 @@ static hipError_t compose_fwd_t(const void* base, const void* lora, const float*
         else if (CW == 128) DORA_LAUNCH_FWD_S(D, I, 128, 2);         \
         else DORA_LAUNCH_FWD_S(D, I, 64, 4);                         \
     } while (0)
-    if (!out) { DORA_LAUNCH_FWD(0, true); }
+    if (!out) {
+        if constexpr (sizeof(T) == 2) DORA_LAUNCH_FWD(0, true);
+        else return hipErrorInvalidValue;              // fp32 forms inner alone in the launch of lora
+    }
     else if (write_delta == 2) { if (inner) DORA_LAUNCH_FWD(3, true); else DORA_LAUNCH_FWD(3, false); }
     else if (write_delta) { if (inner) DORA_LAUNCH_FWD(2, true); else DORA_LAUNCH_FWD(2, false); }
     else { if (inner) DORA_LAUNCH_FWD(1, true); else DORA_LAUNCH_FWD(1, false); }

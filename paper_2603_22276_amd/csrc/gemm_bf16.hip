@@ -419,8 +419,6 @@ hipError_t launch_gemm_bf16_grads(const GemmArgs* dx, int n, const GemmArgs* w, 
     return hipErrorInvalidValue;
 }
 
-int gemm_bf16_tiles_n(const GemmArgs& a) { return (a.N + TileMed::BN - 1) / TileMed::BN; }
-
 hipError_t launch_gemm_bf16(const GemmArgs& a, int trace_id, hipStream_t stream)
 {
     if (a.M == 0 || a.N == 0) return hipSuccess;
