@@ -273,22 +273,29 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 }
 
 // Split of K for the products with a 16-bit output of at most 256 tiles of 128 x 128: h = x A^T and dh = s dz B over [tokens,
-// r], x W^T and dz W of short batches.  K is cut into slices (fp32 partials in the workspace, summed in slice order by a small
-// reduce launch), as many as are cheapest in tenths of a microsecond: for each K step of 64 of a slice 4 while every workgroup
-// has a CU to itself and 7.5 where two share one, 50 for the reduce launch, and the partials written and read at 4 TB/s.  At most
-// two workgroups per CU, 16 slices, and two K steps to a slice at least.  (Against at most four slices of 16 K steps: x A^T of
-// 512 tokens, K 4096, r 64 11.9 -> 7.2 us in 16 slices; of 1501 tokens, K 3000, r 72 16.3 -> 8.7 in eight; steps of 128 tokens
-// through 4096 x 14336 206 -> 173, through 14336 x 4096 165 -> 145.  Two workgroups to a CU pay where K is long: x A^T of 4096
-// tokens, r 384, in two slices and in five, K 4096 42 and 48 us, 14336 106 and 94, 27648 181 and 156; r 640, in one and three, K
-// 4096 49 and 55, 8192 93 and 84, 27648 286 and 207.)
-inline int product_ksplit(int dtype, int64_t M, int64_t N, int64_t K)
+// r], x W^T and dz W of short batches; ldb: row length of the N-side operand.  K is cut into slices (fp32 partials in the workspace,
+// summed in slice order by a small reduce launch), as many as are cheapest in twentieths of a microsecond: for each K step of 64 of
+// a slice 8 while every workgroup has a CU to itself and 15 where two share one, with a weight of 2 MB and more 9 and 17 (10 and 19
+// where its rows do not start at lines of 128 bytes), one more while K is whole (there three), when too few loads are in flight for
+// what comes from memory; 100 for the reduce launch, and the partials written and read at 3.4 TB/s.  At most two workgroups per CU,
+// 16 slices, and two K steps to a slice at least.  (Forward, us with weights from memory / left in a cache: 512 tokens, 4096 x 4096, r 64 with K whole 57 / 43, in
+// two slices 51 / 44; 256 tokens, 3000 x 2056 46 / 29, in three 36 / 32; 512 tokens, 4096 x 4104 72 / 58, in two 58 / 57.  247
+// forwards and backwards of 65 to 2048 tokens are within 0.9 % of the best number of slices with weights from memory and 0.5 % in a
+// cache, those with rows off the lines 1.4 % and 1.0 %.  x A^T of 512 tokens, K 4096, r 64 in one slice 11.9 us, 7.2 in 16; of 4096
+// tokens, r 384, in two slices and in five, K 4096 42 and 48 us, 14336 106 and 94, 27648 181 and 156.)
+// saves: what K whole would save beside, where the product could share a launch with others (a launch and a round of its own, 10 us:
+// step of 2048 x 2048, r 64, 512 tokens 75 us with all gradients in one launch, 84 with dx in slices).
+constexpr int64_t SHARED_LAUNCH_SAVES = 200;
+inline int product_ksplit(int dtype, int64_t M, int64_t N, int64_t K, int64_t ldb, int64_t saves = 0)
 {
     if (!is16(dtype) || M <= 0) return 1;
     const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE), steps = (K + 63) / 64;
     if (tiles > 256) return 1;
-    int64_t best = 1, least = 8 * steps;   // (in twentieths)
+    const bool weight = N * K >= 1 << 20, off = weight && ldb % 64 != 0;   // (a factor of less is in a cache whenever it is used)
+    const int64_t alone = off ? 10 : weight ? 9 : 8, shared = off ? 19 : weight ? 17 : 15, whole = alone + (off ? 3 : 1);
+    int64_t best = 1, least = whole * steps;
     for (int64_t ks = 2; ks <= std::min<int64_t>({512 / tiles, 16, steps / 2}); ++ks) {
-        const int64_t cost = (tiles * ks > 256 ? 15 : 8) * ((steps + ks - 1) / ks) + 100 + ks * M * N * 8 / 200000;
+        const int64_t cost = (tiles * ks > 256 ? shared : alone) * ((steps + ks - 1) / ks) + 100 + saves + ks * M * N / 21000;
         if (cost < least) { least = cost; best = ks; }
     }
     return (int)best;
@@ -326,7 +333,7 @@ SgemmArgs f32_args(bool a_kc, bool b_kc, int M, int N, const Seg* segs, int nseg
 // waiting: see Waiting; a product that is not split leaves it as it is.
 hipError_t launch_product(const GemmArgs& g, int trace_id, float* skp, hipStream_t st, Waiting* waiting = nullptr)
 {
-    const int ks = (skp && g.ldc == g.N) ? product_ksplit(DORA_BF16, g.M, g.N, g.seg[0].K) : 1;
+    const int ks = (skp && g.ldc == g.N) ? product_ksplit(DORA_BF16, g.M, g.N, g.seg[0].K, g.seg[0].ldb) : 1;
     if (ks <= 1) return launch_gemm_bf16(g, trace_id, st);
     const bool compose = g.epilogue == EPI_COMPOSE;
     GemmArgs p = g;
@@ -485,10 +492,10 @@ inline bool few_tokens(const dora_desc* d, bool one_product)
     return one_product ? r <= 128 && d->d_in >= 2048 && d->d_in <= 4096 : r <= 256 && d->d_in <= 4096;
 }
 
-// scratch for the K slices of a [tokens, n] product over k
-inline size_t slice_floats(const dora_desc* d, int64_t n, int64_t k)
+// scratch for the K slices of a [tokens, n] product over k whose N-side operand has rows of ldb
+inline size_t slice_floats(const dora_desc* d, int64_t n, int64_t k, int64_t ldb)
 {
-    const int ks = product_ksplit(d->dtype, d->tokens, n, k);
+    const int ks = product_ksplit(d->dtype, d->tokens, n, k, ldb);
     return ks > 1 ? (size_t)ks * d->tokens * n : 0;
 }
 
@@ -506,7 +513,7 @@ void plan_fwd(const dora_desc* d, Bump& b, FwdPlan& p, bool need_norm, bool need
     if (need_base_a) p.base_a = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
     // (where the K-concatenated product gives way to few_tokens, the compose pass does too)
     size_t slices = few_tokens(d, false) ? (size_t)few_tokens_h_slices(d->tokens, d->r, d->d_in) * d->tokens * d->r : 0;
-    slices = std::max({slices, slice_floats(d, d->r, d->d_in), slice_floats(d, d->d_out, d->d_in)});
+    slices = std::max({slices, slice_floats(d, d->r, d->d_in, d->d_in), slice_floats(d, d->d_out, d->d_in, d->d_in)});
     if (slices) p.skp = b.take<float>(slices);
 }
 
@@ -530,9 +537,9 @@ void plan_bwd(const dora_desc* d, Bump& b, BwdPlan& p, bool need_norm, bool need
     if (need_h) p.h = b.take_bytes((size_t)d->tokens * d->r * esize(d->dtype));
     if (need_inner) p.inner = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
     if (need_dzb) p.dzb = b.take_bytes((size_t)d->tokens * d->d_out * esize(d->dtype));
-    size_t slices = std::max(slice_floats(d, d->r, d->d_out), slice_floats(d, d->d_in, d->d_out));
-    if (need_h) slices = std::max(slices, slice_floats(d, d->r, d->d_in));
-    if (need_inner) slices = std::max(slices, slice_floats(d, d->d_out, d->d_in));
+    size_t slices = std::max(slice_floats(d, d->r, d->d_out, d->r), slice_floats(d, d->d_in, d->d_out, d->d_in));
+    if (need_h) slices = std::max(slices, slice_floats(d, d->r, d->d_in, d->d_in));
+    if (need_inner) slices = std::max(slices, slice_floats(d, d->d_out, d->d_in, d->d_in));
     if (slices) p.skp = b.take<float>(slices);
 }
 
@@ -868,7 +875,7 @@ static dora_status forward_impl(const dora_desc* desc, const void* x, const void
     // base lands in y and lora in the inner buffer; the compose pass then runs in place on both
     void* lora = saved_inner ? saved_inner : p.lora;
     Seg sx{x, d_in, W, d_in, d_in}, sa{x_lora, d_in, W, d_in, d_in};
-    if (dropout && is16(desc->dtype) && product_ksplit(desc->dtype, T, d_out, d_in) == 1) {
+    if (dropout && is16(desc->dtype) && product_ksplit(desc->dtype, T, d_out, d_in, d_in, SHARED_LAUNCH_SAVES) == 1) {
         // x W^T and x_lora W^T in one launch where their tiles fill rounds better together (2056 x 3000, 1501 tokens: 204 of 128 x
         // 128 each, one to a CU: 69 us in two launches, 56 in one)
         const int dt = dt_of(desc->dtype);
@@ -1092,7 +1099,7 @@ static dora_status backward_impl(const dora_desc* desc, const void* dy, const vo
     // 1501 tokens: 288 of 128 x 128 each, one and an eighth to a CU; together 144 of 256 x 256: 77 us in two launches, 59 in
     // one), and the weight gradients with them where CUs are left for those
     bool paired = false;
-    if (is16(dt) && T > 0 && product_ksplit(dt, T, d_in, d_out) == 1) {
+    if (is16(dt) && T > 0 && product_ksplit(dt, T, d_in, d_out, d_in, SHARED_LAUNCH_SAVES) == 1) {
         GemmArgs in[2], wg[2];
         int n = 0, nw = 0;
         if (dropout && dx) in[n++] = bf16_args(dt_of(dt), true, false, T, d_in, &sf, 1, 1.f, dx, d_in, false, 0);

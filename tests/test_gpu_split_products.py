@@ -63,3 +63,37 @@ def test_split_products_with_an_adapter_input_of_its_own(dtype, d_out, d_in):
                                 G.workspace(mod.desc, D.PHASE_BACKWARD_DROPOUT))
         for k, v in (("dx", dx), ("dx_lora", dxl), ("dA", dA), ("dB", dB), ("dm", dm)):
             G.assert_close(k, G.to_f64(v), b[k], tol)
+
+
+@pytest.mark.parametrize("d_out,d_in,r,tokens,forward,backward", [
+    (4096, 4096, 64, 512, 2, 1),    # x A^T and x W^T; dh, and all gradients in one launch
+    (4104, 4096, 72, 200, 2, 2),    # dx in slices too
+    (3000, 2056, 64, 256, 2, 2),    # rows off the lines of 128 bytes
+    (2048, 2048, 64, 512, 1, 1),    # x A^T alone; dh
+    (1024, 1024, 8, 2048, 1, 1),
+    (136, 136, 16, 300, 0, 0),      # nothing
+])
+def test_whole_or_in_slices(d_out, d_in, r, tokens, forward, backward):
+    """Launches of the reduce, and the values with them: the line between K whole and K in slices on both sides."""
+    cfg = I.DoraConfig(f"slices_{d_out}_{d_in}_{r}_{tokens}", d_out, d_in, r, tokens, "bf16", 32.0, 1e-3, seed_offset=9450)
+    mod = G.Module(cfg)
+    x, W, A, B, dy = (t.double() for t in (mod.x, mod.W, mod.A, mod.B, mod.dy))
+    c = mod.norm()
+    s, g = float(mod.inp["s"]), mod.m.double() / c.double()
+
+    def reduces(fn):
+        D.dora_trace_reset(), D.dora_trace_select(~0), D.dora_trace_enable(True)
+        out = fn()
+        D.dora_trace_enable(False), D.dora_trace_collect()
+        return out, {D.dora_trace_name(k): D.dora_trace_get(k)[1] for k in range(20)}["splitk_reduce"]
+
+    out, n = reduces(lambda: mod.forward(w_norm=c))
+    assert n == forward
+    inner = x @ W.T + s * (x @ A.T) @ B.T
+    G.assert_close("y", G.to_f64(out["y"]), G.to_f64(g * inner), G.TOL["bf16"]["tensor"])
+    grads, n = reduces(lambda: mod.backward(w_norm=c, h=out["h"], inner=out["inner"]))
+    assert n == backward
+    dz = g * dy
+    dh = s * dz @ B
+    G.assert_close("dx", G.to_f64(grads["dx"]), G.to_f64(dz @ W + dh @ A), G.TOL["bf16"]["tensor"])
+    G.assert_close("dA", G.to_f64(grads["dA"]), G.to_f64(dh.T @ x), G.TOL["bf16"]["tensor"])
