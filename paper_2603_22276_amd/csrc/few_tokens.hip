@@ -109,24 +109,28 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     uint32_t bias = 0u;
     // Everything the low-rank part and the end need is asked for ahead of the first weight rows: loads complete in order, and
     // one latency covers them all.  (Each slice of h waited for the one before, k-step after k-step, behind the first weight
-    // rows, and g's norm and magnitude for the end: 4096 x 4096, r 384, 1 token 14.7 us, 9.0 now, 3.9 TB/s; with 16 tokens the
-    // forward 22.4 -> 16.1, with 64, whose h stays out of LDS, 33.7 -> 28.3.)
+    // rows, and g's norm and magnitude for the end: forward of 4096 x 4096, r 384, weights from memory, 1 token 20.3 -> 14.1 us,
+    // 16 tokens 23.2 -> 17.1, 64, whose h stays out of LDS, 34.3 -> 29.4; with W left in a cache by the call before, 1 token, this
+    // launch alone 14.7 -> 9.0.)
     constexpr int SLICES = 8 / TB;                     // slices of h at most (few_tokens_h_slices)
-    float4 hs[TB][SLICES][2];                          // of the k-step or item under way
-    auto load_h = [&](int t, int l, float4 (&v)[SLICES][2]) {
+    // all of NS slices are asked for (the last one again past the end: cheaper than a branch at each), summed in slice order and
+    // rounded once to the storage type, as the saved tensor is
+    typedef std::integral_constant<int, SLICES> All;
+    typedef std::integral_constant<int, 1> One;
+    float4 hs[SLICES][2];                              // of the k-step or item under way
+    auto load_h = [&](auto ns, int t, int l, float4 (&v)[decltype(ns)::value][2]) {
 #pragma unroll
-        for (int z = 0; z < SLICES; ++z) {
+        for (int z = 0; z < decltype(ns)::value; ++z) {
             if (DIRECT_H && z >= p.h_slices) continue;
             const int zz = z < p.h_slices ? z : p.h_slices - 1;
             const float4* hp = reinterpret_cast<const float4*>(p.h_part + ((int64_t)zz * T + t) * p.r + l);
             v[z][0] = hp[0]; v[z][1] = hp[1];
         }
     };
-    // summed in slice order, rounded once to the storage type, as the saved tensor is
-    auto sum_h = [&](const float4 (&v)[SLICES][2]) {
+    auto sum_h = [&](auto ns, const float4 (&v)[decltype(ns)::value][2]) {
         float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int z = 0; z < SLICES; ++z)
+        for (int z = 0; z < decltype(ns)::value; ++z)
             if (z < p.h_slices) {
                 a[0] += v[z][0].x; a[1] += v[z][0].y; a[2] += v[z][0].z; a[3] += v[z][0].w;
                 a[4] += v[z][1].x; a[5] += v[z][1].y; a[6] += v[z][1].z; a[7] += v[z][1].w;
@@ -154,13 +158,13 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
         }
         if constexpr (STAGE_H) {
             const int t = (int)threadIdx.x / per0, l = (int)threadIdx.x % per0 * 8;
-            load_h(t < T ? t : T - 1, l < p.r ? l : 0, hs[0]);
+            load_h(All{}, t < T ? t : T - 1, l < p.r ? l : 0, hs);
 #pragma unroll
             for (int q = 0; q < PRE; ++q) bpre[q] = load_b(0, (wave + q * WAVES) * 32 + lq * 8);
         }
         if constexpr (DIRECT_H) {
             const int l = wave * 32 + lq * 8;
-            if (own_step && l16 < T) load_h(l16, l < p.r ? l : 0, hs[0]);
+            if (own_step && l16 < T) load_h(All{}, l16, l < p.r ? l : 0, hs);
             if (own_step) bpre[0] = load_b(0, l);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -180,8 +184,8 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
             }
             for (int i = threadIdx.x; i < T * per; i += 64 * WAVES) {
                 const int t = i / per, k = i % per * 8, l = c0 + k;
-                if (c0 > 0 || i >= 64 * WAVES) load_h(t, l < p.r ? l : 0, hs[0]);
-                uint4 o = sum_h(hs[0]);
+                if (c0 > 0 || i >= 64 * WAVES) load_h(All{}, t, l < p.r ? l : 0, hs);
+                uint4 o = sum_h(All{}, hs);
                 if (l >= p.r) o = make_uint4(0u, 0u, 0u, 0u);
                 if (p.h_out && blockIdx.x == 0 && l < p.r) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * p.r + l) = o;
                 const uint32_t at = hbuf + (uint32_t)(t * (H_RANKS * 2) + (((k >> 3) ^ t) << 4));
@@ -205,38 +209,44 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
     } else if constexpr (DIRECT_H) {
         const int l = wave * 32 + lq * 8;
         if (own_step) {
-            uint4 o = sum_h(hs[0]);                    // (tokens past T: whatever is there reaches only columns that are not stored)
+            uint4 o = sum_h(All{}, hs);                    // (tokens past T: whatever is there reaches only columns that are not stored)
             if (l >= p.r) o = make_uint4(0u, 0u, 0u, 0u);
             if (p.h_out && blockIdx.x == 0 && l < p.r && l16 < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)l16 * p.r + l) = o;
             accl[0][0] = E::mfma16(__builtin_bit_cast(bf16x8_t, bpre[0]), __builtin_bit_cast(bf16x8_t, o), accl[0][0]);
         }
     } else if constexpr (FINAL) {
         // low-rank part while the first weight rows are on their way: h and B straight from memory, the waves share the
-        // k-steps of 32
-        for (int st = wave; st * 32 < p.r; st += WAVES) {
-            const int l = st * 32 + lq * 8;
-            const bool ok = l < p.r;
-            bf16x8_t hf[TB], bfr[MR];
+        // k-steps of 32.  One slice of h, of a short d_in, is not asked for SLICES times (weights from memory: 7760 x 200, r 464,
+        // 32 tokens 16.6 us, 11.0 this way; 4096 x 512, r 512 15.3, 10.1)
+        auto low_rank = [&](auto ns) {
+            for (int st = wave; st * 32 < p.r; st += WAVES) {
+                const int l = st * 32 + lq * 8;
+                const bool ok = l < p.r;
+                bf16x8_t hf[TB], bfr[MR];
+                float4 v[TB][decltype(ns)::value][2];
 #pragma unroll
-            for (int j = 0; j < TB; ++j) {
-                const int t = j * 16 + l16;
-                load_h(t < T ? t : T - 1, ok ? l : 0, hs[j]);
+                for (int j = 0; j < TB; ++j) {
+                    const int t = j * 16 + l16;
+                    load_h(ns, t < T ? t : T - 1, ok ? l : 0, v[j]);
+                }
+#pragma unroll
+                for (int i = 0; i < MR; ++i) bfr[i] = __builtin_bit_cast(bf16x8_t, load_b(i, l));
+#pragma unroll
+                for (int j = 0; j < TB; ++j) {
+                    const int t = j * 16 + l16;
+                    uint4 o = sum_h(ns, v[j]);
+                    if (!ok) o = make_uint4(0u, 0u, 0u, 0u);
+                    hf[j] = __builtin_bit_cast(bf16x8_t, o);
+                    if (p.h_out && blockIdx.x == 0 && ok && t < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * p.r + l) = o;
+                }
+#pragma unroll
+                for (int i = 0; i < MR; ++i)
+#pragma unroll
+                    for (int j = 0; j < TB; ++j) accl[i][j] = E::mfma16(bfr[i], hf[j], accl[i][j]);
             }
-#pragma unroll
-            for (int i = 0; i < MR; ++i) bfr[i] = __builtin_bit_cast(bf16x8_t, load_b(i, l));
-#pragma unroll
-            for (int j = 0; j < TB; ++j) {
-                const int t = j * 16 + l16;
-                uint4 o = sum_h(hs[j]);
-                if (!ok) o = make_uint4(0u, 0u, 0u, 0u);
-                hf[j] = __builtin_bit_cast(bf16x8_t, o);
-                if (p.h_out && blockIdx.x == 0 && ok && t < T) *reinterpret_cast<uint4*>(p.h_out + (int64_t)t * p.r + l) = o;
-            }
-#pragma unroll
-            for (int i = 0; i < MR; ++i)
-#pragma unroll
-                for (int j = 0; j < TB; ++j) accl[i][j] = E::mfma16(bfr[i], hf[j], accl[i][j]);
-        }
+        };
+        if (p.h_slices == 1) low_rank(One{});
+        else low_rank(All{});
     }
 
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_cptr_t)ring;
