@@ -173,10 +173,10 @@ dora_status dora_compose_backward(const dora_desc* desc, const void* dy, const v
 /*
  * The three forward contractions on their own (App. A item 1): base = x W^T [tokens, d_out],
  * h = x A^T [tokens, r], lora = h B^T [tokens, d_out], each rounded once to `dtype`.
- * DORA_F32, and DORA_F16 beyond a few tokens: the launches dora_forward makes for these steps, except that without
- * a workspace no product is split along K (dora_forward splits base and h when their tiles would leave most of the
- * chip idle).  dora_forward in DORA_BF16 and of a few tokens forms y in other launches, with fewer roundings.  Needs
- * no workspace.
+ * DORA_F16 beyond a few tokens: the launches dora_forward makes for these steps, except that without a workspace no
+ * product is split along K (dora_forward splits base and h when their tiles would leave most of the chip idle).
+ * DORA_F32: the same sums, but dora_forward composes lora as it is stored.  dora_forward in DORA_BF16 and of a few
+ * tokens forms y in other launches, with fewer roundings.  Needs no workspace.
  */
 dora_status dora_project(const dora_desc* desc, const void* x, const void* W, const void* A, const void* B,
                          void* base, void* h, void* lora, void* stream);
@@ -184,7 +184,8 @@ dora_status dora_project(const dora_desc* desc, const void* x, const void* W, co
 /*
  * Whole forward of the module (App. A item 1): norm (unless w_norm is given), g,
  * base = x W^T, h = x A^T, lora = h B^T, compose;  y = base + delta = g (.) (base + s*lora).
- * DORA_BF16 runs the K-concatenated product of dora_forward_fused; DORA_F16 and DORA_F32 run base, lora and a compose pass.
+ * DORA_BF16 runs the K-concatenated product of dora_forward_fused; DORA_F16 runs base, lora and a compose pass, DORA_F32 base
+ * and a lora that is composed as it is stored.
  * Up to 64 tokens in either 16-bit type: two launches that stream A and W once, where they are the faster ones.
  *   x [tokens, d_in], W, A, B : const `dtype`.   m : const fp32 [d_out].
  *   w_norm : const fp32 [d_out] or NULL (NULL: computed here into the workspace).
@@ -223,6 +224,7 @@ dora_status dora_forward_fused(const dora_desc* desc, const void* x, const void*
  *   here - the gradient-checkpointing pattern).
  *   dx : out `dtype` [tokens, d_in].  dA : out fp32 [r, d_in].  dB : out fp32 [d_out, r].
  *   dm : out fp32 [d_out] or NULL (frozen magnitude).  Any of dx, dA, dB may be NULL to skip it.
+ *   dx may lie over dy; other outputs and inputs lie apart.
  */
 dora_status dora_backward(const dora_desc* desc, const void* dy, const void* x, const void* W,
                           const void* A, const void* B, const float* m, const float* w_norm,
@@ -241,7 +243,7 @@ dora_status dora_backward(const dora_desc* desc, const void* dy, const void* x, 
  * [tokens, d_out] scratch tensor inside the workspace, DORA_PHASE_FORWARD_DROPOUT.)
  * Backward, norm constant:  dx = dy W (frozen path),  dx_lora = ((g-1) (.) dy) W + dh A,  dh = s (g (.) dy) B,
  * dA = dh^T x_lora,  dB = s (g (.) dy)^T h,  dm = (sum_t dy * inner) / max(w_norm, eps); the caller applies
- * its dropout mask to dx_lora and adds it to dx.  dx, dx_lora, dA, dB, dm may each be NULL.  saved_h /
+ * its dropout mask to dx_lora and adds it to dx (dx_lora may lie over dy).  dx, dx_lora, dA, dB, dm may each be NULL.  saved_h /
  * saved_inner as written by dora_forward_dropout, or NULL (recomputed from x_lora).  With x_lora == x the
  * results are those of dora_forward / dora_backward (dx + dx_lora = dx of the plain module).
  */

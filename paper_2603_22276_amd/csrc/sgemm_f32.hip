@@ -1,6 +1,6 @@
-// fp32 GEMM of the fp32 configuration of the module, on v_mfma_f32_16x16x4_f32 (fp32 products and sums, no narrower
-// type anywhere).  One pair of kernels serves every contraction of the forward and backward (x W^T, x A^T, h B^T, dz B,
-// dz W + dh A, dh^T x, dz^T h) and of Algorithm 1 (W A^T, A A^T, B G); an operand is row-major [rows, K] (K-contiguous) or
+// fp32 module on v_mfma_f32_16x16x4_f32 (fp32 products and sums, no narrower type anywhere).  f32_kernel takes the products of the
+// forward and backward (x W^T, x A^T, h B^T, dz B, dz W + dh A, dh^T x, dz^T h) and A A^T where it is asked for, up to three of
+// them and dm's column sum in a launch; norm_f32_kernel the row norm.  An operand is row-major [rows, K] (K-contiguous) or
 // row-major [K, rows] (K-strided), its row stride and the extent of its contiguous axis multiples of four elements.
 //
 // A lane (m = lane & 15, q = lane >> 4) of the MFMA supplies one k.  Both operands take k = 4 q + j for the j-th of four
@@ -11,7 +11,8 @@
 //
 // Bound: launches and the latency of a chain of loads for small modules, the matrix cores (157 TFLOP/s) and the last round of
 // tiles for larger ones.  Forward and backward of 256 x 512, r 16, 64 tokens take five launches, 29 us (eleven, one for each
-// product and pass, 49), of 1000 x 772, r 36, 1500 tokens 117 us (171); 43 shapes 1.02 to 1.66 times faster.
+// product and pass, 49), of 1000 x 772, r 36, 1500 tokens 118 us (171), of 256 x 512, r 64, 8192 tokens 167 (196), of 4096 x 4096,
+// r 384, 2048 tokens 1950 (2070); 43 shapes 1.02 to 1.84 times faster than the eleven.
 #include "common.hpp"
 
 #include <algorithm>
