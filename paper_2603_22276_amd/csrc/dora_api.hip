@@ -278,11 +278,12 @@ void plan_norm(const dora_desc* d, Bump& b, NormPlan& n)
 // a slice 8 while every workgroup has a CU to itself and 15 where two share one, with a weight of 2 MB and more 9 and 17 (10 and 19
 // where its rows do not start at lines of 128 bytes), one more while K is whole (there three), when too few loads are in flight for
 // what comes from memory; 100 for the reduce launch, and the partials written and read at 3.4 TB/s.  At most two workgroups per CU,
-// 16 slices, and two K steps to a slice at least.  (Forward, us with weights from memory / left in a cache: 512 tokens, 4096 x 4096, r 64 with K whole 57 / 43, in
-// two slices 51 / 44; 256 tokens, 3000 x 2056 46 / 29, in three 36 / 32; 512 tokens, 4096 x 4104 72 / 58, in two 58 / 57.  247
-// forwards and backwards of 65 to 2048 tokens are within 0.9 % of the best number of slices with weights from memory and 0.5 % in a
-// cache, those with rows off the lines 1.4 % and 1.0 %.  x A^T of 512 tokens, K 4096, r 64 in one slice 11.9 us, 7.2 in 16; of 4096
-// tokens, r 384, in two slices and in five, K 4096 42 and 48 us, 14336 106 and 94, 27648 181 and 156.)
+// 16 slices, and two K steps to a slice at least.  (Forward, us with weights from memory / left in a cache: 512 tokens, 4096 x
+// 4096, r 64 with K whole 57 / 43, in two slices 51 / 44; 256 tokens, 3000 x 2056 46 / 29, in three 36 / 32; 512 tokens, 4096 x 4104
+// 72 / 58, in two 58 / 57.  247 forwards and backwards of 65 to 2048 tokens are within 0.9 % of the best number of slices with
+// weights from memory and 0.5 % in a cache, those with rows off the lines 1.4 % and 1.0 %.  x A^T of 512 tokens, K 4096, r 64 in one
+// slice 11.9 us, 7.2 in 16; of 4096 tokens, r 384, in two slices and in five, K 4096 42 and 48 us, 14336 106 and 94, 27648 181 and
+// 156.)
 // saves: what K whole would save beside, where the product could share a launch with others (a launch and a round of its own, 10 us:
 // step of 2048 x 2048, r 64, 512 tokens 75 us with all gradients in one launch, 84 with dx in slices).
 constexpr int64_t SHARED_LAUNCH_SAVES = 200;
