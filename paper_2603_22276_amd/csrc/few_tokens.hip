@@ -245,8 +245,8 @@ __global__ __launch_bounds__(64 * WAVES) void few_tokens_kernel(FewTokensArgs p)
                     for (int j = 0; j < TB; ++j) accl[i][j] = E::mfma16(bfr[i], hf[j], accl[i][j]);
             }
         };
-        if (p.h_slices == 1) low_rank(One{});
-        else low_rank(All{});
+        if (__builtin_expect(p.h_slices > 1, 1)) low_rank(All{});
+        else low_rank(One{});
     }
 
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_cptr_t)ring;
